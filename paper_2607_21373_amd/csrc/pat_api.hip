@@ -1082,17 +1082,41 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
     UP(to_f32(dtm), dtm32);
     UP(to_f32(hp.sw), sw32);
     UP(to_f32(hp.injw), injw32);
-    UP(hp.ell_col, ell_col);
-    UP(hp.xptr, xptr);
+    {
+        // the device keeps a row's 16 padded slots (and a boundary row's first 16 B values)
+        // in quad order; the halo tiles below are built from the plain slot order
+        constexpr int W = pat::HostProblem::kEll;
+        auto quads = [](const auto &v, const std::vector<int64_t> &at) {
+            auto o = v;
+            for (int64_t b : at)
+                for (int j = 0; j < W; ++j) o[size_t(b + 4 * (j % 4) + j / 4)] = v[size_t(b + j)];
+            return o;
+        };
+        std::vector<int64_t> rows, brows;
+        std::vector<int32_t> rspec(size_t(hp.n), 0);
+        std::vector<int4> spec;
+        for (int32_t i = 0; i < hp.n; ++i) {
+            rows.push_back(int64_t(i) * W);
+            if (hp.bsoff[i] >= 0) brows.push_back(hp.bsoff[i]);
+            if (hp.bsoff[i] >= 0 || hp.xptr[i + 1] > hp.xptr[i] || hp.injptr[i + 1] > hp.injptr[i]) {
+                spec.push_back(int4{std::max(hp.bsoff[i], 0), hp.bnum[i], hp.xptr[i], hp.xptr[i + 1]});
+                spec.push_back(int4{hp.injptr[i], hp.injptr[i + 1], 0, 0});
+                rspec[i] = int32_t(spec.size() / 2);
+            }
+        }
+        const std::vector<double> val = quads(hp.ell_val, rows), bval = quads(hp.bslot, brows);
+        UP(quads(hp.ell_col, rows), ell_col);
+        UP(rspec, rspec);
+        UP(spec, spec);
+        UP(val, ell_val64);
+        UP(bval, bslot64);
+        UP(to_f32(val), ell_val32);
+        UP(to_f32(bval), bslot32);
+    }
     UP(hp.xcol, xcol);
     UP(hp.bsoff, bsoff);
-    UP(hp.bnum, bnum);
-    UP(hp.ell_val, ell_val64);
     UP(hp.xval, xval64);
-    UP(hp.bslot, bslot64);
-    UP(to_f32(hp.ell_val), ell_val32);
     UP(to_f32(hp.xval), xval32);
-    UP(to_f32(hp.bslot), bslot32);
     {
         pat::HaloTiles ht;
         pat::build_halo_tiles(hp, ht);

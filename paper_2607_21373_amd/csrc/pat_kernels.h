@@ -17,8 +17,13 @@ struct DevOps {
     const int32_t *snode = nullptr, *injptr = nullptr, *injs = nullptr, *perm = nullptr;
     const double *dtm64 = nullptr, *sqrtm = nullptr, *isqrtm = nullptr, *sw64 = nullptr, *injw64 = nullptr;
     const float *dtm32 = nullptr, *sw32 = nullptr, *injw32 = nullptr;
-    // padded row layout of K for the time-step kernels
-    const int32_t *ell_col = nullptr, *xptr = nullptr, *xcol = nullptr, *bsoff = nullptr, *bnum = nullptr;
+    // padded row layout of K for the time-step kernels: a row's 16 slots in quad order
+    // (slot p + 4 i at 4 p + i), likewise the first 16 B values of a boundary row
+    const int32_t *ell_col = nullptr, *xcol = nullptr, *bsoff = nullptr;
+    // per row 0, or 1 + the index of its record in spec: {first B value, bnum, first and end
+    // of the entries beyond the padded slots}, {first and end of the sensor weights, 0, 0}
+    const int32_t *rspec = nullptr;
+    const int4 *spec = nullptr;
     const double *ell_val64 = nullptr, *xval64 = nullptr, *bslot64 = nullptr;
     const float *ell_val32 = nullptr, *xval32 = nullptr, *bslot32 = nullptr;
     // halo tiles of the float32 step kernels (HaloTiles)

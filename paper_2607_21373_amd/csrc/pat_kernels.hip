@@ -61,38 +61,64 @@ __device__ __forceinline__ double lane_sum(double v) {
     return v;
 }
 
-// Row operands of the padded layout (see HostProblem::kEll): slot j < 16 of row i
-// at i*16 + j, the entries beyond 16 in (xptr, xcol, xval), and for boundary rows
-// the B value of each slot at bslot[bsoff[i] + slot].
+// Row operands of the padded layout (see HostProblem::kEll) as the device holds it:
+// slot j = p + 4 i of row r's 16 at r*16 + 4 p + i (quad p = every fourth slot), so
+// that one 16-byte load gives a lane the columns (or float32 weights) of the four
+// slots it sums or hands out.  Entries beyond 16 in (xptr, xcol, xval); boundary rows
+// hold the B value of each slot at bslot[bsoff[row]], in the same quad order, then
+// the entries beyond 16.  rspec[row] is 0 for the rows with nothing but their padded
+// slots, so that most rows read one word for all of that; any other row's extra ranges
+// are record rspec[row] - 1 of `spec`, loaded while the first gathers are in flight.
 template <typename T>
 struct RowOps {
-    const int32_t *ecol, *xptr, *xcol, *bsoff;
+    const int32_t *ecol, *xcol;
     const T *eval, *xval, *bslot, *dtm;
-    const int32_t *bnum;  // boundary rows: slots with a nonzero B come first, bnum of them
+    const int32_t *rspec;
+    const int4 *spec;
+    const int32_t *bsoff;  // boundary rows of the halo kernels with more than 16 B values
+};
+// B values from bslot[bo], nb slots of them nonzero (nb = 0: interior row); entries
+// beyond the padded slots [x0, x1); sensor weights [e0, e1)
+struct RowSpec {
+    int bo = 0, nb = 0, x0 = 0, x1 = 0, e0 = 0, e1 = 0;
+    __device__ __forceinline__ void load(const int4 *spec, int k) {
+        const int4 u = spec[2 * (k - 1)], v = spec[2 * (k - 1) + 1];
+        bo = u.x; nb = u.y; x0 = u.z; x1 = u.w;
+        e0 = v.x; e1 = v.y;
+    }
 };
 
-// Operands of one row as seen by one lane: its padded slots' columns and
-// weights, the boundary-slot offset, the overflow range and dt/m.
+// the four values of one quad
+template <typename T>
+__device__ __forceinline__ void load_quad(const T *p, T v[4]) {
+    if constexpr (sizeof(T) == 4) {
+        const auto q = *reinterpret_cast<const T __attribute__((ext_vector_type(4))) *>(p);
+        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+    } else {
+        using V2 = T __attribute__((ext_vector_type(2)));
+        const V2 q0 = reinterpret_cast<const V2 *>(p)[0], q1 = reinterpret_cast<const V2 *>(p)[1];
+        v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
+    }
+}
+
+// Operands of one row as seen by one lane of the scalar-lane kernels: its quad of
+// padded slots (part, part + 4, ...), the row's special record and dt/m.
 template <typename T, int RB>
 struct RowMeta {
     int c[Geo<RB>::PER];
     T w[Geo<RB>::PER];
-    int bo, x0, x1;
+    int sp;
     T dm;
 };
 
 template <typename T, int RB>
 __device__ __forceinline__ void load_meta(const RowOps<T> &o, int row, int part, RowMeta<T, RB> &m) {
     using G = Geo<RB>;
-    const int64_t eb = int64_t(row) * G::W;
-#pragma unroll
-    for (int j = 0; j < G::PER; ++j) {
-        m.c[j] = o.ecol[eb + part + j * G::SPLIT];
-        m.w[j] = o.eval[eb + part + j * G::SPLIT];
-    }
-    m.bo = o.bsoff[row];
-    m.x0 = o.xptr[row];
-    m.x1 = o.xptr[row + 1];
+    static_assert(G::SPLIT == 4 && G::PER == 4, "one quad of slots per lane");
+    const int64_t eb = int64_t(row) * G::W + 4 * part;
+    load_quad(o.ecol + eb, m.c);
+    load_quad(o.eval + eb, m.w);
+    m.sp = o.rspec[row];
     m.dm = o.dtm[row];
 }
 
@@ -119,32 +145,32 @@ __device__ __forceinline__ T adj_result(T cur, T prev, T acc, T bacc, T src, T d
 // acc = sum over the row's entries of K(row, k) X[col_k][r], and for a boundary row
 // bacc = sum of B(row, k) bdiff(X[col_k][r], Y[col_k][r]).  All PER gathers of the
 // lane are issued before any is consumed; sums run in slot order, then the entries
-// beyond 16.
+// beyond 16.  rs receives the row's record.
 template <typename T, int RB>
 __device__ __forceinline__ void row_sums(const RowOps<T> &o, const RowMeta<T, RB> &m, int part, int r,
-                                         const T *__restrict__ X, const T *__restrict__ Y, bool with_b,
-                                         bool only_prev, T &acc, T &bacc) {
+                                         const T *__restrict__ X, const T *__restrict__ Y, bool only_prev, T &acc,
+                                         T &bacc, RowSpec &rs) {
     using G = Geo<RB>;
     T x[G::PER];
 #pragma unroll
     for (int j = 0; j < G::PER; ++j) x[j] = X[int64_t(m.c[j]) * RB + r];
+    if (m.sp) rs.load(o.spec, m.sp);
 #pragma unroll
     for (int j = 0; j < G::PER; ++j) acc = mad(m.w[j], x[j], acc);
-    if (with_b) {
-        const T *Bv = o.bslot + m.bo;
+    if (!m.sp) return;
+    if (rs.nb) {
         T bw[G::PER], y[G::PER];
-#pragma unroll
-        for (int j = 0; j < G::PER; ++j) bw[j] = Bv[part + j * G::SPLIT];
+        load_quad(o.bslot + rs.bo + 4 * part, bw);
 #pragma unroll
         for (int j = 0; j < G::PER; ++j) y[j] = Y[int64_t(m.c[j]) * RB + r];
 #pragma unroll
         for (int j = 0; j < G::PER; ++j) bacc = mad(bw[j], bdiff(x[j], y[j], only_prev), bacc);
     }
-    for (int k = m.x0 + part; k < m.x1; k += G::SPLIT) {
+    for (int k = rs.x0 + part; k < rs.x1; k += G::SPLIT) {
         const int64_t cj = int64_t(o.xcol[k]) * RB + r;
         const T xv = X[cj];
         acc = mad(o.xval[k], xv, acc);
-        if (with_b) bacc = mad(o.bslot[m.bo + G::W + (k - m.x0)], bdiff(xv, Y[cj], only_prev), bacc);
+        if (rs.nb) bacc = mad(o.bslot[rs.bo + G::W + (k - rs.x0)], bdiff(xv, Y[cj], only_prev), bacc);
     }
 }
 
@@ -179,7 +205,8 @@ __global__ void __launch_bounds__(256) k_fwd(const FwdArgs<T> a) {
         load_meta<T, RB>(a.o, row, part, m);
         const int64_t id = int64_t(row) * RB + r;
         T acc = T(0), bacc = T(0);
-        row_sums<T, RB>(a.o, m, part, r, a.S, a.Sp, m.bo >= 0, false, acc, bacc);
+        RowSpec rs;
+        row_sums<T, RB>(a.o, m, part, r, a.S, a.Sp, false, acc, bacc, rs);
         acc = lane_sum<RB, G::LPR>(acc);
         bacc = lane_sum<RB, G::LPR>(bacc);
         if (part == 0) a.Sn[id] = step_update(a.S[id], a.Sp[id], acc, bacc, T(0), m.dm, a.dt);
@@ -211,16 +238,6 @@ struct AdjArgs {
     T dt;
 };
 
-// Rows with sensor weights are few (four per sensor at most): one wave-uniform
-// test of the injection range of the wave's rows [r0, r0 + nrows) lets waves
-// without any skip the per-row range loads.
-__device__ __forceinline__ bool wave_injects(const int32_t *injptr, int r0, int nrows, int n) {
-    const int w0 = __builtin_amdgcn_readfirstlane(r0);
-    if (w0 >= n) return false;
-    const int w1 = w0 + nrows < n ? w0 + nrows : n;
-    return injptr[w0] != injptr[w1];
-}
-
 // (Pi^T (yhat^{ta} + yhat^{tb}))_row for RHS r over the row's injection entries
 // [e0, e1) (yhat^{ta} left out for ta < 0)
 template <typename T, typename YT, int RB>
@@ -244,32 +261,26 @@ __device__ __forceinline__ T inject(const AdjArgs<T> &a, int row, int r) {
 // - inj/2), inj = Pi^T (yhat^{ta} + yhat^{tb}); with `last`, the result
 // (q_k - q_{k-1}) m/dt - (dt K q_k - B q_{k-1} - inj/2), inj = Pi^T yhat^{tb}.
 // One tile of RPB rows per workgroup, each XCD's range walked from its end
-// (xcd_tile_rev).  The injection range is loaded with the row operands, a round
-// trip earlier than after the sums.
+// (xcd_tile_rev).
 template <typename T, typename YT, int RB>
 __global__ void __launch_bounds__(256) k_adj(const AdjArgs<T> a) {
     using G = Geo<RB>;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
     const int part = (lane / RB) % G::SPLIT, r = lane % RB;
     const int wrow0 = xcd_tile_rev(blockIdx.x, gridDim.x) * G::RPB + wave * G::RPW;
-    const bool winj = wave_injects(a.injptr, wrow0, G::RPW, a.n);
     const int row = wrow0 + lane / G::LPR;
     if (row >= a.n) return;
     RowMeta<T, RB> m;
     load_meta<T, RB>(a.o, row, part, m);
-    int e0 = 0, e1 = 0;
-    if (winj) {
-        e0 = a.injptr[row];
-        e1 = a.injptr[row + 1];
-    }
     const int64_t id = int64_t(row) * RB + r;
     T kq = T(0), bq = T(0);
-    row_sums<T, RB>(a.o, m, part, r, a.S, a.Sp, m.bo >= 0, a.last, kq, bq);
+    RowSpec rs;
+    row_sums<T, RB>(a.o, m, part, r, a.S, a.Sp, a.last, kq, bq, rs);
     kq = lane_sum<RB, G::LPR>(kq);
     bq = lane_sum<RB, G::LPR>(bq);
     if (part == 0) {
         const T cur = a.S[id], prev = a.Sp[id];
-        const T src = winj ? T(0.5) * inject_range<T, YT, RB>(a, e0, e1, r) : T(0);
+        const T src = T(0.5) * inject_range<T, YT, RB>(a, rs.e0, rs.e1, r);
         a.Sn[id] = a.last ? adj_result(cur, prev, kq, bq, src, m.dm, a.dt)
                           : step_update(cur, prev, kq, bq, src, m.dm, a.dt);
     }
@@ -280,9 +291,18 @@ __global__ void __launch_bounds__(256) k_adj(const AdjArgs<T> a) {
 //
 // Each lane moves 16 bytes (VEC = 4 floats or 2 doubles, i.e. VEC right-hand
 // sides), a lane group of LPR = RB / VEC lanes owns one row, and one wave64
-// instruction gathers 64/LPR neighbour rows at once.  The padded row operands
-// of a tile (column, stiffness and boundary weight per slot, dt/m, overflow
-// range) are staged in LDS once per tile and read back as LDS broadcasts.
+// instruction gathers 64/LPR neighbour rows at once.  A row's padded operands are
+// held in registers by HL = min(LPR, 4) of its lanes (each quad of lanes holds a
+// copy in wider rows), loaded with 16-byte accesses and handed to the others slot
+// by slot by DPP quad permutes.
+//
+// Bound: the chain operands -> gathers (-> boundary gathers) of each wave, then the
+// traffic.  Operands staged in LDS for the whole tile (a round trip and two barriers
+// more per tile, and for 16-byte rows 82 KiB of LDS per workgroup, one workgroup per
+// CU) took 29.2 us per forward step of 4 float32 RHS on the 195,112-node ball against
+// 10.3 us here (34 MB, 3.3 TB/s); 19.2 -> 12.6 us at 8 RHS, 19.0 -> 15.7 at 16 (63 MB,
+// 4.0 TB/s), 25.5 -> 23.0 at 32; float64: 42.5 -> 13.9 us at 2 RHS, 21.5 -> 16.6 at 8,
+// 43.2 -> 41.9 at 32.
 // ---------------------------------------------------------------------------
 
 template <typename T>
@@ -300,16 +320,15 @@ struct Vec16<double> {
 
 // Gathers in flight per lane before they are consumed.
 constexpr int kGatherChunk = 8;
-// Waves per SIMD the register allocation of the step kernels must allow: 8 for
-// float32 state, 5 for float64; capped by what the tile's LDS image allows
-// (160 KiB per CU; one 4-wave workgroup per tile, one wave per SIMD).
-template <typename T, int RB, typename Ops>
+// Waves per SIMD the register allocation of the step kernels must allow.  Rows of 16
+// or 32 bytes put 64 or 32 rows on a wave, so a launch has few waves and takes the
+// registers; wider rows need the waves (two chunks of eight gathers and the four-slot
+// boundary chunks fit 96 registers).
+template <typename T, int RB>
 constexpr int vwaves() {
-    const int want = sizeof(T) == 4 ? 8 : 5;
-    const int lds = int(163840 / sizeof(Ops));
-    return want < lds ? want : (lds > 0 ? lds : 1);
+    return RB * sizeof(T) <= 32 ? 2 : 5;
 }
-#define PAT_VOCC(T, RB) __attribute__((amdgpu_waves_per_eu(vwaves<T, RB, TileOps<T, RB>>())))
+#define PAT_VOCC(T, RB) __attribute__((amdgpu_waves_per_eu(vwaves<T, RB>())))
 
 // Stores of the new state and loads of a row's own state (each touched once per
 // step).  When the step's state exceeds the Infinity Cache (`stream`), they are
@@ -338,50 +357,64 @@ struct VGeo {
     static constexpr int RPW = 64 / LPR;     // rows per wave
     static constexpr int RPB = 4 * RPW;      // rows per 256-thread workgroup (one tile)
     static constexpr int W = 16;             // padded slots per row
+    static constexpr int HL = LPR < 4 ? LPR : 4;  // lanes that share a row's padded operands
+    static constexpr int QPL = 4 / HL;            // quads of slots per lane
 };
 
-// LDS image of one tile's row operands.
-template <typename T, int RB>
-struct TileOps {
-    using G = VGeo<T, RB>;
-    int col[G::RPB * G::W];
-    T kv[G::RPB * G::W];
-    T bv[G::RPB * G::W];
-    T dm[G::RPB];
-    int bo[G::RPB], bn[G::RPB], x0[G::RPB], x1[G::RPB];
-};
-
-// Stage the operands of rows [row0, row0 + RPB) (rows >= n get zero weights); the
-// B values when need_b (every step of the three-level form needs them).
-// Contains __syncthreads(); every thread of the workgroup must call it.
-template <typename T, int RB>
-__device__ __forceinline__ void stage_tile(const RowOps<T> &o, int n, int row0, bool need_b, TileOps<T, RB> &L) {
-    using G = VGeo<T, RB>;
-    for (int e = threadIdx.x; e < G::RPB * G::W; e += 256) {
-        const int rw = row0 + e / G::W;
-        const bool ok = rw < n;
-        const int64_t src = int64_t(ok ? rw : 0) * G::W + e % G::W;
-        L.col[e] = ok ? o.ecol[src] : 0;
-        L.kv[e] = ok ? o.eval[src] : T(0);
-    }
-    for (int e = threadIdx.x; e < G::RPB; e += 256) {
-        const int rw = row0 + e;
-        const bool ok = rw < n;
-        L.bo[e] = ok ? o.bsoff[rw] : -1;
-        L.bn[e] = ok ? o.bnum[rw] : 0;
-        L.x0[e] = ok ? o.xptr[rw] : 0;
-        L.x1[e] = ok ? o.xptr[rw + 1] : 0;
-        L.dm[e] = ok ? o.dtm[rw] : T(0);
-    }
-    __syncthreads();
-    if (need_b) {
-        for (int e = threadIdx.x; e < G::RPB * G::W; e += 256) {
-            const int bo = L.bo[e / G::W];
-            L.bv[e] = bo >= 0 ? o.bslot[bo + e % G::W] : T(0);
-        }
-        __syncthreads();
+// Compile-time loop: f(std::integral_constant<int, I>) for I = B, B + S, ... < E.
+template <int B, int E, int S = 1, typename F>
+__device__ __forceinline__ void static_for(F &&f) {
+    if constexpr (B < E) {
+        f(std::integral_constant<int, B>{});
+        static_for<B + S, E, S>(f);
     }
 }
+
+// lane H of each group of HL neighbouring lanes, to the whole group (DPP quad permute;
+// every lane of a group works on the same row, so none of them is ever off alone)
+template <int HL, int H>
+__device__ __forceinline__ uint32_t group_bcast(uint32_t x) {
+    if constexpr (HL == 1) {
+        return x;
+    } else {
+        constexpr int ctrl = HL == 4 ? H * 0x55 : H ? 0xF5 : 0xA0;
+        return uint32_t(__builtin_amdgcn_update_dpp(0, int(x), ctrl, 0xF, 0xF, true));
+    }
+}
+template <int HL, int H>
+__device__ __forceinline__ int group_bcast(int x) { return int(group_bcast<HL, H>(uint32_t(x))); }
+template <int HL, int H>
+__device__ __forceinline__ float group_bcast(float x) {
+    return __uint_as_float(group_bcast<HL, H>(__float_as_uint(x)));
+}
+template <int HL, int H>
+__device__ __forceinline__ double group_bcast(double x) {
+    const unsigned long long b = static_cast<unsigned long long>(__double_as_longlong(x));
+    const unsigned long long lo = group_bcast<HL, H>(uint32_t(b)), hi = group_bcast<HL, H>(uint32_t(b >> 32));
+    return __longlong_as_double(static_cast<long long>(hi << 32 | lo));
+}
+
+// v is needed here: keeps the compiler from moving its computation further down
+template <typename VT>
+__device__ __forceinline__ void pin(VT &v) { asm volatile("" : "+v"(v)); }
+
+// One value per padded slot of a row, held in quads by the row's lanes (RowOps).
+template <typename T, int RB, typename U>
+struct SlotRegs {
+    using G = VGeo<T, RB>;
+    U v[4 * G::QPL];
+    // lane q of the row; p: the row's 16 values in quad order
+    __device__ __forceinline__ void load(const U *p, int q) {
+#pragma unroll
+        for (int k = 0; k < G::QPL; ++k) load_quad(p + 4 * ((q % G::HL) * G::QPL + k), v + 4 * k);
+    }
+    // slot J: quad J % 4, element J / 4 of it
+    template <int J>
+    __device__ __forceinline__ U get() const {
+        constexpr int p = J % 4, i = J / 4;
+        return group_bcast<G::HL, p / G::QPL>(v[4 * (p % G::QPL) + i]);
+    }
+};
 
 template <typename VT, typename T>
 __device__ __forceinline__ VT vfma(T w, VT x, VT acc) {
@@ -391,77 +424,100 @@ __device__ __forceinline__ VT vfma(T w, VT x, VT acc) {
     return o;
 }
 
-// acc += sum_slots K(row, slot) X[col][q-th vector]; with_b: bacc += B(row, slot)
-// bdiff(X[col], Y[col]).  The B sums (boundary rows only) run after the K sums have
-// been consumed, with their own gathers, so the two sets of gathers are never live
+// acc += sum_slots K(row, slot) X[col][q-th vector]; for boundary rows bacc +=
+// B(row, slot) bdiff(X[col], Y[col]).  The B sums run after the K sums have been
+// consumed, with their own gathers, so the two sets of gathers are never live
 // together and the kernel keeps the register budget (and occupancy) of the interior
 // rows.  Slot 0 of every row is its diagonal, so the first gather is the row's own
-// X value; it is returned in `own`.
+// X value; it is returned in `own`.  sp: the row's rspec, its record is returned in rs.
 template <typename T, int RB>
-__device__ __forceinline__ void vrow_sums(const RowOps<T> &o, const TileOps<T, RB> &L, int lr, int q,
-                                          const T *__restrict__ X, const T *__restrict__ Y, bool with_b,
-                                          bool only_prev, typename Vec16<T>::t &acc, typename Vec16<T>::t &bacc,
-                                          typename Vec16<T>::t &own) {
+__device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, const T *__restrict__ X,
+                                          const T *__restrict__ Y, bool only_prev, typename Vec16<T>::t &acc,
+                                          typename Vec16<T>::t &bacc, typename Vec16<T>::t &own,
+                                          const SlotRegs<T, RB, int> &off, const SlotRegs<T, RB, T> &kv, RowSpec &rs) {
     using G = VGeo<T, RB>;
     using VT = typename Vec16<T>::t;
-    const int base = lr * G::W;
     constexpr int CH = kGatherChunk;
     // 32-bit byte offsets from the uniform bases (state arrays are < 4 GiB)
     const char *Xc = reinterpret_cast<const char *>(X);
     const char *Yc = reinterpret_cast<const char *>(Y);
     const uint32_t qoff = uint32_t(q) * 16u;
     constexpr uint32_t ROWB = uint32_t(RB * sizeof(T));
-#pragma unroll
-    for (int j0 = 0; j0 < G::W; j0 += CH) {
+    static_for<0, G::W, CH>([&](auto J0) {
+        constexpr int j0 = decltype(J0)::value;
         VT x[CH];
-#pragma unroll
-        for (int j = 0; j < CH; ++j)
-            x[j] = *reinterpret_cast<const VT *>(Xc + (uint32_t(L.col[base + j0 + j]) * ROWB + qoff));
-        if (j0 == 0) own = x[0];
-#pragma unroll
-        for (int j = 0; j < CH; ++j) acc = vfma(L.kv[base + j0 + j], x[j], acc);
-    }
-    const int x0 = L.x0[lr], x1 = L.x1[lr];
-    for (int k = x0; k < x1; ++k) {
+        static_for<0, CH>([&](auto J) {
+            constexpr int j = j0 + decltype(J)::value;
+            x[J.value] = *reinterpret_cast<const VT *>(Xc + (uint32_t(off.template get<j>()) + qoff));
+        });
+        if constexpr (j0 == 0) {
+            own = x[0];
+            if (sp) rs.load(o.spec, sp);
+        }
+        static_for<0, CH>([&](auto J) {
+            constexpr int j = j0 + decltype(J)::value;
+            acc = vfma(kv.template get<j>(), x[J.value], acc);
+        });
+    });
+    pin(acc);  // the sums end here: moved further down, they would keep the gathers live
+    if (!sp) return;
+    for (int k = rs.x0; k < rs.x1; ++k) {
         const VT xv = *reinterpret_cast<const VT *>(Xc + (uint32_t(o.xcol[k]) * ROWB + qoff));
         acc = vfma(o.xval[k], xv, acc);
     }
-    if (with_b) {
-        // only the row's first bnum slots carry B; re-read the slot operands from LDS
-        // instead of keeping them live across the K sums
-        int bbase = base;
-        asm volatile("" : "+v"(bbase));
-        const int nb = L.bn[lr];
-        constexpr int BCH = CH / 4;  // two gathers per slot
-#pragma unroll
-        for (int j0 = 0; j0 < G::W; j0 += BCH) {
+    if (rs.nb) {
+        // only the row's first bnum slots carry B; the neighbours' X values are read again
+        // (the asm hides that) instead of staying live across the K sums
+        uint32_t boff = qoff;
+        asm volatile("" : "+v"(boff));
+        const int nb = rs.nb;
+        SlotRegs<T, RB, T> bv;
+        bv.load(o.bslot + rs.bo, q);
+        constexpr int BCH = G::HL < 4 ? 8 : 4;  // slots at a time, two gathers each
+        static_for<0, G::W, BCH>([&](auto J0) {
+            constexpr int j0 = decltype(J0)::value;
             if (j0 < nb) {
-                VT y[BCH];
-#pragma unroll
-                for (int j = 0; j < BCH; ++j) {
-                    y[j] = VT{};
-                    if (j0 + j < nb) {
-                        const uint32_t off = uint32_t(L.col[bbase + j0 + j]) * ROWB + qoff;
-                        const VT xv = *reinterpret_cast<const VT *>(Xc + off);
-                        const VT yv = *reinterpret_cast<const VT *>(Yc + off);
-#pragma unroll
-                        for (int i = 0; i < G::VEC; ++i) y[j][i] = bdiff(xv[i], yv[i], only_prev);
+                VT y[BCH], z[BCH];
+                static_for<0, BCH>([&](auto J) {
+                    constexpr int j = j0 + decltype(J)::value;
+                    y[J.value] = VT{};
+                    z[J.value] = VT{};
+                    const uint32_t at = uint32_t(off.template get<j>()) + boff;
+                    if (j < nb) {
+                        z[J.value] = *reinterpret_cast<const VT *>(Xc + at);
+                        y[J.value] = *reinterpret_cast<const VT *>(Yc + at);
                     }
-                }
+                });
+                static_for<0, BCH>([&](auto J) {
+                    constexpr int j = j0 + decltype(J)::value;
+                    VT d;
 #pragma unroll
-                for (int j = 0; j < BCH; ++j) bacc = vfma(L.bv[bbase + j0 + j], y[j], bacc);
+                    for (int i = 0; i < G::VEC; ++i) d[i] = bdiff(z[J.value][i], y[J.value][i], only_prev);
+                    bacc = vfma(bv.template get<j>(), d, bacc);
+                });
             }
-        }
-        for (int k = x0; k < x0 + nb - G::W; ++k) {
-            const uint32_t off = uint32_t(o.xcol[k]) * ROWB + qoff;
-            const VT xv = *reinterpret_cast<const VT *>(Xc + off);
-            const VT yv = *reinterpret_cast<const VT *>(Yc + off);
+        });
+        for (int k = rs.x0; k < rs.x0 + nb - G::W; ++k) {
+            const uint32_t at = uint32_t(o.xcol[k]) * ROWB + qoff;
+            const VT xv = *reinterpret_cast<const VT *>(Xc + at);
+            const VT yv = *reinterpret_cast<const VT *>(Yc + at);
             VT dv;
 #pragma unroll
             for (int i = 0; i < G::VEC; ++i) dv[i] = bdiff(xv[i], yv[i], only_prev);
-            bacc = vfma(o.bslot[L.bo[lr] + G::W + (k - x0)], dv, bacc);
+            bacc = vfma(o.bslot[rs.bo + G::W + (k - rs.x0)], dv, bacc);
         }
     }
+}
+
+// The padded operands of row `row` for lane q: byte offsets of the slots' rows, and K.
+template <typename T, int RB>
+__device__ __forceinline__ void load_slots(const RowOps<T> &o, int row, int q, SlotRegs<T, RB, int> &off,
+                                           SlotRegs<T, RB, T> &kv) {
+    using G = VGeo<T, RB>;
+    off.load(o.ecol + int64_t(row) * G::W, q);
+    kv.load(o.eval + int64_t(row) * G::W, q);
+#pragma unroll
+    for (int k = 0; k < 4 * G::QPL; ++k) off.v[k] = int(uint32_t(off.v[k]) * uint32_t(RB * sizeof(T)));
 }
 
 template <typename T>
@@ -501,27 +557,27 @@ __device__ __forceinline__ void fwd_sample(const VFwdArgs<T> &a, int j) {
 // Forward step (same update as k_fwd) with vector lanes on logical tile `tile`;
 // the tiles after the row tiles write the samples of the incoming state.
 template <typename T, typename OT, int RB, bool NT>
-__device__ __forceinline__ void fwd_tile(const VFwdArgs<T> &a, int tile, TileOps<T, RB> &L) {
+__device__ __forceinline__ void fwd_tile(const VFwdArgs<T> &a, int tile) {
     using G = VGeo<T, RB>;
     using VT = typename Vec16<T>::t;
     if (tile < a.n_tiles) {
-        const int row0 = tile * G::RPB;
-        stage_tile<T, RB>(a.o, a.n, row0, true, L);
-        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-        const int lr = wave * G::RPW + lane / G::LPR, q = lane % G::LPR;
-        const int row = row0 + lr;
-        if (row < a.n) {
-            const int64_t id = int64_t(row) * RB + q * G::VEC;
-            VT acc = {}, bacc = {}, cur;
-            vrow_sums<T, RB>(a.o, L, lr, q, a.S, a.Sp, L.bo[lr] >= 0, false, acc, bacc, cur);
-            // loaded after the sums: the kernel has no register to spare for it before
-            const VT prev = vload_own<NT, VT>(a.Sp + id);
-            const T dm = L.dm[lr];
-            VT sn;
+        const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane % G::LPR;
+        const int row = tile * G::RPB + wave * G::RPW + lane / G::LPR;
+        if (row >= a.n) return;
+        const int64_t id = int64_t(row) * RB + q * G::VEC;
+        SlotRegs<T, RB, int> off;
+        SlotRegs<T, RB, T> kv;
+        load_slots<T, RB>(a.o, row, q, off, kv);
+        const int sp = a.o.rspec[row];
+        const T dm = a.o.dtm[row];
+        const VT prev = vload_own<NT, VT>(a.Sp + id);
+        VT acc = {}, bacc = {}, cur;
+        RowSpec rs;
+        vrow_sums<T, RB>(a.o, q, sp, a.S, a.Sp, false, acc, bacc, cur, off, kv, rs);
+        VT sn;
 #pragma unroll
-            for (int i = 0; i < G::VEC; ++i) sn[i] = step_update(cur[i], prev[i], acc[i], bacc[i], T(0), dm, a.dt);
-            vstore<NT, VT>(a.Sn + id, sn);
-        }
+        for (int i = 0; i < G::VEC; ++i) sn[i] = step_update(cur[i], prev[i], acc[i], bacc[i], T(0), dm, a.dt);
+        vstore<NT, VT>(a.Sn + id, sn);
     } else if (a.sample) {
         fwd_sample<T, OT, RB>(a, tile - a.n_tiles);
     }
@@ -529,8 +585,7 @@ __device__ __forceinline__ void fwd_tile(const VFwdArgs<T> &a, int tile, TileOps
 
 template <typename T, typename OT, int RB, bool NT>
 __global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_fwd_v(const VFwdArgs<T> a) {
-    __shared__ TileOps<T, RB> L;
-    fwd_tile<T, OT, RB, NT>(a, fwd_work(xcd_tile(blockIdx.x, gridDim.x), a.n_tiles, a.n_samp), L);
+    fwd_tile<T, OT, RB, NT>(a, fwd_work(xcd_tile(blockIdx.x, gridDim.x), a.n_tiles, a.n_samp));
 }
 
 // Several meshes in one launch; mesh m has tiles[m] logical tiles.  Every XCD
@@ -548,10 +603,9 @@ struct Multi {
 
 template <typename T, typename OT, int RB, bool NT>
 __global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_fwd_vm(const Multi<VFwdArgs<T>> mm) {
-    __shared__ TileOps<T, RB> L;
     int m, local;
     if (!mesh_tile(mm.tiles, mm.n, blockIdx.x, &m, &local, false)) return;
-    fwd_tile<T, OT, RB, NT>(mm.a[m], fwd_work(local, mm.a[m].n_tiles, mm.a[m].n_samp), L);
+    fwd_tile<T, OT, RB, NT>(mm.a[m], fwd_work(local, mm.a[m].n_tiles, mm.a[m].n_samp));
 }
 
 template <typename T>
@@ -593,49 +647,47 @@ __device__ __forceinline__ VT vinject(const VAdjArgs<T> &a, int e0, int e1, int 
     return inj;
 }
 
-// Transposed step (same update as k_adj) with vector lanes on logical tile `tile`.
-template <typename T, typename YT, int RB, bool NT>
-__device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile, TileOps<T, RB> &L) {
+// Transposed step (same update as k_adj) with vector lanes on logical tile `tile`;
+// LAST: the closing launch.
+template <typename T, typename YT, int RB, bool NT, bool LAST>
+__device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile) {
     using G = VGeo<T, RB>;
     using VT = typename Vec16<T>::t;
     if (tile >= a.n_tiles) return;
-    const int row0 = tile * G::RPB;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const bool winj = wave_injects(a.injptr, row0 + wave * G::RPW, G::RPW, a.n);
-    stage_tile<T, RB>(a.o, a.n, row0, true, L);
-    const int lr = wave * G::RPW + lane / G::LPR, q = lane % G::LPR;
-    const int row = row0 + lr;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, q = lane % G::LPR;
+    const int row = tile * G::RPB + wave * G::RPW + lane / G::LPR;
     if (row >= a.n) return;
     const int64_t id = int64_t(row) * RB + q * G::VEC;
-    VT kq = {}, bq = {}, cur;
-    vrow_sums<T, RB>(a.o, L, lr, q, a.S, a.Sp, L.bo[lr] >= 0, a.last, kq, bq, cur);
-    // loaded after the sums: the kernel has no register to spare for it before
+    const int sp = a.o.rspec[row];
+    SlotRegs<T, RB, int> off;
+    SlotRegs<T, RB, T> kv;
+    load_slots<T, RB>(a.o, row, q, off, kv);
+    const T dm = a.o.dtm[row];
     const VT prev = vload_own<NT, VT>(a.Sp + id);
-    const T dm = L.dm[lr];
-    VT inj = {};
-    if (winj) inj = vinject<T, YT, RB, VT>(a, a.injptr[row], a.injptr[row + 1], q * G::VEC);
+    VT kq = {}, bq = {}, cur, inj = {};
+    RowSpec rs;
+    vrow_sums<T, RB>(a.o, q, sp, a.S, a.Sp, LAST, kq, bq, cur, off, kv, rs);
+    if (rs.e1 > rs.e0) inj = vinject<T, YT, RB, VT>(a, rs.e0, rs.e1, q * G::VEC);
     VT out;
 #pragma unroll
     for (int i = 0; i < G::VEC; ++i) {
         const T src = T(0.5) * inj[i];
-        out[i] = a.last ? adj_result(cur[i], prev[i], kq[i], bq[i], src, dm, a.dt)
-                        : step_update(cur[i], prev[i], kq[i], bq[i], src, dm, a.dt);
+        if constexpr (LAST) out[i] = adj_result(cur[i], prev[i], kq[i], bq[i], src, dm, a.dt);
+        else out[i] = step_update(cur[i], prev[i], kq[i], bq[i], src, dm, a.dt);
     }
     vstore<NT, VT>(a.Sn + id, out);
 }
 
-template <typename T, typename YT, int RB, bool NT>
+template <typename T, typename YT, int RB, bool NT, bool LAST>
 __global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_adj_v(const VAdjArgs<T> a) {
-    __shared__ TileOps<T, RB> L;
-    adj_tile<T, YT, RB, NT>(a, xcd_tile_rev(blockIdx.x, gridDim.x), L);
+    adj_tile<T, YT, RB, NT, LAST>(a, xcd_tile_rev(blockIdx.x, gridDim.x));
 }
 
-template <typename T, typename YT, int RB, bool NT>
+template <typename T, typename YT, int RB, bool NT, bool LAST>
 __global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_adj_vm(const Multi<VAdjArgs<T>> mm) {
-    __shared__ TileOps<T, RB> L;
     int m, local;
     if (!mesh_tile(mm.tiles, mm.n, blockIdx.x, &m, &local, true)) return;
-    adj_tile<T, YT, RB, NT>(mm.a[m], local, L);
+    adj_tile<T, YT, RB, NT, LAST>(mm.a[m], local);
 }
 
 // ---------------------------------------------------------------------------
@@ -768,15 +820,6 @@ __device__ __forceinline__ void halo_issue(const char *X, const char *Y, uint32_
     const int nu = d.mbytes >> 4, u = kHWaves - 1 - wave;  // metadata: 16-byte units, 64 per instruction
     if (u * 64 < nu && u * 64 + lane < nu)
         lds_copy16(hmeta + 4 * (int64_t(d.moff) + u * 64 + lane), &Lb.meta[u * 256]);
-}
-
-// Compile-time loop: f(std::integral_constant<int, I>) for I = B, B + S, ... < E.
-template <int B, int E, int S = 1, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + S, E, S>(f);
-    }
 }
 
 // Lane J of this lane's row of 16 lanes (DPP row broadcast): the 16 lanes of a row
@@ -1704,13 +1747,13 @@ template <typename T>
 RowOps<T> row_ops(const DevOps &op);
 template <>
 RowOps<double> row_ops<double>(const DevOps &op) {
-    return RowOps<double>{op.ell_col, op.xptr, op.xcol, op.bsoff, op.ell_val64, op.xval64, op.bslot64, op.dtm64,
-                          op.bnum};
+    return RowOps<double>{op.ell_col, op.xcol, op.ell_val64, op.xval64, op.bslot64, op.dtm64, op.rspec,
+                          op.spec, op.bsoff};
 }
 template <>
 RowOps<float> row_ops<float>(const DevOps &op) {
-    return RowOps<float>{op.ell_col, op.xptr, op.xcol, op.bsoff, op.ell_val32, op.xval32, op.bslot32, op.dtm32,
-                         op.bnum};
+    return RowOps<float>{op.ell_col, op.xcol, op.ell_val32, op.xval32, op.bslot32, op.dtm32, op.rspec,
+                          op.spec, op.bsoff};
 }
 template <typename T>
 const T *sw_of(const DevOps &op);
@@ -1827,8 +1870,10 @@ void adj_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool 
             return;
         }
     }
-    if (a.stream) hipLaunchKernelGGL((k_adj_v<T, YT, RB, true>), dim3(a.n_tiles), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_adj_v<T, YT, RB, false>), dim3(a.n_tiles), dim3(256), 0, s, a);
+    const dim3 g(a.n_tiles), b(256);
+    if (last) hipLaunchKernelGGL((k_adj_v<T, YT, RB, false, true>), g, b, 0, s, a);
+    else if (a.stream) hipLaunchKernelGGL((k_adj_v<T, YT, RB, true, false>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_adj_v<T, YT, RB, false, false>), g, b, 0, s, a);
 }
 
 template <typename T, typename YT, int RB>
@@ -1844,8 +1889,10 @@ void adj_impl_vm(const AdjStep *st, int n, hipStream_t s) {
     for (int m = 0; m < n; ++m) sb += state_bytes(*st[m].op, RB, sizeof(T));
     const int grid = multi_grid(mm.tiles, n);
     if (grid <= 0) return;
-    if (sb > kInfinityCacheBytes) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, true>), dim3(grid), dim3(256), 0, s, mm);
-    else hipLaunchKernelGGL((k_adj_vm<T, YT, RB, false>), dim3(grid), dim3(256), 0, s, mm);
+    const dim3 g(grid), b(256);
+    if (st[0].last) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, false, true>), g, b, 0, s, mm);
+    else if (sb > kInfinityCacheBytes) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, true, false>), g, b, 0, s, mm);
+    else hipLaunchKernelGGL((k_adj_vm<T, YT, RB, false, false>), g, b, 0, s, mm);
 }
 
 template <typename T, typename OT, int RB>
