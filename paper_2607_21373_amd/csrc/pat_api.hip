@@ -302,6 +302,10 @@ pat_status capture(pat_problem *p, hipGraphExec_t *exec, F &&body) {
 void enqueue_forward(pat_problem *p, SweepWS &w, void *y_out, bool y_f64, double yscale, hipStream_t s) {
     const pat::DevOps &op = p->ops;
     const int NT = op.n_steps;
+    if (pat::small_sweep_supported(w.prec, op)) {
+        pat::launch_fwd_small(w.prec, w.RB, op, w.S[0], y_out, y_f64, yscale, s);
+        return;
+    }
     for (int k = 0; k < NT; ++k)
         pat::launch_fwd_step(w.prec, w.RB, op, w.S[k % 3], w.S[k == 0 ? 0 : (k - 1) % 3], w.S[(k + 1) % 3], true,
                              k > 0, k - 1, y_out, y_f64, yscale, s);
@@ -317,6 +321,10 @@ inline int adj_slot(int j, int NT) { return ((j - NT) % 3 + 3) % 3; }
 void enqueue_adjoint(pat_problem *p, SweepWS &w, const void *yhat, bool y_f64, hipStream_t s) {
     const pat::DevOps &op = p->ops;
     const int NT = op.n_steps;
+    if (pat::small_sweep_supported(w.prec, op)) {
+        pat::launch_adj_small(w.prec, w.RB, op, yhat, y_f64, 1.0, w.S[0], s);
+        return;
+    }
     auto q = [&](int j) { return w.S[adj_slot(j, NT)]; };
     pat::launch_adj_init(w.prec, w.RB, op, q(0), q(-1), yhat, y_f64, 1.0, s);
     for (int k = 0; k + 1 < NT; ++k)
@@ -484,11 +492,37 @@ void adj_steps(pat::Prec prec, int RB, bool y_f64, const std::vector<pat::AdjSte
         pat::launch_adj_step(prec, RB, *a.op, a.S, a.Sp, a.Sn, a.last, a.tb, a.yh, y_f64, a.yscale, s);
 }
 
+// Meshes whose sweeps run in one launch each take no part in the shared steps.  Runs
+// `whole` for those and returns the others' indices.
+template <class F>
+std::vector<size_t> split_small(const std::vector<pat_problem *> &P, pat::Prec prec, F &&whole) {
+    std::vector<size_t> rest;
+    for (size_t m = 0; m < P.size(); ++m)
+        if (pat::small_sweep_supported(prec, P[m]->ops)) whole(m);
+        else rest.push_back(m);
+    return rest;
+}
+template <typename V>
+V pick(const V &v, const std::vector<size_t> &at) {
+    V o;
+    for (size_t m : at) o.push_back(v[m]);
+    return o;
+}
+
 // enqueue_forward for several meshes with equal N_T: the same launches, merged per step.
-void enqueue_forward_multi(const std::vector<pat_problem *> &P, const std::vector<SweepWS *> &W,
-                           const std::vector<void *> &yout, bool y_f64, const std::vector<double> &scale,
+void enqueue_forward_multi(const std::vector<pat_problem *> &Pall, const std::vector<SweepWS *> &Wall,
+                           const std::vector<void *> &yall, bool y_f64, const std::vector<double> &scall,
                            hipStream_t s, bool merge) {
+    const std::vector<size_t> rest = split_small(Pall, Wall[0]->prec, [&](size_t m) {
+        enqueue_forward(Pall[m], *Wall[m], yall[m], y_f64, scall[m], s);
+    });
+    if (rest.empty()) return;
+    const auto P = pick(Pall, rest);
+    const auto W = pick(Wall, rest);
+    const auto yout = pick(yall, rest);
+    const auto scale = pick(scall, rest);
     const size_t n = P.size();
+    merge = merge && n > 1;
     const int NT = P[0]->ops.n_steps;
     const pat::Prec prec = W[0]->prec;
     const int RB = W[0]->RB;
@@ -506,9 +540,17 @@ void enqueue_forward_multi(const std::vector<pat_problem *> &P, const std::vecto
 }
 
 // enqueue_adjoint for several meshes with equal N_T.
-void enqueue_adjoint_multi(const std::vector<pat_problem *> &P, const std::vector<SweepWS *> &W,
-                           const std::vector<const void *> &yin, bool y_f64, hipStream_t s, bool merge) {
+void enqueue_adjoint_multi(const std::vector<pat_problem *> &Pall, const std::vector<SweepWS *> &Wall,
+                           const std::vector<const void *> &yall, bool y_f64, hipStream_t s, bool merge) {
+    const std::vector<size_t> rest = split_small(Pall, Wall[0]->prec, [&](size_t m) {
+        enqueue_adjoint(Pall[m], *Wall[m], yall[m], y_f64, s);
+    });
+    if (rest.empty()) return;
+    const auto P = pick(Pall, rest);
+    const auto W = pick(Wall, rest);
+    const auto yin = pick(yall, rest);
     const size_t n = P.size();
+    merge = merge && n > 1;
     const int NT = P[0]->ops.n_steps;
     const pat::Prec prec = W[0]->prec;
     const int RB = W[0]->RB;
@@ -529,14 +571,15 @@ void enqueue_adjoint_multi(const std::vector<pat_problem *> &P, const std::vecto
 // steps of all meshes (after a warm-up) with HIP events and price a run of S
 // samples as ceil(S/RB) * (forward + transpose step); return the cheapest.  With
 // several meshes each direction is timed merged (one launch per step) and one
-// launch per mesh, and the faster is kept (*mf, *ma).
-pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t S, pat::Prec pr, hipStream_t s,
+// launch per mesh, and the faster is kept (*mf, *ma).  Small meshes, whose sweeps
+// are one launch each, are timed by whole sweeps and take no part in that choice.
+pat_status tune_rb(const std::vector<pat_problem *> &Pall, hipStream_t cap, int64_t S, pat::Prec pr, hipStream_t s,
                    int *best, double *best_us, int *mf = nullptr, int *ma = nullptr) {
     // candidates: up to the smallest block holding all S samples (beyond 64 only when S needs it)
     int top = 1;
     while (top < S && top < pat::max_rhs_block(pr)) top <<= 1;
     int64_t nmax = 0;
-    for (const pat_problem *q : P) nmax = std::max<int64_t>(nmax, q->ops.n);
+    for (const pat_problem *q : Pall) nmax = std::max<int64_t>(nmax, q->ops.n);
     top = fit_rb(nmax, pr, top);
     const int lo = std::max(1, std::min(top, 64) / 16);
     const int reps = 8;
@@ -553,44 +596,71 @@ pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t
     if (ma) *ma = 1;
     pat_status st = PAT_OK;
     for (int RB = lo; RB <= top && st == PAT_OK; RB <<= 1) {
-        std::vector<SweepWS *> W(P.size());
-        std::vector<void *> Y(P.size());
-        std::vector<double> one(P.size(), 1.0);
-        for (size_t m = 0; m < P.size() && st == PAT_OK; ++m) {
-            st = get_sweep(P[m], pr, RB, true, &W[m]);
+        std::vector<SweepWS *> Wall(Pall.size());
+        for (size_t m = 0; m < Pall.size() && st == PAT_OK; ++m) {
+            st = get_sweep(Pall[m], pr, RB, true, &Wall[m]);
             if (st != PAT_OK) break;
-            const size_t nb = size_t(P[m]->ops.n) * RB * tsize(pr);
-            const size_t yb = size_t(P[m]->ops.n_steps) * P[m]->ops.n_obs * RB * tsize(pr);
+            const size_t nb = size_t(Pall[m]->ops.n) * RB * tsize(pr);
+            const size_t yb = size_t(Pall[m]->ops.n_steps) * Pall[m]->ops.n_obs * RB * tsize(pr);
             for (int k = 0; k < 3; ++k) {
-                if (hipMemsetAsync(W[m]->S[k], 0, nb, s) != hipSuccess)
+                if (hipMemsetAsync(Wall[m]->S[k], 0, nb, s) != hipSuccess)
                     st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
             }
-            if (hipMemsetAsync(W[m]->Y, 0, yb, s) != hipSuccess) st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
-            Y[m] = W[m]->Y;
+            if (hipMemsetAsync(Wall[m]->Y, 0, yb, s) != hipSuccess)
+                st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
         }
         if (st != PAT_OK) break;
         const bool yf = pr == pat::Prec::F64;
+        std::vector<size_t> small;
+        const std::vector<size_t> rest = split_small(Pall, pr, [&](size_t m) { small.push_back(m); });
+        const auto P = pick(Pall, rest);
+        const auto W = pick(Wall, rest);
         std::vector<pat::FwdStep> fs(P.size());
         std::vector<pat::AdjStep> as(P.size());
         for (size_t m = 0; m < P.size(); ++m) {
-            fs[m] = pat::FwdStep{&P[m]->ops, W[m]->S[0], W[m]->S[1], W[m]->S[2], true, true, 0, Y[m], 1.0};
+            fs[m] = pat::FwdStep{&P[m]->ops, W[m]->S[0], W[m]->S[1], W[m]->S[2], true, true, 0, W[m]->Y, 1.0};
             // a plain step reads the data of sample times 0 and 1; one-step problems time the closing launch
-            as[m] = pat::AdjStep{&P[m]->ops, W[m]->S[0], W[m]->S[1], W[m]->S[2], P[m]->ops.n_steps < 2, 0, Y[m], 1.0};
+            as[m] = pat::AdjStep{&P[m]->ops, W[m]->S[0], W[m]->S[1], W[m]->S[2], P[m]->ops.n_steps < 2, 0, W[m]->Y,
+                                 1.0};
         }
+        // milliseconds of one replay of a captured graph, after a warm-up
+        auto timed = [&](hipGraphExec_t x, float *out) {
+            (void)hipGraphLaunch(x, s);
+            (void)hipEventRecord(ev[0], s);
+            (void)hipGraphLaunch(x, s);
+            (void)hipEventRecord(ev[1], s);
+            if (hipEventSynchronize(ev[1]) != hipSuccess) return fail(PAT_ERR_HIP, "autotune: a timed step failed");
+            (void)hipEventElapsedTime(out, ev[0], ev[1]);
+            return PAT_OK;
+        };
+        double small_ms = 0.0;  // of `reps` forward and transpose steps of the small meshes
+        for (size_t m : small)
+            for (int q = 0; q < 2 && st == PAT_OK; ++q) {
+                hipGraphExec_t x = nullptr;
+                float ms = 0.f;
+                st = capture_on(cap, &x, [&](hipStream_t cs) {
+                    if (q == 0) enqueue_forward(Pall[m], *Wall[m], Wall[m]->Y, yf, 1.0, cs);
+                    else enqueue_adjoint(Pall[m], *Wall[m], Wall[m]->Y, yf, cs);
+                });
+                if (st == PAT_OK) st = timed(x, &ms);
+                if (x) (void)hipGraphExecDestroy(x);
+                small_ms += double(ms) * reps / Pall[m]->ops.n_steps;
+            }
+        if (st != PAT_OK) break;
         // The sweeps replay captured graphs, so time captured sequences of `reps` steps
         // (sequence q: direction q % 2).  Several meshes: q = 0, 1 merged launches per
         // step; q = 2, 3 one launch per mesh within each step; then one graph per mesh
         // and direction (that mesh alone, as a whole sweep per mesh runs it).
         const size_t nm = P.size();
         const bool multi = nm > 1;
-        const int nq = multi ? 4 + 2 * int(nm) : 2;
+        const int nq = multi ? 4 + 2 * int(nm) : 2 * int(nm);
         std::vector<hipGraphExec_t> g(size_t(nq), nullptr);
         for (int q = 0; q < nq && st == PAT_OK; ++q)
             st = capture_on(cap, &g[size_t(q)], [&](hipStream_t cs) {
                 for (int k = 0; k < reps; ++k) {
                     if (q < 4) {
-                        if (q % 2 == 0) fwd_steps(pr, RB, yf, fs, cs, q < 2);
-                        else adj_steps(pr, RB, yf, as, cs, q < 2);
+                        if (q % 2 == 0) fwd_steps(pr, RB, yf, fs, cs, multi && q < 2);
+                        else adj_steps(pr, RB, yf, as, cs, multi && q < 2);
                     } else {
                         const size_t m = size_t(q - 4) / 2;
                         if (q % 2 == 0) fwd_steps(pr, RB, yf, {fs[m]}, cs, false);
@@ -600,19 +670,12 @@ pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t
             });
         std::vector<float> ms(size_t(nq), 0.f);
         if (st == PAT_OK) {
-            for (int q = 0; q < nq && st == PAT_OK; ++q) {
-                (void)hipGraphLaunch(g[size_t(q)], s);  // warm-up
-                (void)hipEventRecord(ev[0], s);
-                (void)hipGraphLaunch(g[size_t(q)], s);
-                (void)hipEventRecord(ev[1], s);
-                if (hipEventSynchronize(ev[1]) != hipSuccess) st = fail(PAT_ERR_HIP, "autotune: a timed step failed");
-                else (void)hipEventElapsedTime(&ms[size_t(q)], ev[0], ev[1]);
-            }
+            for (int q = 0; q < nq && st == PAT_OK; ++q) st = timed(g[size_t(q)], &ms[size_t(q)]);
         }
         for (auto &x : g)
             if (x) (void)hipGraphExecDestroy(x);
         if (st != PAT_OK) break;
-        float f_ms = ms[0], a_ms = ms[1];
+        float f_ms = nm ? ms[0] : 0.f, a_ms = nm ? ms[1] : 0.f;
         int m_f = 1, m_a = 1;
         if (multi) {
             const bool merged_ok = pat::multi_step_supported(pr, RB);
@@ -626,7 +689,7 @@ pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t
             if (sf < f_ms) { f_ms = sf; m_f = 2; }
             if (sa < a_ms) { a_ms = sa; m_a = 2; }
         }
-        const double us = double((S + RB - 1) / RB) * 1e3 * double(f_ms + a_ms) / reps;
+        const double us = double((S + RB - 1) / RB) * 1e3 * (double(f_ms + a_ms) + small_ms) / reps;
         if (us < *best_us) {
             *best_us = us;
             *best = RB;
@@ -1100,10 +1163,16 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
             if (hp.bsoff[i] >= 0) brows.push_back(hp.bsoff[i]);
             if (hp.bsoff[i] >= 0 || hp.xptr[i + 1] > hp.xptr[i] || hp.injptr[i + 1] > hp.injptr[i]) {
                 spec.push_back(int4{std::max(hp.bsoff[i], 0), hp.bnum[i], hp.xptr[i], hp.xptr[i + 1]});
-                spec.push_back(int4{hp.injptr[i], hp.injptr[i + 1], 0, 0});
+                spec.push_back(int4{hp.injptr[i], hp.injptr[i + 1], op.n_bnd, 0});
+                if (hp.bsoff[i] >= 0) ++op.n_bnd;
+                op.max_nb = std::max(op.max_nb, hp.bnum[i]);
+                op.max_spec = std::max({op.max_spec, hp.xptr[i + 1] - hp.xptr[i], hp.injptr[i + 1] - hp.injptr[i]});
                 rspec[i] = int32_t(spec.size() / 2);
             }
         }
+        op.n_spec = int32_t(spec.size() / 2);
+        op.n_x = hp.xptr[hp.n];
+        op.n_inj = hp.injptr[hp.n];
         const std::vector<double> val = quads(hp.ell_val, rows), bval = quads(hp.bslot, brows);
         UP(quads(hp.ell_col, rows), ell_col);
         UP(rspec, rspec);

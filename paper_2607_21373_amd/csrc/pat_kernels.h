@@ -21,7 +21,8 @@ struct DevOps {
     // (slot p + 4 i at 4 p + i), likewise the first 16 B values of a boundary row
     const int32_t *ell_col = nullptr, *xcol = nullptr, *bsoff = nullptr;
     // per row 0, or 1 + the index of its record in spec: {first B value, bnum, first and end
-    // of the entries beyond the padded slots}, {first and end of the sensor weights, 0, 0}
+    // of the entries beyond the padded slots}, {first and end of the sensor weights, the row's rank among the boundary
+    // rows, 0}
     const int32_t *rspec = nullptr;
     const int4 *spec = nullptr;
     const double *ell_val64 = nullptr, *xval64 = nullptr, *bslot64 = nullptr;
@@ -32,6 +33,9 @@ struct DevOps {
     int32_t n_ht = 0;
     int32_t n_cu = 0;  // compute units of the device (the halo kernels keep two workgroups on each)
     double dt = 0.0;
+    // sizes of the extra tables: records, boundary rows and their largest bnum, entries beyond the
+    // padded slots, sensor weights, and the largest count of either kind in one row
+    int32_t n_spec = 0, n_bnd = 0, max_nb = 0, n_x = 0, n_inj = 0, max_spec = 0;
 };
 
 enum class Prec { F64, F32 };
@@ -57,6 +61,15 @@ void launch_adj_init(Prec prec, int RB, const DevOps &op, void *q0, void *qm1, c
                      double yscale, hipStream_t s);
 void launch_adj_step(Prec prec, int RB, const DevOps &op, const void *S, const void *Sp, void *Sn, bool last, int tb,
                      const void *yhat, bool y_is_f64, double yscale, hipStream_t s);
+
+// Whole sweeps of a small mesh in one launch (pat_small.hip), where supported: y =
+// samples of the sweep from p0 [N][RB]; out [N][RB] = the transpose of yhat.  Bit for
+// bit the step launches' results.
+bool small_sweep_supported(Prec prec, const DevOps &op);
+void launch_fwd_small(Prec prec, int RB, const DevOps &op, const void *p0, void *y, bool y_is_f64, double yscale,
+                      hipStream_t s);
+void launch_adj_small(Prec prec, int RB, const DevOps &op, const void *yhat, bool y_is_f64, double yscale, void *out,
+                      hipStream_t s);
 
 // Several meshes' steps in one launch (vector-lane kernels only: RB * sizeof(T) >= 16,
 // see multi_step_supported; at most kMaxMeshes meshes).  Each entry is one mesh's

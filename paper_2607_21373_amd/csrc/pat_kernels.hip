@@ -32,13 +32,11 @@
 
 #include "pat_internal.h"
 #include "pat_kernels.h"
+#include "pat_step.h"
 #include "pat_tiles.h"
 
 namespace pat {
 namespace {
-
-__device__ __forceinline__ float mad(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double mad(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 template <int RB>
 struct Geo {
@@ -77,30 +75,6 @@ struct RowOps {
     const int4 *spec;
     const int32_t *bsoff;  // boundary rows of the halo kernels with more than 16 B values
 };
-// B values from bslot[bo], nb slots of them nonzero (nb = 0: interior row); entries
-// beyond the padded slots [x0, x1); sensor weights [e0, e1)
-struct RowSpec {
-    int bo = 0, nb = 0, x0 = 0, x1 = 0, e0 = 0, e1 = 0;
-    __device__ __forceinline__ void load(const int4 *spec, int k) {
-        const int4 u = spec[2 * (k - 1)], v = spec[2 * (k - 1) + 1];
-        bo = u.x; nb = u.y; x0 = u.z; x1 = u.w;
-        e0 = v.x; e1 = v.y;
-    }
-};
-
-// the four values of one quad
-template <typename T>
-__device__ __forceinline__ void load_quad(const T *p, T v[4]) {
-    if constexpr (sizeof(T) == 4) {
-        const auto q = *reinterpret_cast<const T __attribute__((ext_vector_type(4))) *>(p);
-        v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
-    } else {
-        using V2 = T __attribute__((ext_vector_type(2)));
-        const V2 q0 = reinterpret_cast<const V2 *>(p)[0], q1 = reinterpret_cast<const V2 *>(p)[1];
-        v[0] = q0.x; v[1] = q0.y; v[2] = q1.x; v[3] = q1.y;
-    }
-}
-
 // Operands of one row as seen by one lane of the scalar-lane kernels: its quad of
 // padded slots (part, part + 4, ...), the row's special record and dt/m.
 template <typename T, int RB>
@@ -120,26 +94,6 @@ __device__ __forceinline__ void load_meta(const RowOps<T> &o, int row, int part,
     load_quad(o.eval + eb, m.w);
     m.sp = o.rspec[row];
     m.dm = o.dtm[row];
-}
-
-// The value a boundary slot multiplies: S - S_prev in a step, -S_prev in the
-// transpose sweep's closing launch (only_prev).
-template <typename T>
-__device__ __forceinline__ T bdiff(T x, T y, bool only_prev) { return only_prev ? -y : x - y; }
-
-// One row of a three-level step: S' = S + ((S - Sp) - (dt/m)(dt K S + B (S - Sp) - src))
-// from acc = (K S)_row, bacc = (B (S - Sp))_row and the source src (0 forward).
-template <typename T>
-__device__ __forceinline__ T step_update(T cur, T prev, T acc, T bacc, T src, T dm, T dt) {
-    const T f = mad(dt, acc, bacc) - src;
-    return cur + mad(-dm, f, cur - prev);
-}
-// The transpose sweep's result, (q - q_prev) m/dt - (dt K q - B q_prev - src), from
-// acc = (K q)_row and bacc = -(B q_prev)_row.
-template <typename T>
-__device__ __forceinline__ T adj_result(T cur, T prev, T acc, T bacc, T src, T dm, T dt) {
-    const T f = mad(dt, acc, bacc) - src;
-    return (cur - prev) / dm - f;
 }
 
 // acc = sum over the row's entries of K(row, k) X[col_k][r], and for a boundary row
@@ -360,15 +314,6 @@ struct VGeo {
     static constexpr int HL = LPR < 4 ? LPR : 4;  // lanes that share a row's padded operands
     static constexpr int QPL = 4 / HL;            // quads of slots per lane
 };
-
-// Compile-time loop: f(std::integral_constant<int, I>) for I = B, B + S, ... < E.
-template <int B, int E, int S = 1, typename F>
-__device__ __forceinline__ void static_for(F &&f) {
-    if constexpr (B < E) {
-        f(std::integral_constant<int, B>{});
-        static_for<B + S, E, S>(f);
-    }
-}
 
 // lane H of each group of HL neighbouring lanes, to the whole group (DPP quad permute;
 // every lane of a group works on the same row, so none of them is ever off alone)
