@@ -1183,14 +1183,40 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
         UP(to_f32(bval), bslot32);
     }
     UP(hp.xcol, xcol);
-    UP(hp.bsoff, bsoff);
     UP(hp.xval, xval64);
     UP(to_f32(hp.xval), xval32);
     {
         pat::HaloTiles ht;
         pat::build_halo_tiles(hp, ht);
-        UP(ht.desc, ht_desc);
+        // the float64 kernels read the row operands from the padded layout and a tile's own
+        // local indices, info words and B values from these arrays
+        std::vector<int4> desc;
+        std::vector<uint8_t> loc(ht.n_tiles ? size_t(hp.n) * 16 : 0), bloc;
+        std::vector<uint32_t> rinfo(ht.n_tiles ? size_t(hp.n) * 4 : 0);
+        std::vector<double> bw;
+        for (int32_t t = 0; t < ht.n_tiles; ++t) {
+            const int32_t *D = &ht.desc[size_t(t) * 4];
+            constexpr int B = pat::HaloTiles::kNrBits, M = (1 << B) - 1;
+            const int32_t r0 = D[0], nr = D[3] & M, nbr = (D[3] >> (B + 16)) & M;
+            const uint32_t *m = ht.meta.data() + size_t(D[2]) * 4, *info = m + size_t(nr) * 4;
+            const auto *l8 = reinterpret_cast<const uint8_t *>(m);
+            const auto *b8 = reinterpret_cast<const uint8_t *>(m + size_t(nr) * 24 + size_t(nbr) * 16);
+            desc.push_back(int4{r0, D[1], int32_t(bloc.size() / 16), D[3]});
+            std::copy(l8, l8 + size_t(nr) * 16, loc.begin() + size_t(r0) * 16);
+            bloc.insert(bloc.end(), b8, b8 + size_t(nbr) * 16);
+            for (int32_t g = 0; g < nr; ++g) {
+                std::copy(info + size_t(g) * 4, info + size_t(g) * 4 + 4, rinfo.begin() + size_t(r0 + g) * 4);
+                if (hp.bsoff[r0 + g] >= 0)
+                    bw.insert(bw.end(), hp.bslot.begin() + hp.bsoff[r0 + g],
+                              hp.bslot.begin() + hp.bsoff[r0 + g] + pat::HostProblem::kEll);
+            }
+        }
+        UP(desc, ht_desc);
         UP(ht.hrow, ht_hrow);
+        UP(loc, ht_loc);
+        UP(bloc, ht_bloc);
+        UP(rinfo, ht_info);
+        UP(bw, ht_bw);
         UP(ht.meta, ht_meta);
         op.n_ht = ht.n_tiles;
         int ncu = 0;

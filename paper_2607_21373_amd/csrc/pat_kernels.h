@@ -19,7 +19,7 @@ struct DevOps {
     const float *dtm32 = nullptr, *sw32 = nullptr, *injw32 = nullptr;
     // padded row layout of K for the time-step kernels: a row's 16 slots in quad order
     // (slot p + 4 i at 4 p + i), likewise the first 16 B values of a boundary row
-    const int32_t *ell_col = nullptr, *xcol = nullptr, *bsoff = nullptr;
+    const int32_t *ell_col = nullptr, *xcol = nullptr;
     // per row 0, or 1 + the index of its record in spec: {first B value, bnum, first and end
     // of the entries beyond the padded slots}, {first and end of the sensor weights, the row's rank among the boundary
     // rows, 0}
@@ -27,11 +27,17 @@ struct DevOps {
     const int4 *spec = nullptr;
     const double *ell_val64 = nullptr, *xval64 = nullptr, *bslot64 = nullptr;
     const float *ell_val32 = nullptr, *xval32 = nullptr, *bslot32 = nullptr;
-    // halo tiles of the float32 step kernels (HaloTiles)
-    const int32_t *ht_desc = nullptr, *ht_hrow = nullptr;
-    const uint32_t *ht_meta = nullptr;
+    // halo tiles (HaloTiles; pat_halo.hip): per tile {first row, first halo entry, rank of its
+    // first boundary row, packed counts}, the halos' rows and the metadata blocks (float32);
+    // for the float64 kernels per row the K-local index of each slot and the four info words,
+    // per boundary row the B-local index and the value of each slot
+    const int4 *ht_desc = nullptr;
+    const int32_t *ht_hrow = nullptr;
+    const uint8_t *ht_loc = nullptr, *ht_bloc = nullptr;
+    const uint32_t *ht_info = nullptr, *ht_meta = nullptr;
+    const double *ht_bw = nullptr;
     int32_t n_ht = 0;
-    int32_t n_cu = 0;  // compute units of the device (the halo kernels keep two workgroups on each)
+    int32_t n_cu = 0;  // compute units of the device
     double dt = 0.0;
     // sizes of the extra tables: records, boundary rows and their largest bnum, entries beyond the
     // padded slots, sensor weights, and the largest count of either kind in one row
@@ -60,6 +66,13 @@ void launch_fwd_step(Prec prec, int RB, const DevOps &op, const void *S, const v
 void launch_adj_init(Prec prec, int RB, const DevOps &op, void *q0, void *qm1, const void *yhat, bool y_is_f64,
                      double yscale, hipStream_t s);
 void launch_adj_step(Prec prec, int RB, const DevOps &op, const void *S, const void *Sp, void *Sn, bool last, int tb,
+                     const void *yhat, bool y_is_f64, double yscale, hipStream_t s);
+
+// The same steps on halo tiles (pat_halo.hip), for the block widths they take
+bool halo_step_supported(Prec prec, int RB, const DevOps &op);
+void launch_fwd_halo(Prec prec, int RB, const DevOps &op, const void *S, const void *Sp, void *Sn, bool sample, int t,
+                     void *y, bool y_is_f64, double yscale, hipStream_t s);
+void launch_adj_halo(Prec prec, int RB, const DevOps &op, const void *S, const void *Sp, void *Sn, bool last, int tb,
                      const void *yhat, bool y_is_f64, double yscale, hipStream_t s);
 
 // Whole sweeps of a small mesh in one launch (pat_small.hip), where supported: y =

@@ -73,7 +73,6 @@ struct RowOps {
     const T *eval, *xval, *bslot, *dtm;
     const int32_t *rspec;
     const int4 *spec;
-    const int32_t *bsoff;  // boundary rows of the halo kernels with more than 16 B values
 };
 // Operands of one row as seen by one lane of the scalar-lane kernels: its quad of
 // padded slots (part, part + 4, ...), the row's special record and dt/m.
@@ -477,10 +476,6 @@ struct VFwdArgs {
     int n, n_obs, n_tiles, n_samp, sample, t;
     int stream;  // state beyond the Infinity Cache: launch the non-temporal variant
     T dt;
-    // halo tiles (HaloTiles), float32 blocks of 256-byte row chunks
-    const int32_t *hdesc, *hrow;
-    const uint32_t *hmeta;
-    int n_ht;
 };
 
 // Sampling block j of a forward step: y = Pi (S^n + S^{n-1})/2 of the incoming
@@ -566,9 +561,6 @@ struct VAdjArgs {
     int ta, tb;  // sources: Pi^T yhat at sample indices ta (if >= 0) and tb
     int stream;  // state beyond the Infinity Cache: launch the non-temporal variant
     T dt;
-    const int32_t *hdesc, *hrow;
-    const uint32_t *hmeta;
-    int n_ht;
 };
 
 // Pi^T (yhat^{ta} + yhat^{tb}) over the injection entries [e0, e1) of a row, for
@@ -633,389 +625,6 @@ __global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_adj_vm(const Multi<VAdj
     int m, local;
     if (!mesh_tile(mm.tiles, mm.n, blockIdx.x, &m, &local, true)) return;
     adj_tile<T, YT, RB, NT, LAST>(mm.a[m], local);
-}
-
-// ---------------------------------------------------------------------------
-// Halo step kernels: float32 blocks whose rows are 64, 128 or 256 RHS (one to
-// four 256-byte chunks).
-//
-// The vector-lane kernels above gather 16 neighbour rows per row through the
-// CU's texture units, which keeps those units busy most of the step.  Here a
-// tile of consecutive rows (HaloTiles: at most 32 rows whose distinct neighbour
-// rows, the halo, fit 132 LDS rows; on the 195,112-node ball 4.7 halo rows per
-// row) copies its halo and its row operands from memory straight into LDS
-// (global_load_lds_dwordx4, 64 lanes x 16 bytes per instruction, no registers
-// in between), and every slot reads its neighbour from there.  Each workgroup
-// (512 threads: 32 rows x 16 lanes of 16 bytes) walks its tiles in a loop with
-// two LDS buffers: while it computes one tile, the copies of the next are in
-// flight, and the stores of the previous one drain.  Work item = (row chunk,
-// tile); XCD x takes the x-th eighth of the tiles, its workgroups interleaved
-// over them, so the tiles in flight on one XCD are neighbours and share their
-// halo rows in that XCD's L2.  The halo holds rows of the state S (the K part)
-// and, at the rows that its boundary slots refer to, rows of the previous state
-// S_prev (the B part).  Each lane of a
-// row's 16 reads one slot's operands from the LDS image and hands them to the
-// others by DPP row broadcast.  Sums run in the slot order of the vector-lane
-// kernels, with the same operations, so both give the same bits.
-// ---------------------------------------------------------------------------
-
-using F4 = Vec16<float>::t;  // 16 bytes of float32
-constexpr int kHRows = HaloTiles::kRows;
-constexpr int kHMax = HaloTiles::kMax;
-constexpr int kHMetaWords = HaloTiles::kMetaBytes / 4;
-constexpr int kHThreads = kHRows * 16;
-constexpr int kHWaves = kHThreads / 64;
-constexpr int kHPerWave = (kHMax / 4 + kHWaves - 1) / kHWaves;  // halo copy instructions per wave at most
-constexpr int kHChunk = 4;  // LDS reads in flight per lane before they are consumed
-constexpr uint32_t kNoRow = 0xFFFFFFFFu;
-static_assert(kHThreads % 64 == 0 && kHThreads <= 1024 && (kHMetaWords + 255) / 256 <= kHWaves, "halo tile geometry");
-
-// LDS image of one tile
-struct alignas(16) HaloBuf {
-    F4 rows[kHMax * 16];      // halo rows (256-byte chunks): K part, then B part
-    uint32_t meta[kHMetaWords];   // the tile's metadata block (HaloTiles)
-};
-// LDS of a workgroup: two tile images and two halo row lists, each its own
-// __shared__ variable, so that the compiler can tell the copies into one buffer
-// from the reads of the other and does not wait for the former before the latter
-struct alignas(16) HaloList {  // copied into 16 bytes per lane
-    int32_t r[kHMax];
-};
-// workgroups per CU that the LDS of two tile images and two lists allows (160 KiB per CU)
-constexpr int kHPerCU = int(163840 / (2 * (sizeof(HaloBuf) + sizeof(HaloList))));
-static_assert(kHPerCU >= 1, "one workgroup per CU at least");
-
-struct HDesc {
-    int r0, nr, h0, nk4, nb4, moff, mbytes, nbr;
-};
-
-// unpack a tile descriptor (HaloTiles::desc) into wave-uniform values
-__device__ __forceinline__ HDesc desc_uniform(const int4 u) {
-    const int r0 = __builtin_amdgcn_readfirstlane(u.x), h0 = __builtin_amdgcn_readfirstlane(u.y);
-    const int moff = __builtin_amdgcn_readfirstlane(u.z), f = __builtin_amdgcn_readfirstlane(u.w);
-    constexpr int B = HaloTiles::kNrBits, M = (1 << B) - 1;
-    const int nr = f & M, nk4 = (f >> B) & 255, nb4 = (f >> (B + 8)) & 255, nbr = (f >> (B + 16)) & M;
-    return {r0, nr, h0, nk4, nb4, moff, nr * 96 + nbr * 80, nbr};
-}
-
-// Work items of this workgroup: (chunk c, tile t).  XCD x (workgroups b with
-// b % 8 == x) owns the x-th eighth of the tiles, [t_lo, t_lo + ntx), seen as rows
-// of G8 consecutive tiles (one per workgroup of the XCD: neighbouring tiles are in
-// flight together and share halo rows in its L2).  Two workgroups share a CU, and
-// the one dispatched first (k = b / 8 < G8 / 2) runs about a fifth faster than
-// the other; so every kRowPeriod-th row goes to the first half only, two tiles
-// each, and they take 10 tiles for every 8 of the others.  A workgroup walks its
-// tiles in row order, once per 256-byte chunk.
-struct HWork {
-    int t_lo, ntx, k, G8, per_c, n;
-    bool weighted, first_half;
-    // local index (tile - t_lo) of this workgroup's j-th tile; increasing in j
-    __device__ int local(int j) const { return hwork_local(j, G8, k, weighted, first_half); }
-    __device__ HWork(int n_ht, int NC) {
-        G8 = int(gridDim.x >> 3);
-        const int x = int(blockIdx.x & 7);
-        k = int(blockIdx.x >> 3);
-        t_lo = int(int64_t(n_ht) * x / 8);
-        ntx = int(int64_t(n_ht) * (x + 1) / 8) - t_lo;
-        weighted = kHPerCU == 2 && G8 % 2 == 0;
-        first_half = 2 * k < G8;
-        per_c = 0;
-        while (local(per_c) < ntx) ++per_c;
-        n = per_c * NC;
-    }
-    __device__ int chunk(int it) const { return it / per_c; }
-    __device__ int tile(int it) const { return t_lo + local(it - chunk(it) * per_c); }
-};
-
-__device__ __forceinline__ void lds_copy16(const void *src, void *lds) {
-    __builtin_amdgcn_global_load_lds(src, (__attribute__((address_space(3))) void *)lds, 16, 0, 0);
-}
-
-// Start the copy of a tile's halo row list (nh entries, a multiple of 4 from a
-// 16-byte aligned start) into list; one wave issues it.
-__device__ __forceinline__ void halo_list_issue(const int32_t *hrow, const HDesc &d, int nh, int32_t *list, int wave,
-                                                int lane) {
-    if (wave == 1 && 4 * lane < nh) lds_copy16(hrow + d.h0 + 4 * lane, list);
-}
-
-// Start the copies of a tile into Lb: its nh halo rows (row numbers from list; the
-// first nk4 from X, the rest from Y) at byte offset coff of each row, and its
-// metadata block.  Copy instruction h (halo rows 4h .. 4h+3) is issued by wave h % 8.
-template <uint32_t RS>
-__device__ __forceinline__ void halo_issue(const char *X, const char *Y, uint32_t coff, const uint32_t *hmeta,
-                                           const HDesc &d, int nh, const int32_t *list, HaloBuf &Lb, int wave,
-                                           int lane) {
-    // wave is wave-uniform (callers pass it through readfirstlane), so the tests and
-    // the base select below are scalar; the list entries are read in one batch
-    int hr[kHPerWave];
-#pragma unroll
-    for (int m = 0; m < kHPerWave; ++m) {
-        const int h = wave + kHWaves * m;
-        hr[m] = list[min(4 * h, kHMax - 4) + (lane >> 4)];
-    }
-    const uint32_t lo = coff + uint32_t(lane & 15) * 16u;
-#pragma unroll
-    for (int m = 0; m < kHPerWave; ++m) {
-        const int h = wave + kHWaves * m;
-        if (4 * h < nh) {
-            const char *base = 4 * h < d.nk4 ? X : Y;
-            lds_copy16(base + (uint32_t(hr[m]) * RS + lo), &Lb.rows[h * 64]);
-        }
-    }
-    const int nu = d.mbytes >> 4, u = kHWaves - 1 - wave;  // metadata: 16-byte units, 64 per instruction
-    if (u * 64 < nu && u * 64 + lane < nu)
-        lds_copy16(hmeta + 4 * (int64_t(d.moff) + u * 64 + lane), &Lb.meta[u * 256]);
-}
-
-// Lane J of this lane's row of 16 lanes (DPP row broadcast): the 16 lanes of a row
-// group each hold one slot's operands and hand them to the group slot by slot.
-template <int J>
-__device__ __forceinline__ uint32_t row_bcast(uint32_t x) {
-    return uint32_t(__builtin_amdgcn_update_dpp(0, int(x), 0x150 + J, 0xF, 0xF, true));
-}
-template <int J>
-__device__ __forceinline__ float row_bcast(float x) {
-    return __uint_as_float(row_bcast<J>(__float_as_uint(x)));
-}
-
-// The operands of row g of the tile in Lb (metadata layout of HaloTiles) as held by
-// lane q of its row group: slot q's K value and K-halo byte offset, and info word
-// q % 4.  Per-row values come from the info words by row broadcast.
-struct HLane {
-    uint32_t koff;  // byte offset of slot q's neighbour in the K part of the halo
-    float kv;
-    uint32_t info;
-};
-__device__ __forceinline__ HLane halo_lane(const HaloBuf &Lb, int nr, int g, int q) {
-    HLane h;
-    h.koff = uint32_t(reinterpret_cast<const uint8_t *>(Lb.meta + g * 4)[q]) * 256u;
-    h.info = Lb.meta[nr * 4 + g * 4 + (q & 3)];
-    h.kv = reinterpret_cast<const float *>(Lb.meta + nr * 8 + g * 16)[q];
-    return h;
-}
-// per-row values from the info words: dt/m, boundary row (0xFF: none), bnum, the
-// overflow range [x0, x0 + nx) and the injection range [inj0, inj0 + ninj)
-__device__ __forceinline__ float hl_dm(const HLane &h) { return __uint_as_float(row_bcast<0>(h.info)); }
-__device__ __forceinline__ uint32_t hl_word(const HLane &h) { return row_bcast<1>(h.info); }
-__device__ __forceinline__ int hl_x0(const HLane &h) { return int(row_bcast<2>(h.info)); }
-__device__ __forceinline__ int hl_inj0(const HLane &h) { return int(row_bcast<3>(h.info)); }
-__device__ __forceinline__ int hw_brow(uint32_t w) { return int(w & 0xFFu); }
-__device__ __forceinline__ int hw_bnum(uint32_t w) { return int((w >> 8) & 0xFFu); }
-__device__ __forceinline__ int hw_nx(uint32_t w) { return int((w >> 16) & 0xFFu); }
-__device__ __forceinline__ int hw_ninj(uint32_t w) { return int(w >> 24); }
-// boundary row br's B value and B-halo byte offset (base: the B part's first row) of slot q
-__device__ __forceinline__ float hb_value(const HaloBuf &Lb, int nr, int br, int q) {
-    return reinterpret_cast<const float *>(Lb.meta + nr * 24 + br * 16)[q];
-}
-__device__ __forceinline__ uint32_t hb_offset(const HaloBuf &Lb, int nr, int nbr, int br, int q, int base) {
-    return (uint32_t(base) + reinterpret_cast<const uint8_t *>(Lb.meta + nr * 24 + nbr * 16 + br * 4)[q]) * 256u;
-}
-
-__device__ __forceinline__ F4 lds_row(const HaloBuf &Lb, uint32_t off) {
-    return *reinterpret_cast<const F4 *>(reinterpret_cast<const char *>(Lb.rows) + off);
-}
-
-// acc += sum_slots K(row, slot) X[col] from the halo, slot order as vrow_sums, then
-// the entries beyond 16 from memory; own = slot 0 (the row's diagonal).
-__device__ __forceinline__ void halo_ksums(const HaloBuf &Lb, const HLane &h, uint32_t q16, int x0, int x1,
-                                           const float *__restrict__ xval, const int32_t *__restrict__ xcol,
-                                           const char *Xc, uint32_t RS, uint32_t coff, F4 &acc, F4 &own) {
-    static_for<0, 16, kHChunk>([&](auto J0) {
-        constexpr int j0 = decltype(J0)::value;
-        F4 x[kHChunk];
-        static_for<0, kHChunk>([&](auto J) { x[J.value] = lds_row(Lb, row_bcast<j0 + J.value>(h.koff) + q16); });
-        if constexpr (j0 == 0) own = x[0];
-        static_for<0, kHChunk>([&](auto J) { acc = vfma(row_bcast<j0 + J.value>(h.kv), x[J.value], acc); });
-    });
-    for (int k = x0; k < x1; ++k) {
-        const F4 xv = *reinterpret_cast<const F4 *>(Xc + (uint32_t(xcol[k]) * RS + coff + q16));
-        acc = vfma(xval[k], xv, acc);
-    }
-}
-
-// bacc += sum over the first nb slots of B(row, slot) bdiff(X[col], Y[col]), as
-// vrow_sums: slot j's X row at the halo byte offset koffq of lane j (the K part), its
-// Y row at boffq of lane j (the B part), the entries beyond 16 from memory.  bwq:
-// this lane's slot's B value.
-__device__ __forceinline__ void halo_bsums(const HaloBuf &Lb, uint32_t koffq, uint32_t boffq, float bwq, int nb,
-                                           uint32_t q16, const float *__restrict__ bslot, int bo,
-                                           const int32_t *__restrict__ xcol, int x0, const char *Xc, const char *Yc,
-                                           uint32_t RS, uint32_t coff, bool only_prev, F4 &bacc) {
-    // re-read the K part's rows from LDS instead of keeping the K sums' reads live
-    asm volatile("" : "+v"(koffq));
-    // slots j >= nb carry B = 0: the vector-lane kernels add 0 * 0 there, which leaves
-    // bacc unchanged (it starts at +0 and a sum that starts at +0 never becomes -0),
-    // so skipping them keeps the bits
-    static_for<0, 16, kHChunk>([&](auto J0) {
-        constexpr int j0 = decltype(J0)::value;
-        if (j0 < nb) {
-            F4 y[kHChunk];
-            static_for<0, kHChunk>([&](auto J) {
-                if (j0 + J.value < nb) {
-                    const F4 xv = lds_row(Lb, row_bcast<j0 + J.value>(koffq) + q16);
-                    const F4 yv = lds_row(Lb, row_bcast<j0 + J.value>(boffq) + q16);
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) y[J.value][i] = bdiff(xv[i], yv[i], only_prev);
-                }
-            });
-            static_for<0, kHChunk>([&](auto J) {
-                if (j0 + J.value < nb) bacc = vfma(row_bcast<j0 + J.value>(bwq), y[J.value], bacc);
-            });
-        }
-    });
-    for (int k = x0; k < x0 + nb - 16; ++k) {
-        const uint32_t off = uint32_t(xcol[k]) * RS + coff + q16;
-        const F4 xv = *reinterpret_cast<const F4 *>(Xc + off);
-        const F4 yv = *reinterpret_cast<const F4 *>(Yc + off);
-        F4 dv;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) dv[i] = bdiff(xv[i], yv[i], only_prev);
-        bacc = vfma(bslot[bo + 16 + (k - x0)], dv, bacc);
-    }
-}
-
-// Pipeline of one workgroup over its work items: fn_list(d, list) starts the copy
-// of an item's halo row list, fn_issue(it, d, list, buffer) the copies of its halo
-// and metadata, fn_pre(it, d) loads its own rows into the "next" registers and
-// fn_rot moves them to the "current" ones, fn_compute(it, d, buffer) computes
-// item it into registers and fn_store() writes the last computed item.  While
-// item it is computed, the copies of item it + 1, the row list of item it + 2 and
-// the descriptor of item it + 4 are in flight, and item it - 1's stores drain.
-// Even items use (B0, L0), odd items (B1, L1); the loop is unrolled by two so
-// that each access names its buffer at compile time.
-template <typename List, typename Issue, typename Pre, typename Rot, typename Compute, typename Store>
-__device__ __forceinline__ void halo_loop(const HWork &wk, const int32_t *hdesc, HaloBuf &B0, HaloBuf &B1,
-                                          HaloList &L0, HaloList &L1, List fn_list, Issue fn_issue, Pre fn_pre,
-                                          Rot fn_rot, Compute fn_compute, Store fn_store) {
-    const int n = wk.n;
-    if (n == 0) return;
-    const int4 *D = reinterpret_cast<const int4 *>(hdesc);
-    auto raw = [&](int it) { return it < n ? D[wk.tile(it)] : int4{0, 0, 0, 0}; };
-    HDesc d0 = desc_uniform(raw(0)), d1 = desc_uniform(raw(1)), d2 = desc_uniform(raw(2));
-    fn_list(d0, L0.r);
-    if (1 < n) fn_list(d1, L1.r);
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    __syncthreads();
-    fn_issue(0, d0, L0.r, B0);
-    fn_pre(0, d0);
-    int4 u3 = raw(3);
-    __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the copies of item 0 have landed
-    __syncthreads();
-    auto step = [&](int it, HaloBuf &Bc, HaloBuf &Bn, HaloList &Lc, HaloList &Ln) {
-        fn_rot();
-        if (it + 1 < n) fn_issue(it + 1, d1, Ln.r, Bn);
-        if (it + 2 < n) fn_list(d2, Lc.r);
-        if (it > 0) fn_store();
-        if (it + 1 < n) fn_pre(it + 1, d1);
-        const int4 u4 = raw(it + 4);
-        fn_compute(it, d0, Bc);
-        __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0): the copies of item it + 1 and list it + 2 have landed
-        __syncthreads();                     // ... for every wave, and item it's buffer is free
-        d0 = d1;
-        d1 = d2;
-        d2 = desc_uniform(u3);
-        u3 = u4;
-    };
-    for (int it = 0; it < n; it += 2) {
-        step(it, B0, B1, L0, L1);
-        if (it + 1 < n) step(it + 1, B1, B0, L1, L0);
-    }
-    fn_store();
-}
-
-// One halo-tile step (forward: FWD, no sources; transposed: sources, and with LAST the
-// closing launch).  The K part of a tile's halo holds rows of S, the B part rows of
-// Sp; each row's own Sp comes from memory one item ahead.  (LAST is a template
-// parameter: as a run-time flag its selects cost 2% of every step.)
-template <bool FWD, bool LAST, int RB, bool NT, typename Args, typename Src>
-__device__ __forceinline__ void halo_step(const Args &a, Src fn_src) {
-    constexpr int NC = RB / 64;
-    constexpr uint32_t RS = uint32_t(RB) * 4u;
-    __shared__ HaloBuf B0, B1;
-    __shared__ HaloList L0, L1;
-    const int tid = int(threadIdx.x), wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, g = tid >> 4,
-              q = tid & 15;
-    const HWork wk(a.n_ht, NC);
-    const char *Sc = reinterpret_cast<const char *>(a.S);
-    const char *Spc = reinterpret_cast<const char *>(a.Sp);
-    F4 prev_cur = {}, prev_nxt = {}, out = {};
-    uint32_t out_id = kNoRow;  // byte offset of the pending result, kNoRow: none
-    auto fn_list = [&](const HDesc &d, int32_t *list) {
-        halo_list_issue(a.hrow, d, d.nk4 + d.nb4, list, wave, lane);
-    };
-    auto fn_issue = [&](int it, const HDesc &d, const int32_t *list, HaloBuf &Bn) {
-        halo_issue<RS>(Sc, Spc, uint32_t(wk.chunk(it)) * 256u, a.hmeta, d, d.nk4 + d.nb4, list, Bn, wave, lane);
-    };
-    auto fn_pre = [&](int it, const HDesc &d) {
-        if (g < d.nr)
-            prev_nxt = vload_own<NT, F4>(reinterpret_cast<const float *>(
-                Spc + (uint32_t(d.r0 + g) * RS + uint32_t(wk.chunk(it)) * 256u + uint32_t(q) * 16u)));
-    };
-    auto fn_rot = [&]() { prev_cur = prev_nxt; };
-    auto fn_store = [&]() {
-        if (out_id != kNoRow) vstore<NT, F4>(reinterpret_cast<float *>(reinterpret_cast<char *>(a.Sn) + out_id), out);
-    };
-    auto fn_compute = [&](int it, const HDesc &d, const HaloBuf &Lb) {
-        out_id = kNoRow;
-        if (g >= d.nr) return;
-        const int c = wk.chunk(it);
-        const uint32_t coff = uint32_t(c) * 256u, q16 = uint32_t(q) * 16u;
-        const HLane h = halo_lane(Lb, d.nr, g, q);
-        const uint32_t hw = hl_word(h);
-        const int x0 = hl_x0(h), x1 = x0 + hw_nx(hw);
-        F4 acc = {}, bacc = {}, cur;
-        halo_ksums(Lb, h, q16, x0, x1, a.o.xval, a.o.xcol, Sc, RS, coff, acc, cur);
-        const int row = d.r0 + g;
-        if (hw_brow(hw) != 0xFF) {
-            const int nb = hw_bnum(hw), br = hw_brow(hw);
-            const int bo = nb > 16 ? a.o.bsoff[row] : 0;
-            halo_bsums(Lb, h.koff, hb_offset(Lb, d.nr, d.nbr, br, q, d.nk4), hb_value(Lb, d.nr, br, q), nb, q16,
-                       a.o.bslot, bo, a.o.xcol, x0, Sc, Spc, RS, coff, LAST, bacc);
-        }
-        const float dm = hl_dm(h);
-        F4 inj = {};
-        if constexpr (!FWD) {
-            const int e0 = hl_inj0(h), e1 = e0 + hw_ninj(hw);
-            if (e1 > e0) inj = fn_src(e0, e1, c * 64 + q * 4);
-        }
-        F4 res;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const float src = 0.5f * inj[i];
-            if constexpr (LAST) res[i] = adj_result(cur[i], prev_cur[i], acc[i], bacc[i], src, dm, a.dt);
-            else res[i] = step_update(cur[i], prev_cur[i], acc[i], bacc[i], src, dm, a.dt);
-        }
-        out = res;
-        out_id = uint32_t(row) * RS + coff + q16;
-    };
-    halo_loop(wk, a.hdesc, B0, B1, L0, L1, fn_list, fn_issue, fn_pre, fn_rot, fn_compute, fn_store);
-}
-
-template <typename OT, int RB, bool NT>
-__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(4)))
-k_fwd_h(const VFwdArgs<float> a) {
-    halo_step<true, false, RB, NT>(a, [](int, int, int) { return F4{}; });
-    if (a.sample) {
-        // y = Pi (S^n + S^{n-1})/2 of the incoming state, one lane per (sensor, rhs)
-        const int64_t total = int64_t(a.n_obs) * RB;
-        OT *yo = static_cast<OT *>(a.y);
-        for (int64_t e = int64_t(blockIdx.x) * kHThreads + threadIdx.x; e < total;
-             e += int64_t(gridDim.x) * kHThreads) {
-            const int s = int(e / RB), rr = int(e % RB);
-            float y = 0.0f;
-            for (int k = 0; k < 4; ++k) {
-                const int64_t id = int64_t(a.snode[4 * s + k]) * RB + rr;
-                y = mad(a.sw[4 * s + k], 0.5f * (a.S[id] + a.Sp[id]), y);
-            }
-            yo[(int64_t(a.t) * a.n_obs + s) * RB + rr] = static_cast<OT>(static_cast<double>(y) * a.yscale);
-        }
-    }
-}
-
-template <typename YT, int RB, bool NT, bool LAST>
-__global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(4)))
-k_adj_h(const VAdjArgs<float> a) {
-    halo_step<false, LAST, RB, NT>(a, [&](int e0, int e1, int rhs0) { return vinject<float, YT, RB, F4>(a, e0, e1, rhs0); });
 }
 
 // q_{-1} = 0 and q_0 = (dt/2m) Pi^T yhat^{tb} (tb = N_T - 1, the last sample)
@@ -1693,12 +1302,12 @@ RowOps<T> row_ops(const DevOps &op);
 template <>
 RowOps<double> row_ops<double>(const DevOps &op) {
     return RowOps<double>{op.ell_col, op.xcol, op.ell_val64, op.xval64, op.bslot64, op.dtm64, op.rspec,
-                          op.spec, op.bsoff};
+                          op.spec};
 }
 template <>
 RowOps<float> row_ops<float>(const DevOps &op) {
     return RowOps<float>{op.ell_col, op.xcol, op.ell_val32, op.xval32, op.bslot32, op.dtm32, op.rspec,
-                          op.spec, op.bsoff};
+                          op.spec};
 }
 template <typename T>
 const T *sw_of(const DevOps &op);
@@ -1732,19 +1341,8 @@ VFwdArgs<T> fwd_args_v(const DevOps &op, const void *S, const void *Sp, void *Sn
     a.dt = T(op.dt);
     a.n_samp = sample ? int((int64_t(op.n_obs) * RB + 255) / 256) : 0;
     a.stream = state_bytes(op, RB, sizeof(T)) > kInfinityCacheBytes;
-    a.hdesc = op.ht_desc; a.hrow = op.ht_hrow; a.hmeta = op.ht_meta; a.n_ht = op.n_ht;
     *blocks = a.n_tiles + a.n_samp;
     return a;
-}
-
-// workgroups of a halo kernel launch: as many per CU as the LDS allows, a multiple of the 8 XCDs
-inline int halo_grid(const DevOps &op) { return (kHPerCU * op.n_cu + 7) / 8 * 8; }
-
-// the halo kernels take float32 blocks of 256-byte row chunks (rows == false:
-// a sampling-only launch stays with the vector-lane kernel)
-template <typename T, int RB>
-bool use_halo(const DevOps &op, bool rows) {
-    return std::is_same<T, float>::value && RB >= 64 && RB <= 256 && rows && op.n_ht > 0 && op.n_cu > 0;
 }
 
 template <typename T, typename OT, int RB>
@@ -1753,13 +1351,6 @@ void fwd_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool 
     int grid = 0;
     const VFwdArgs<T> a = fwd_args_v<T, RB>(op, S, Sp, Sn, rows, sample, t, y, yscale, &grid);
     if (grid <= 0) return;
-    if constexpr (std::is_same<T, float>::value && RB >= 64 && RB <= 256) {
-        if (use_halo<T, RB>(op, rows)) {
-            if (a.stream) hipLaunchKernelGGL((k_fwd_h<OT, RB, true>), dim3(halo_grid(op)), dim3(kHThreads), 0, s, a);
-            else hipLaunchKernelGGL((k_fwd_h<OT, RB, false>), dim3(halo_grid(op)), dim3(kHThreads), 0, s, a);
-            return;
-        }
-    }
     if (a.stream) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, true>), dim3(grid), dim3(256), 0, s, a);
     else hipLaunchKernelGGL((k_fwd_v<T, OT, RB, false>), dim3(grid), dim3(256), 0, s, a);
 }
@@ -1794,7 +1385,6 @@ VAdjArgs<T> adj_args_v(const DevOps &op, const void *S, const void *Sp, void *Sn
     a.n_tiles = (op.n + G::RPB - 1) / G::RPB;
     a.dt = T(op.dt);
     a.stream = state_bytes(op, RB, sizeof(T)) > kInfinityCacheBytes;
-    a.hdesc = op.ht_desc; a.hrow = op.ht_hrow; a.hmeta = op.ht_meta; a.n_ht = op.n_ht;
     return a;
 }
 
@@ -1802,19 +1392,6 @@ template <typename T, typename YT, int RB>
 void adj_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool last, int tb, const void *yh,
                 double yscale, hipStream_t s) {
     const VAdjArgs<T> a = adj_args_v<T, RB>(op, S, Sp, Sn, last, tb, yh, yscale);
-    if constexpr (std::is_same<T, float>::value && RB >= 64 && RB <= 256) {
-        if (use_halo<T, RB>(op, true)) {
-            const dim3 g(halo_grid(op)), b(kHThreads);
-            if (a.stream) {
-                if (last) hipLaunchKernelGGL((k_adj_h<YT, RB, true, true>), g, b, 0, s, a);
-                else hipLaunchKernelGGL((k_adj_h<YT, RB, true, false>), g, b, 0, s, a);
-            } else {
-                if (last) hipLaunchKernelGGL((k_adj_h<YT, RB, false, true>), g, b, 0, s, a);
-                else hipLaunchKernelGGL((k_adj_h<YT, RB, false, false>), g, b, 0, s, a);
-            }
-            return;
-        }
-    }
     const dim3 g(a.n_tiles), b(256);
     if (last) hipLaunchKernelGGL((k_adj_v<T, YT, RB, false, true>), g, b, 0, s, a);
     else if (a.stream) hipLaunchKernelGGL((k_adj_v<T, YT, RB, true, false>), g, b, 0, s, a);
@@ -1925,6 +1502,10 @@ void adj_multi(const AdjStep *st, int n, hipStream_t s) {
 
 void launch_fwd_step(Prec prec, int RB, const DevOps &op, const void *S, const void *Sp, void *Sn, bool rows,
                      bool sample, int t, void *y, bool y_is_f64, double yscale, hipStream_t s) {
+    if (rows && halo_step_supported(prec, RB, op)) {  // the sampling launch that ends a sweep has no rows
+        launch_fwd_halo(prec, RB, op, S, Sp, Sn, sample, t, y, y_is_f64, yscale, s);
+        return;
+    }
     if (prec == Prec::F64) {
         PAT_RB_SWITCH(RB, (fwd_impl<double, double, RB_>(op, S, Sp, Sn, rows, sample, t, y, yscale, s)));
     } else if (y_is_f64) {
@@ -1947,6 +1528,10 @@ void launch_adj_init(Prec prec, int RB, const DevOps &op, void *q0, void *qm1, c
 
 void launch_adj_step(Prec prec, int RB, const DevOps &op, const void *S, const void *Sp, void *Sn, bool last, int tb,
                      const void *yhat, bool y_is_f64, double yscale, hipStream_t s) {
+    if (halo_step_supported(prec, RB, op)) {
+        launch_adj_halo(prec, RB, op, S, Sp, Sn, last, tb, yhat, y_is_f64, yscale, s);
+        return;
+    }
     if (prec == Prec::F64) {
         PAT_RB_SWITCH(RB, (adj_impl<double, double, RB_>(op, S, Sp, Sn, last, tb, yhat, yscale, s)));
     } else if (y_is_f64) {

@@ -47,3 +47,13 @@ def test_block_widths(R, dtype, tol):
     O, G = _problem(17, 6)
     print(f"block width {R} {dtype}", flush=True)
     _check(O, G, R, dtype, tol)
+
+
+# Whole 256-byte chunks on a mesh with enough halo tiles (24,389 nodes) run the halo-tile
+# kernels: one, two and four chunks per row.
+@pytest.mark.parametrize("R,dtype,tol", [(32, torch.float64, 1e-11), (64, torch.float64, 1e-11),
+                                         (64, torch.float32, 2e-5)])
+def test_halo_widths(R, dtype, tol):
+    O, G = _problem(28, 3)
+    print(f"halo width {R} {dtype}", flush=True)
+    _check(O, G, R, dtype, tol)
