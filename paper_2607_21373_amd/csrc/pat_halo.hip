@@ -385,8 +385,23 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
             if constexpr (j0 == 0) cur = xs[0];
             static_for<0, kHChunk>([&](auto J) { acc = hfma(row_bcast<j0 + J.value>(o.kv), xs[J.value], acc); });
         });
-        for (int k = x0; k < x0 + nx; ++k)
-            acc = hfma(a.xval[k], *reinterpret_cast<const VT *>(Sc + (uint32_t(a.xcol[k]) * RS + coff + q16)), acc);
+        for (int k = 0; k < nx; k += 4) {  // four entries' loads at a time, clamped to the row's last
+            T w[4];
+            int cl[4];
+            VT xv[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int e = x0 + min(k + j, nx - 1);
+                cl[j] = a.xcol[e];
+                w[j] = a.xval[e];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                xv[j] = *reinterpret_cast<const VT *>(Sc + (uint32_t(cl[j]) * RS + coff + q16));
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (k + j < nx) acc = hfma(w[j], xv[j], acc);
+        }
         const int br = int(hw & 0xFFu);
         if (br != 0xFF) {
             int nb = int((hw >> 8) & 0xFFu);

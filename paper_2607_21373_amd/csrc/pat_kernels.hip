@@ -273,15 +273,18 @@ struct Vec16<double> {
 
 // Gathers in flight per lane before they are consumed.
 constexpr int kGatherChunk = 8;
+// Variants of the vector-lane kernels: plain, with non-temporal own rows (beyond the
+// Infinity Cache), and for launches with few waves.
+enum class Var : int { Plain, Stream, Few };
 // Waves per SIMD the register allocation of the step kernels must allow.  Rows of 16
 // or 32 bytes put 64 or 32 rows on a wave, so a launch has few waves and takes the
 // registers; wider rows need the waves (two chunks of eight gathers and the four-slot
 // boundary chunks fit 96 registers).
 template <typename T, int RB>
-constexpr int vwaves() {
-    return RB * sizeof(T) <= 32 ? 2 : 5;
+constexpr int vwaves(Var v) {
+    return v == Var::Few ? 1 : RB * sizeof(T) <= 32 ? 2 : 5;
 }
-#define PAT_VOCC(T, RB) __attribute__((amdgpu_waves_per_eu(vwaves<T, RB>())))
+#define PAT_VOCC(T, RB, VAR) __attribute__((amdgpu_waves_per_eu(vwaves<T, RB>(VAR))))
 
 // Stores of the new state and loads of a row's own state (each touched once per
 // step).  When the step's state exceeds the Infinity Cache (`stream`), they are
@@ -374,7 +377,10 @@ __device__ __forceinline__ VT vfma(T w, VT x, VT acc) {
 // together and the kernel keeps the register budget (and occupancy) of the interior
 // rows.  Slot 0 of every row is its diagonal, so the first gather is the row's own
 // X value; it is returned in `own`.  sp: the row's rspec, its record is returned in rs.
-template <typename T, int RB>
+// LAT (launches with few waves, see few_waves): everything a row needs is in flight at
+// once, all 16 gathers and, as soon as the row's record is there, the boundary gathers,
+// so that a wave waits for three round trips instead of up to seven.
+template <typename T, int RB, bool LAT>
 __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, const T *__restrict__ X,
                                           const T *__restrict__ Y, bool only_prev, typename Vec16<T>::t &acc,
                                           typename Vec16<T>::t &bacc, typename Vec16<T>::t &own,
@@ -387,6 +393,25 @@ __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, con
     const char *Yc = reinterpret_cast<const char *>(Y);
     const uint32_t qoff = uint32_t(q) * 16u;
     constexpr uint32_t ROWB = uint32_t(RB * sizeof(T));
+    constexpr int YL = LAT ? 12 : 0;  // boundary slots gathered early (more follow below)
+    VT ye[YL + 1], xe[YL + 1];
+    SlotRegs<T, RB, T> bv;
+    if constexpr (LAT) {
+        if (sp) rs.load(o.spec, sp);
+        VT x[G::W];
+        static_for<0, G::W>([&](auto J) {
+            x[J.value] = *reinterpret_cast<const VT *>(Xc + (uint32_t(off.template get<J.value>()) + qoff));
+        });
+        if (rs.nb) {
+            bv.load(o.bslot + rs.bo, q);
+            static_for<0, YL>([&](auto J) {
+                ye[J.value] = *reinterpret_cast<const VT *>(Yc + (uint32_t(off.template get<J.value>()) + qoff));
+            });
+        }
+        own = x[0];
+        static_for<0, G::W>([&](auto J) { acc = vfma(kv.template get<J.value>(), x[J.value], acc); });
+        static_for<0, YL>([&](auto J) { xe[J.value] = x[J.value]; });
+    } else
     static_for<0, G::W, CH>([&](auto J0) {
         constexpr int j0 = decltype(J0)::value;
         VT x[CH];
@@ -405,9 +430,21 @@ __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, con
     });
     pin(acc);  // the sums end here: moved further down, they would keep the gathers live
     if (!sp) return;
-    for (int k = rs.x0; k < rs.x1; ++k) {
-        const VT xv = *reinterpret_cast<const VT *>(Xc + (uint32_t(o.xcol[k]) * ROWB + qoff));
-        acc = vfma(o.xval[k], xv, acc);
+    for (int k = rs.x0; k < rs.x1; k += 4) {  // four entries at a time, clamped to the row's last
+        int c[4];
+        T w[4];
+        VT xv[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = min(k + j, rs.x1 - 1);
+            c[j] = o.xcol[e];
+            w[j] = o.xval[e];
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) xv[j] = *reinterpret_cast<const VT *>(Xc + (uint32_t(c[j]) * ROWB + qoff));
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (k + j < rs.x1) acc = vfma(w[j], xv[j], acc);
     }
     if (rs.nb) {
         // only the row's first bnum slots carry B; the neighbours' X values are read again
@@ -415,10 +452,15 @@ __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, con
         uint32_t boff = qoff;
         asm volatile("" : "+v"(boff));
         const int nb = rs.nb;
-        SlotRegs<T, RB, T> bv;
-        bv.load(o.bslot + rs.bo, q);
-        constexpr int BCH = G::HL < 4 ? 8 : 4;  // slots at a time, two gathers each
-        static_for<0, G::W, BCH>([&](auto J0) {
+        if constexpr (!LAT) bv.load(o.bslot + rs.bo, q);
+        static_for<0, YL>([&](auto J) {
+            VT d;
+#pragma unroll
+            for (int i = 0; i < G::VEC; ++i) d[i] = bdiff(xe[J.value][i], ye[J.value][i], only_prev);
+            if (J.value < nb) bacc = vfma(bv.template get<J.value>(), d, bacc);
+        });
+        constexpr int BCH = G::HL < 4 && !LAT ? 8 : 4;  // slots at a time, two gathers each
+        static_for<YL, G::W, BCH>([&](auto J0) {
             constexpr int j0 = decltype(J0)::value;
             if (j0 < nb) {
                 VT y[BCH], z[BCH];
@@ -496,7 +538,7 @@ __device__ __forceinline__ void fwd_sample(const VFwdArgs<T> &a, int j) {
 
 // Forward step (same update as k_fwd) with vector lanes on logical tile `tile`;
 // the tiles after the row tiles write the samples of the incoming state.
-template <typename T, typename OT, int RB, bool NT>
+template <typename T, typename OT, int RB, Var VAR>
 __device__ __forceinline__ void fwd_tile(const VFwdArgs<T> &a, int tile) {
     using G = VGeo<T, RB>;
     using VT = typename Vec16<T>::t;
@@ -510,22 +552,22 @@ __device__ __forceinline__ void fwd_tile(const VFwdArgs<T> &a, int tile) {
         load_slots<T, RB>(a.o, row, q, off, kv);
         const int sp = a.o.rspec[row];
         const T dm = a.o.dtm[row];
-        const VT prev = vload_own<NT, VT>(a.Sp + id);
+        const VT prev = vload_own<VAR == Var::Stream, VT>(a.Sp + id);
         VT acc = {}, bacc = {}, cur;
         RowSpec rs;
-        vrow_sums<T, RB>(a.o, q, sp, a.S, a.Sp, false, acc, bacc, cur, off, kv, rs);
+        vrow_sums<T, RB, VAR == Var::Few>(a.o, q, sp, a.S, a.Sp, false, acc, bacc, cur, off, kv, rs);
         VT sn;
 #pragma unroll
         for (int i = 0; i < G::VEC; ++i) sn[i] = step_update(cur[i], prev[i], acc[i], bacc[i], T(0), dm, a.dt);
-        vstore<NT, VT>(a.Sn + id, sn);
+        vstore<VAR == Var::Stream, VT>(a.Sn + id, sn);
     } else if (a.sample) {
         fwd_sample<T, OT, RB>(a, tile - a.n_tiles);
     }
 }
 
-template <typename T, typename OT, int RB, bool NT>
-__global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_fwd_v(const VFwdArgs<T> a) {
-    fwd_tile<T, OT, RB, NT>(a, fwd_work(xcd_tile(blockIdx.x, gridDim.x), a.n_tiles, a.n_samp));
+template <typename T, typename OT, int RB, Var VAR>
+__global__ void __launch_bounds__(256) PAT_VOCC(T, RB, VAR) k_fwd_v(const VFwdArgs<T> a) {
+    fwd_tile<T, OT, RB, VAR>(a, fwd_work(xcd_tile(blockIdx.x, gridDim.x), a.n_tiles, a.n_samp));
 }
 
 // Several meshes in one launch; mesh m has tiles[m] logical tiles.  Every XCD
@@ -541,11 +583,11 @@ struct Multi {
     int n;
 };
 
-template <typename T, typename OT, int RB, bool NT>
-__global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_fwd_vm(const Multi<VFwdArgs<T>> mm) {
+template <typename T, typename OT, int RB, Var VAR>
+__global__ void __launch_bounds__(256) PAT_VOCC(T, RB, VAR) k_fwd_vm(const Multi<VFwdArgs<T>> mm) {
     int m, local;
     if (!mesh_tile(mm.tiles, mm.n, blockIdx.x, &m, &local, false)) return;
-    fwd_tile<T, OT, RB, NT>(mm.a[m], fwd_work(local, mm.a[m].n_tiles, mm.a[m].n_samp));
+    fwd_tile<T, OT, RB, VAR>(mm.a[m], fwd_work(local, mm.a[m].n_tiles, mm.a[m].n_samp));
 }
 
 template <typename T>
@@ -586,7 +628,7 @@ __device__ __forceinline__ VT vinject(const VAdjArgs<T> &a, int e0, int e1, int 
 
 // Transposed step (same update as k_adj) with vector lanes on logical tile `tile`;
 // LAST: the closing launch.
-template <typename T, typename YT, int RB, bool NT, bool LAST>
+template <typename T, typename YT, int RB, Var VAR, bool LAST>
 __device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile) {
     using G = VGeo<T, RB>;
     using VT = typename Vec16<T>::t;
@@ -600,10 +642,10 @@ __device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile) {
     SlotRegs<T, RB, T> kv;
     load_slots<T, RB>(a.o, row, q, off, kv);
     const T dm = a.o.dtm[row];
-    const VT prev = vload_own<NT, VT>(a.Sp + id);
+    const VT prev = vload_own<VAR == Var::Stream, VT>(a.Sp + id);
     VT kq = {}, bq = {}, cur, inj = {};
     RowSpec rs;
-    vrow_sums<T, RB>(a.o, q, sp, a.S, a.Sp, LAST, kq, bq, cur, off, kv, rs);
+    vrow_sums<T, RB, VAR == Var::Few>(a.o, q, sp, a.S, a.Sp, LAST, kq, bq, cur, off, kv, rs);
     if (rs.e1 > rs.e0) inj = vinject<T, YT, RB, VT>(a, rs.e0, rs.e1, q * G::VEC);
     VT out;
 #pragma unroll
@@ -612,19 +654,19 @@ __device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile) {
         if constexpr (LAST) out[i] = adj_result(cur[i], prev[i], kq[i], bq[i], src, dm, a.dt);
         else out[i] = step_update(cur[i], prev[i], kq[i], bq[i], src, dm, a.dt);
     }
-    vstore<NT, VT>(a.Sn + id, out);
+    vstore<VAR == Var::Stream, VT>(a.Sn + id, out);
 }
 
-template <typename T, typename YT, int RB, bool NT, bool LAST>
-__global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_adj_v(const VAdjArgs<T> a) {
-    adj_tile<T, YT, RB, NT, LAST>(a, xcd_tile_rev(blockIdx.x, gridDim.x));
+template <typename T, typename YT, int RB, Var VAR, bool LAST>
+__global__ void __launch_bounds__(256) PAT_VOCC(T, RB, VAR) k_adj_v(const VAdjArgs<T> a) {
+    adj_tile<T, YT, RB, VAR, LAST>(a, xcd_tile_rev(blockIdx.x, gridDim.x));
 }
 
-template <typename T, typename YT, int RB, bool NT, bool LAST>
-__global__ void __launch_bounds__(256) PAT_VOCC(T, RB) k_adj_vm(const Multi<VAdjArgs<T>> mm) {
+template <typename T, typename YT, int RB, Var VAR, bool LAST>
+__global__ void __launch_bounds__(256) PAT_VOCC(T, RB, VAR) k_adj_vm(const Multi<VAdjArgs<T>> mm) {
     int m, local;
     if (!mesh_tile(mm.tiles, mm.n, blockIdx.x, &m, &local, true)) return;
-    adj_tile<T, YT, RB, NT, LAST>(mm.a[m], local);
+    adj_tile<T, YT, RB, VAR, LAST>(mm.a[m], local);
 }
 
 // q_{-1} = 0 and q_0 = (dt/2m) Pi^T yhat^{tb} (tb = N_T - 1, the last sample)
@@ -1345,14 +1387,22 @@ VFwdArgs<T> fwd_args_v(const DevOps &op, const void *S, const void *Sp, void *Sn
     return a;
 }
 
+// Launches of at most 512 workgroups, two waves per SIMD, take the variant with everything
+// in flight and up to 200 registers: it saves round trips (15,625 nodes, 8 float32 RHS 4.5 /
+// 4.9 -> 4.0 / 4.6 us per forward / transposed step, 4,913 nodes, 16 RHS 4.9 -> 4.6), and
+// loses once a launch has the waves to hide them (64,000 nodes, 16 RHS 7.0 -> 7.8).
+inline bool few_waves(int workgroups) { return workgroups <= 512; }
+
 template <typename T, typename OT, int RB>
 void fwd_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool rows, bool sample, int t, void *y,
                 double yscale, hipStream_t s) {
     int grid = 0;
     const VFwdArgs<T> a = fwd_args_v<T, RB>(op, S, Sp, Sn, rows, sample, t, y, yscale, &grid);
     if (grid <= 0) return;
-    if (a.stream) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, true>), dim3(grid), dim3(256), 0, s, a);
-    else hipLaunchKernelGGL((k_fwd_v<T, OT, RB, false>), dim3(grid), dim3(256), 0, s, a);
+    const dim3 g(grid), b(256);
+    if (few_waves(grid)) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Few>), g, b, 0, s, a);
+    else if (a.stream) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Stream>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Plain>), g, b, 0, s, a);
 }
 
 template <typename T, typename OT, int RB>
@@ -1366,8 +1416,9 @@ void fwd_impl_vm(const FwdStep *st, int n, hipStream_t s) {
     for (int m = 0; m < n; ++m) sb += state_bytes(*st[m].op, RB, sizeof(T));
     const int grid = multi_grid(mm.tiles, n);
     if (grid <= 0) return;
-    if (sb > kInfinityCacheBytes) hipLaunchKernelGGL((k_fwd_vm<T, OT, RB, true>), dim3(grid), dim3(256), 0, s, mm);
-    else hipLaunchKernelGGL((k_fwd_vm<T, OT, RB, false>), dim3(grid), dim3(256), 0, s, mm);
+    const dim3 g(grid), b(256);
+    if (sb > kInfinityCacheBytes) hipLaunchKernelGGL((k_fwd_vm<T, OT, RB, Var::Stream>), g, b, 0, s, mm);
+    else hipLaunchKernelGGL((k_fwd_vm<T, OT, RB, Var::Plain>), g, b, 0, s, mm);
 }
 
 template <typename T, int RB>
@@ -1393,9 +1444,10 @@ void adj_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool 
                 double yscale, hipStream_t s) {
     const VAdjArgs<T> a = adj_args_v<T, RB>(op, S, Sp, Sn, last, tb, yh, yscale);
     const dim3 g(a.n_tiles), b(256);
-    if (last) hipLaunchKernelGGL((k_adj_v<T, YT, RB, false, true>), g, b, 0, s, a);
-    else if (a.stream) hipLaunchKernelGGL((k_adj_v<T, YT, RB, true, false>), g, b, 0, s, a);
-    else hipLaunchKernelGGL((k_adj_v<T, YT, RB, false, false>), g, b, 0, s, a);
+    if (last) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Plain, true>), g, b, 0, s, a);
+    else if (few_waves(a.n_tiles)) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Few, false>), g, b, 0, s, a);
+    else if (a.stream) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Stream, false>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Plain, false>), g, b, 0, s, a);
 }
 
 template <typename T, typename YT, int RB>
@@ -1412,9 +1464,9 @@ void adj_impl_vm(const AdjStep *st, int n, hipStream_t s) {
     const int grid = multi_grid(mm.tiles, n);
     if (grid <= 0) return;
     const dim3 g(grid), b(256);
-    if (st[0].last) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, false, true>), g, b, 0, s, mm);
-    else if (sb > kInfinityCacheBytes) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, true, false>), g, b, 0, s, mm);
-    else hipLaunchKernelGGL((k_adj_vm<T, YT, RB, false, false>), g, b, 0, s, mm);
+    if (st[0].last) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, Var::Plain, true>), g, b, 0, s, mm);
+    else if (sb > kInfinityCacheBytes) hipLaunchKernelGGL((k_adj_vm<T, YT, RB, Var::Stream, false>), g, b, 0, s, mm);
+    else hipLaunchKernelGGL((k_adj_vm<T, YT, RB, Var::Plain, false>), g, b, 0, s, mm);
 }
 
 template <typename T, typename OT, int RB>
