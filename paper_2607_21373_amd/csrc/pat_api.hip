@@ -730,13 +730,8 @@ struct Solve {
 // Residual history column `it` from the data part rd [M][RB] and prior part rp [N][RB].
 void record(Solve &v, const double *rd, const double *rp, int it) {
     if (!v.resid_hist && !v.diag_hist) return;
-    double *pA = v.c->part, *pB = v.c->part + pat::kDotBlocks * v.RB;
-    double *t1 = v.c->scal + 14 * v.RB, *t2 = v.c->scal + 15 * v.RB;
-    pat::launch_dot_partial(rd, rd, v.M, v.RB, pA, v.s);
-    pat::launch_dot_partial(rp, rp, v.NX, v.RB, pB, v.s);
-    pat::launch_dot_final(pA, nullptr, v.RB, t1, v.s);
-    pat::launch_dot_final(pB, nullptr, v.RB, t2, v.s);
-    pat::launch_resid(t1, t2, v.resid_hist, v.diag_hist, v.ld, it, v.rb0, v.S, v.RB, v.s);
+    const pat::NormParts n = pat::launch_norms(rd, v.M, rp, v.NX, v.RB, v.c->part, v.s);
+    pat::launch_norm_resid(n, v.resid_hist, v.diag_hist, v.ld, it, v.rb0, v.S, v.RB, v.s);
 }
 
 // s -= Q coef over the basis Q_j, j < k: classical Gram-Schmidt applied twice, in the
@@ -769,22 +764,19 @@ void prior_part(Solve &v, const double *x) {
 // ---- CGLS: b in (rd, rp) and x = 0 on entry.  The normal-equation residuals
 // s_j are kept orthogonal by two classical Gram-Schmidt passes (App. A).
 struct CglsScal {
-    double *gamma, *delta, *alpha, *beta, *invn, *gnew;
+    double *gamma, *alpha, *beta, *invn;
     explicit CglsScal(const Solve &v)
-        : gamma(v.c->scal), delta(v.c->scal + v.RB), alpha(v.c->scal + 2 * v.RB), beta(v.c->scal + 3 * v.RB),
-          invn(v.c->scal + 4 * v.RB), gnew(v.c->scal + 5 * v.RB) {}
+        : gamma(v.c->scal), alpha(v.c->scal + v.RB), beta(v.c->scal + 2 * v.RB), invn(v.c->scal + 3 * v.RB) {}
 };
 
 void cgls_post_adj(Solve &v, int k) {
     CglsWS *c = v.c;
     const CglsScal z(v);
-    double *pA = c->part;
     combine_t(v, c->rp);
     reorthogonalise(v, k);
-    pat::launch_dot_partial(c->s, c->s, v.NX, v.RB, pA, v.s);
-    pat::launch_dot_final(pA, nullptr, v.RB, z.gnew, v.s);
     // beta = gamma_new / gamma ; d = s + beta d ; Q[k] = s / ||s||
-    pat::launch_scalar_gamma(z.gamma, z.gnew, z.beta, z.invn, k == 0, v.RB, v.s);
+    const pat::NormParts n = pat::launch_norms(c->s, v.NX, nullptr, 0, v.RB, c->part, v.s);
+    pat::launch_norm_gamma(n, v.RB, z.gamma, z.beta, z.invn, k == 0, v.s);
     pat::launch_append_dir(c->s, v.reorth ? c->Q + size_t(k) * v.NX * v.RB : nullptr, c->d, z.invn, z.beta, k == 0,
                            v.NX, v.RB, v.s);
 }
@@ -792,13 +784,10 @@ void cgls_post_adj(Solve &v, int k) {
 void cgls_post_fwd(Solve &v, int k) {
     CglsWS *c = v.c;
     const CglsScal z(v);
-    double *pA = c->part, *pB = c->part + pat::kDotBlocks * v.RB;
     // q = (G d / sigma, L d) ; alpha = gamma / ||q||^2 ; x += alpha d ; r -= alpha q
     prior_part(v, c->d);
-    pat::launch_dot_partial(c->qd, c->qd, v.M, v.RB, pA, v.s);
-    pat::launch_dot_partial(c->qp, c->qp, v.NX, v.RB, pB, v.s);
-    pat::launch_dot_final(pA, pB, v.RB, z.delta, v.s);
-    pat::launch_scalar_alpha(z.gamma, z.delta, z.alpha, v.RB, v.s);
+    const pat::NormParts n = pat::launch_norms(c->qd, v.M, c->qp, v.NX, v.RB, c->part, v.s);
+    pat::launch_norm_alpha(n, v.RB, z.gamma, z.alpha, v.s);
     pat::launch_update_xr(c->x, c->d, c->rp, c->qp, z.alpha, v.NX, v.RB, v.s);
     pat::launch_axpy_neg(c->rd, c->qd, z.alpha, v.M, v.RB, v.s);
     record(v, c->rd, c->rp, k);
@@ -811,15 +800,12 @@ void cgls_post_fwd(Solve &v, int k) {
 // z = G_ext w) only when a history is asked for.
 struct LsqrState {
     pat::LsqrScalars L;
-    double *n1, *n2;
     bool track;
     explicit LsqrState(const Solve &v) {
         double *sc = v.c->scal;
         const int RB = v.RB;
         L = pat::LsqrScalars{sc, sc + RB, sc + 2 * RB, sc + 3 * RB, sc + 4 * RB, sc + 5 * RB,
                              sc + 6 * RB, sc + 7 * RB, sc + 8 * RB, sc + 9 * RB, sc + 10 * RB, sc + 11 * RB};
-        n1 = sc + 12 * RB;
-        n2 = sc + 13 * RB;
         track = v.resid_hist || v.diag_hist;
     }
 };
@@ -828,18 +814,14 @@ void lsqr_init(Solve &v) {
     CglsWS *c = v.c;
     const LsqrState z(v);
     const int RB = v.RB;
-    double *pA = c->part, *pB = c->part + pat::kDotBlocks * RB;
     if (z.track) {
         pat::launch_lincomb(c->lrd, c->rd, nullptr, 1.0, nullptr, nullptr, 0.0, v.M, RB, v.s);
         pat::launch_lincomb(c->lrp, c->rp, nullptr, 1.0, nullptr, nullptr, 0.0, v.NX, RB, v.s);
         record(v, c->lrd, c->lrp, 0);
     }
     // beta_1 u_1 = b
-    pat::launch_dot_partial(c->rd, c->rd, v.M, RB, pA, v.s);
-    pat::launch_dot_partial(c->rp, c->rp, v.NX, RB, pB, v.s);
-    pat::launch_dot_final(pA, nullptr, RB, z.n1, v.s);
-    pat::launch_dot_final(pB, nullptr, RB, z.n2, v.s);
-    pat::launch_lsqr_scalar(pat::LsqrStage::InitBeta, z.L, z.n1, z.n2, RB, v.s);
+    pat::launch_lsqr_scalar(pat::LsqrStage::InitBeta, z.L,
+                            pat::launch_norms(c->rd, v.M, c->rp, v.NX, RB, c->part, v.s), RB, v.s);
     pat::launch_lincomb(c->rd, c->rd, z.L.inv, 1.0, nullptr, nullptr, 0.0, v.M, RB, v.s);
     pat::launch_lincomb(c->rp, c->rp, z.L.inv, 1.0, nullptr, nullptr, 0.0, v.NX, RB, v.s);
 }
@@ -847,14 +829,12 @@ void lsqr_init(Solve &v) {
 void lsqr_post_adj(Solve &v, int k) {
     CglsWS *c = v.c;
     const LsqrState z(v);
-    double *pA = c->part;
     // alpha_{k+1} v_{k+1} = G_ext^T u_{k+1} - beta_{k+1} v_k, reorthogonalised ; w = v - zfac w
     combine_t(v, c->rp);
     if (k > 0) pat::launch_lincomb(c->s, c->s, nullptr, 1.0, c->v, z.L.beta, -1.0, v.NX, v.RB, v.s);
     reorthogonalise(v, k);
-    pat::launch_dot_partial(c->s, c->s, v.NX, v.RB, pA, v.s);
-    pat::launch_dot_final(pA, nullptr, v.RB, z.n1, v.s);
-    pat::launch_lsqr_scalar(k == 0 ? pat::LsqrStage::InitAlpha : pat::LsqrStage::Alpha, z.L, z.n1, nullptr, v.RB, v.s);
+    pat::launch_lsqr_scalar(k == 0 ? pat::LsqrStage::InitAlpha : pat::LsqrStage::Alpha, z.L,
+                            pat::launch_norms(c->s, v.NX, nullptr, 0, v.RB, c->part, v.s), v.RB, v.s);
     pat::launch_lsqr_vw(c->s, z.L.inv, z.L.zfac, c->v, c->d, v.reorth ? c->Q + size_t(k) * v.NX * v.RB : nullptr,
                         k == 0, v.NX, v.RB, v.s);
 }
@@ -864,7 +844,6 @@ void lsqr_post_fwd(Solve &v, int k) {
     const LsqrState z(v);
     const int RB = v.RB;
     const int64_t N = v.NX, M = v.M;
-    double *pA = c->part, *pB = c->part + pat::kDotBlocks * RB;
     // q = G_ext v_k ; z_k = q - zfac z_{k-1}
     prior_part(v, c->v);
     if (z.track) {
@@ -874,11 +853,8 @@ void lsqr_post_fwd(Solve &v, int k) {
     // beta_{k+1} u_{k+1} = q - alpha_k u_k ; plane rotation
     pat::launch_lincomb(c->rd, c->qd, nullptr, 1.0, c->rd, z.L.alpha, -1.0, M, RB, v.s);
     pat::launch_lincomb(c->rp, c->qp, nullptr, 1.0, c->rp, z.L.alpha, -1.0, N, RB, v.s);
-    pat::launch_dot_partial(c->rd, c->rd, M, RB, pA, v.s);
-    pat::launch_dot_partial(c->rp, c->rp, N, RB, pB, v.s);
-    pat::launch_dot_final(pA, nullptr, RB, z.n1, v.s);
-    pat::launch_dot_final(pB, nullptr, RB, z.n2, v.s);
-    pat::launch_lsqr_scalar(pat::LsqrStage::Beta, z.L, z.n1, z.n2, RB, v.s);
+    pat::launch_lsqr_scalar(pat::LsqrStage::Beta, z.L, pat::launch_norms(c->rd, M, c->rp, N, RB, c->part, v.s), RB,
+                            v.s);
     pat::launch_lincomb(c->rd, c->rd, z.L.inv, 1.0, nullptr, nullptr, 0.0, M, RB, v.s);
     pat::launch_lincomb(c->rp, c->rp, z.L.inv, 1.0, nullptr, nullptr, 0.0, N, RB, v.s);
     // x += (phi/rho) w ; r -= (phi/rho) z
@@ -954,13 +930,11 @@ pat_status final_check(Solve &v, const double *y_obs, const pat_rto_params *prm,
     pat_problem *p = v.p;
     CglsWS *c = v.c;
     const int RB = v.RB;
-    double *pA = c->part, *pB = c->part + pat::kDotBlocks * RB;
     double *t1 = c->scal + 14 * RB, *t2 = c->scal + 15 * RB;
     build_b(v, y_obs, prm);
     prior_part(v, c->x);  // qp = L x (latent prior: x)
     pat::launch_lincomb(c->rp, c->rp, nullptr, 1.0, c->qp, nullptr, -1.0, v.NX, RB, v.s);
-    pat::launch_dot_partial(c->rp, c->rp, v.NX, RB, pB, v.s);
-    pat::launch_dot_final(pB, nullptr, RB, t2, v.s);
+    pat::launch_norm_store(pat::launch_norms(c->rp, v.NX, nullptr, 0, RB, c->part, v.s), RB, t2, v.s);
     const int RBf = fit_rb(v.N, pat::Prec::F64, std::min(RB, pat::max_rhs_block(pat::Prec::F64)));
     SweepWS *w64;
     PAT_TRY(get_sweep(p, pat::Prec::F64, RBf, false, &w64));
@@ -977,8 +951,7 @@ pat_status final_check(Solve &v, const double *y_obs, const pat_rto_params *prm,
     for (int h = 0; h < RB; h += RBf) {
         pat::launch_cols(src, RB, h, static_cast<double *>(w64->S[0]), v.N, RBf, v.s);
         PAT_HIP(hipGraphLaunch(w64->g_fwd_chk, v.s));  // qd [M][RBf] = G p / sigma
-        pat::launch_diff_sq_partial(c->rd, RB, h, c->qd, v.M, RBf, pA, v.s);
-        pat::launch_dot_final(pA, nullptr, RBf, t1 + h, v.s);
+        pat::launch_norm_store(pat::launch_diff_sq(c->rd, RB, h, c->qd, v.M, RBf, c->part, v.s), RBf, t1 + h, v.s);
     }
     pat::launch_resid(t1, t2, out, nullptr, 1, 0, v.rb0, v.S, RB, v.s);
     return PAT_OK;

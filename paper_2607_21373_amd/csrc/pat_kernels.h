@@ -160,21 +160,30 @@ void launch_prior(const DevOps &op, int RB, double a, const double *x, double *y
 void launch_prior_t(const DevOps &op, int RB, double a, const double *x, double *y, hipStream_t s);
 void launch_gext_t_combine(Prec prec, const DevOps &op, int RB, double a, double isig, const void *PH,
                            const double *rp, double *out, hipStream_t s);
-// partial sums: part[b][r] = sum over rows of block b of x*y (y == x gives squares)
+// Squared norms per right-hand side, as partial sums over row blocks (at most kDotBlocks
+// per array, in a buffer of 2 kDotBlocks x RB) that the launch_norm_* calls finish.
 constexpr int kDotBlocks = 512;
-void launch_dot_partial(const double *x, const double *y, int64_t rows, int RB, double *part, hipStream_t s);
-// finalize: mode 0: out[r] = sum partA (+ sum partB if non-null)
-void launch_dot_final(const double *partA, const double *partB, int RB, double *out, hipStream_t s);
-// part[b][r] = sum over rows of block b of (a[row*lda + aoff + r] - y[row*RB + r])^2, r < RB
-// (kDotBlocks partial blocks; finish with launch_dot_final)
-void launch_diff_sq_partial(const double *a, int lda, int aoff, const double *y, int64_t rows, int RB, double *part,
-                            hipStream_t s);
+struct NormParts {
+    double *a = nullptr, *b = nullptr;
+    int na = 0, nb = 0;
+};
+// of x [xrows][RB] and, unless null, y [yrows][RB]
+NormParts launch_norms(const double *x, int64_t xrows, const double *y, int64_t yrows, int RB, double *part,
+                       hipStream_t s);
+// of a[row*lda + aoff + r] - y[row*RB + r], r < RB
+NormParts launch_diff_sq(const double *a, int lda, int aoff, const double *y, int64_t rows, int RB, double *part,
+                         hipStream_t s);
+// out = |x|^2 + |y|^2
+void launch_norm_store(const NormParts &n, int RB, double *out, hipStream_t s);
+// scalar stages of CGLS: alpha = gamma / (|x|^2 + |y|^2); beta = |x|^2 / gamma, invn = 1 / |x|, gamma = |x|^2
+void launch_norm_alpha(const NormParts &n, int RB, const double *gamma, double *alpha, hipStream_t s);
+void launch_norm_gamma(const NormParts &n, int RB, double *gamma, double *beta, double *invn, int first,
+                       hipStream_t s);
+// as launch_resid from the two norms
+void launch_norm_resid(const NormParts &n, double *hist, double *diag, int64_t ld, int64_t col, int64_t rb0, int64_t R,
+                       int RB, hipStream_t s);
 // out[row*RB + r] = in[row*ldin + c0 + r]: columns [c0, c0 + RB) of a wider block
 void launch_cols(const double *in, int ldin, int c0, double *out, int64_t rows, int RB, hipStream_t s);
-// scalar stages of CGLS, on device arrays of length RB
-void launch_scalar_alpha(const double *gamma, const double *delta, double *alpha, int RB, hipStream_t s);
-void launch_scalar_gamma(double *gamma, const double *gnew, double *beta, double *invn, int first, int RB,
-                         hipStream_t s);
 // hist[(rb0+r)*ld + col] = sqrt(a + b) and diag[2*(that)] = (sqrt(a), sqrt(b)); either may be null
 void launch_resid(const double *a, const double *b, double *hist, double *diag, int64_t ld, int64_t col, int64_t rb0,
                   int64_t R, int RB, hipStream_t s);
@@ -186,7 +195,7 @@ void launch_axpy_neg(double *y, const double *x, const double *alpha, int64_t ro
 void launch_append_dir(const double *sv, double *Qk, double *d, const double *invn, const double *beta, int first,
                        int64_t rows, int RB, hipStream_t s);
 // reorthogonalisation: s -= sum_j coef[j] Q[j] (j < k), coef from launch_reorth_coef.  The
-// multi-dot streams k basis vectors per call and needs more workgroups than the plain dots
+// multi-dot streams k basis vectors per call and needs more workgroups than the norms
 // (4 per CU); its partial sums take kMultiBlocks x 2k x RB doubles.
 constexpr int kMultiBlocks = 1024;
 void launch_project(const double *Q, double *sv, const double *coef, int k, int64_t rows, int RB, hipStream_t s);
@@ -199,13 +208,13 @@ void launch_reorth_coef(const double *Q, const double *sv, int k, int64_t rows, 
 struct LsqrScalars {
     double *alpha, *beta, *alpha1, *beta1, *rhob, *phib, *cs, *sn, *rho, *zfac, *step, *inv;
 };
+// (n1, n2: the squared norms of the two arrays)
 // InitBeta:  beta_1 = sqrt(n1 + n2), inv = 1/beta_1
 // InitAlpha: alpha_1 = sqrt(n1), inv = 1/alpha_1, phi_bar = beta_1, rho_bar = alpha_1
 // Beta:      beta_{k+1} = sqrt(n1 + n2), inv = 1/beta, rotation (rho, c, s), phi_bar, step = phi/rho
 // Alpha:     alpha_{k+1} = sqrt(n1), inv = 1/alpha, rho_bar = -c alpha, zfac = s alpha / rho
 enum class LsqrStage : int { InitBeta, InitAlpha, Beta, Alpha };
-void launch_lsqr_scalar(LsqrStage st, const LsqrScalars &c, const double *n1, const double *n2, int RB,
-                        hipStream_t s);
+void launch_lsqr_scalar(LsqrStage st, const LsqrScalars &c, const NormParts &n, int RB, hipStream_t s);
 // out = sa*ca[r]*a + sb*cb[r]*b (null ca/cb: 1; null b: no second term); out may alias a or b
 void launch_lincomb(double *out, const double *a, const double *ca, double sa, const double *b, const double *cb,
                     double sb, int64_t rows, int RB, hipStream_t s);

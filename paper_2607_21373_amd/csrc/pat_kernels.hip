@@ -979,40 +979,27 @@ __global__ void __launch_bounds__(256) k_prior_t(const int32_t *rowptr, const in
     }
 }
 
-// part[b][r] = sum over rows of block b of x[row][r] * y[row][r]
-__global__ void __launch_bounds__(256) k_dot_partial(const double *x, const double *y, int64_t rows, int RB,
-                                                     double *part) {
-    __shared__ double red[256];
+// Squares of x [rows][RB] summed over the rows of block b of nb into part[b][r].  Four rows
+// per pass into four partial sums, so that each lane keeps four loads in flight.
+__device__ __forceinline__ void norm_partial(const double *x, int64_t rows, int RB, int b, int nb, double *part,
+                                             double *red) {
     const int G = 256 / RB;
     const int r = threadIdx.x % RB, g = threadIdx.x / RB;
-    const int64_t chunk = (rows + gridDim.x - 1) / gridDim.x;
-    const int64_t a0 = int64_t(blockIdx.x) * chunk, a1 = a0 + chunk < rows ? a0 + chunk : rows;
-    // four rows per pass into four partial sums, so that each lane keeps four loads
-    // in flight; a norm (x == y) loads each element once
+    const int64_t chunk = (rows + nb - 1) / nb;
+    const int64_t a0 = int64_t(b) * chunk, a1 = a0 + chunk < rows ? a0 + chunk : rows;
     double acc0 = 0.0, acc1 = 0.0, acc2 = 0.0, acc3 = 0.0;
     int64_t row = a0 + g;
-    if (x == y) {
-        for (; row + 3 * G < a1; row += 4 * G) {
-            const double v0 = x[row * RB + r], v1 = x[(row + G) * RB + r], v2 = x[(row + 2 * G) * RB + r],
-                         v3 = x[(row + 3 * G) * RB + r];
-            acc0 = __builtin_fma(v0, v0, acc0);
-            acc1 = __builtin_fma(v1, v1, acc1);
-            acc2 = __builtin_fma(v2, v2, acc2);
-            acc3 = __builtin_fma(v3, v3, acc3);
-        }
-    } else {
-        for (; row + 3 * G < a1; row += 4 * G) {
-            const int64_t e0 = row * RB + r, e1 = e0 + int64_t(G) * RB, e2 = e1 + int64_t(G) * RB,
-                          e3 = e2 + int64_t(G) * RB;
-            acc0 = __builtin_fma(x[e0], y[e0], acc0);
-            acc1 = __builtin_fma(x[e1], y[e1], acc1);
-            acc2 = __builtin_fma(x[e2], y[e2], acc2);
-            acc3 = __builtin_fma(x[e3], y[e3], acc3);
-        }
+    for (; row + 3 * G < a1; row += 4 * G) {
+        const double v0 = x[row * RB + r], v1 = x[(row + G) * RB + r], v2 = x[(row + 2 * G) * RB + r],
+                     v3 = x[(row + 3 * G) * RB + r];
+        acc0 = __builtin_fma(v0, v0, acc0);
+        acc1 = __builtin_fma(v1, v1, acc1);
+        acc2 = __builtin_fma(v2, v2, acc2);
+        acc3 = __builtin_fma(v3, v3, acc3);
     }
     for (; row < a1; row += G) {
-        const int64_t e = row * RB + r;
-        acc0 = __builtin_fma(x[e], y[e], acc0);
+        const double v = x[row * RB + r];
+        acc0 = __builtin_fma(v, v, acc0);
     }
     red[threadIdx.x] = (acc0 + acc1) + (acc2 + acc3);
     __syncthreads();
@@ -1020,7 +1007,20 @@ __global__ void __launch_bounds__(256) k_dot_partial(const double *x, const doub
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x < RB) part[int64_t(blockIdx.x) * RB + threadIdx.x] = red[threadIdx.x];
+    if (threadIdx.x < RB) part[int64_t(b) * RB + threadIdx.x] = red[threadIdx.x];
+}
+
+// The partial norms of one or two arrays in one launch: na blocks on x, nb on y.  Each
+// scalar stage below finishes the norms it needs in its own launch: on small meshes a solver
+// iteration is a chain of 5 us launches (4913 nodes, 200 steps, 16 float32 samples,
+// 50 LSQR iterations: 115 -> 101 ms with the reductions of this file; 864 nodes, 10 float64
+// samples, 30 CGLS iterations: 28.0 -> 23.9 ms).
+__global__ void __launch_bounds__(256) k_norms(const double *x, int64_t xrows, int na, double *pa, const double *y,
+                                               int64_t yrows, int nb, double *pb, int RB) {
+    __shared__ double red[256];
+    const int b = int(blockIdx.x);
+    if (b < na) norm_partial(x, xrows, RB, b, na, pa, red);
+    else norm_partial(y, yrows, RB, b - na, nb, pb, red);
 }
 
 // part[b][r] = sum over rows of block b of (a[row][aoff + r] - y[row][r])^2, a with row
@@ -1052,49 +1052,83 @@ __global__ void k_cols(const double *in, int ldin, int c0, double *out, int64_t 
         out[e] = in[(e / RB) * ldin + c0 + e % RB];
 }
 
-// out[r] = sum_b partA[b][r] (+ sum_b partB[b][r]), nb partial blocks each
-__global__ void __launch_bounds__(256) k_dot_final(const double *partA, const double *partB, int nb, int RB,
-                                                   double *out) {
-    __shared__ double red[256];
+// acc + p[b0 stride] + p[(b0 + G) stride] + ... in that order, 16 loads at a time: one
+// workgroup sums all partial blocks, and its loads' latency is what it costs.
+__device__ __forceinline__ double strided_sum(const double *p, int b, int G, int nb, int64_t stride, double acc) {
+    for (; b + 15 * G < nb; b += 16 * G) {
+        double v[16];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) v[q] = p[int64_t(b + q * G) * stride];
+#pragma unroll
+        for (int q = 0; q < 16; ++q) acc += v[q];
+    }
+    for (; b < nb; b += G) acc += p[int64_t(b) * stride];
+    return acc;
+}
+
+// sum over the na blocks of pa (and then the nb of pb), for thread r < RB of the workgroup
+__device__ __forceinline__ double sum_parts(const double *pa, int na, const double *pb, int nb, int RB, double *red) {
     const int G = 256 / RB;
     const int r = threadIdx.x % RB, g = threadIdx.x / RB;
-    double acc = 0.0;
-    for (int b = g; b < nb; b += G) acc += partA[int64_t(b) * RB + r];
-    if (partB)
-        for (int b = g; b < nb; b += G) acc += partB[int64_t(b) * RB + r];
+    double acc = strided_sum(pa + r, g, G, na, RB, 0.0);
+    if (pb) acc = strided_sum(pb + r, g, G, nb, RB, acc);
+    __syncthreads();
     red[threadIdx.x] = acc;
     __syncthreads();
     for (int s = 128; s >= RB; s >>= 1) {
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
         __syncthreads();
     }
-    if (threadIdx.x < RB) out[threadIdx.x] = red[threadIdx.x];
+    return red[r];
 }
 
-__global__ void k_alpha(const double *gamma, const double *delta, double *alpha, int RB) {
+__global__ void __launch_bounds__(256) k_norm_store(const NormParts n, int RB, double *out) {
+    __shared__ double red[256];
+    const double v = sum_parts(n.a, n.na, n.b, n.nb, RB, red);
+    if (threadIdx.x < RB) out[threadIdx.x] = v;
+}
+
+// alpha = gamma / ||(x, y)||^2
+__global__ void __launch_bounds__(256) k_norm_alpha(const NormParts n, int RB, const double *gamma, double *alpha) {
+    __shared__ double red[256];
+    const double delta = sum_parts(n.a, n.na, n.b, n.nb, RB, red);
     const int r = threadIdx.x;
-    if (r < RB) alpha[r] = delta[r] > 0.0 ? gamma[r] / delta[r] : 0.0;
+    if (r < RB) alpha[r] = delta > 0.0 ? gamma[r] / delta : 0.0;
 }
 
-__global__ void k_gamma(double *gamma, const double *gnew, double *beta, double *invn, int first, int RB) {
+// g = ||x||^2: beta = g / gamma, invn = 1 / ||x||, gamma = g
+__global__ void __launch_bounds__(256) k_norm_gamma(const NormParts n, int RB, double *gamma, double *beta,
+                                                    double *invn, int first) {
+    __shared__ double red[256];
+    const double g = sum_parts(n.a, n.na, n.b, n.nb, RB, red);
     const int r = threadIdx.x;
     if (r >= RB) return;
-    const double g = gnew[r];
     beta[r] = (first || !(gamma[r] > 0.0)) ? 0.0 : g / gamma[r];
     invn[r] = g > 0.0 ? 1.0 / sqrt(g) : 0.0;
     gamma[r] = g;
 }
 
+// hist and diag of one right-hand side from its squared data and prior residuals
+__device__ __forceinline__ void store_resid(double a, double b, double *hist, double *diag, int64_t at) {
+    if (hist) hist[at] = sqrt(a + b);
+    if (diag) {
+        diag[2 * at] = sqrt(a);
+        diag[2 * at + 1] = sqrt(b);
+    }
+}
+
+__global__ void __launch_bounds__(256) k_norm_resid(const NormParts n, int RB, double *hist, double *diag, int64_t ld,
+                                                    int64_t col, int64_t rb0, int64_t R) {
+    __shared__ double red[256];
+    const double a = sum_parts(n.a, n.na, nullptr, 0, RB, red), b = sum_parts(n.b, n.nb, nullptr, 0, RB, red);
+    const int r = threadIdx.x;
+    if (r < RB && rb0 + r < R) store_resid(a, b, hist, diag, (rb0 + r) * ld + col);
+}
+
 __global__ void k_resid(const double *a, const double *b, double *hist, double *diag, int64_t ld, int64_t col,
                         int64_t rb0, int64_t R, int RB) {
     const int r = threadIdx.x;
-    if (r >= RB || rb0 + r >= R) return;
-    const int64_t at = (rb0 + r) * ld + col;
-    if (hist) hist[at] = sqrt(a[r] + b[r]);
-    if (diag) {
-        diag[2 * at] = sqrt(a[r]);
-        diag[2 * at + 1] = sqrt(b[r]);
-    }
+    if (r < RB && rb0 + r < R) store_resid(a[r], b[r], hist, diag, (rb0 + r) * ld + col);
 }
 
 // Grid-stride loops over [rows][RB] arrays: the RHS index of a thread's elements,
@@ -1142,10 +1176,13 @@ __global__ void k_append(const double *sv, double *Qk, double *d, const double *
 // ---- LSQR (Golub-Kahan bidiagonalisation) ---------------------------------
 // Per-RHS scalar stages; one thread per right-hand side.  A new alpha or beta
 // below 1e-15 of its first value is exact breakdown and is set to zero.
-__global__ void k_lsqr_scalar(LsqrStage st, LsqrScalars c, const double *n1, const double *n2, int RB) {
+__global__ void __launch_bounds__(256) k_lsqr_scalar(LsqrStage st, LsqrScalars c, const NormParts n, int RB) {
+    __shared__ double red[256];
+    const double n1 = sum_parts(n.a, n.na, nullptr, 0, RB, red);
+    const double n2 = n.b ? sum_parts(n.b, n.nb, nullptr, 0, RB, red) : 0.0;
     const int r = threadIdx.x;
     if (r >= RB) return;
-    const double nrm = sqrt(n1[r] + (n2 ? n2[r] : 0.0));
+    const double nrm = sqrt(n1 + n2);
     switch (st) {
     case LsqrStage::InitBeta:
         c.beta[r] = c.beta1[r] = nrm;
@@ -1214,11 +1251,15 @@ __global__ void k_lsqr_vw(const double *sv, const double *inv, const double *zfa
 // first Gram-Schmidt coefficients and the new row of the Gram matrix in one read of Q.
 __global__ void __launch_bounds__(256) k_multidot2_partial(const double *Q, const double *sv, int k, int64_t rows,
                                                            int RB, double *part) {
-    __shared__ double red[256];
+    __shared__ double red[16 * 256];
     const int G = 256 / RB;
     const int r = threadIdx.x % RB, g = threadIdx.x / RB;
     const int64_t chunk = (rows + gridDim.x - 1) / gridDim.x;
     const int64_t a0 = int64_t(blockIdx.x) * chunk, a1 = a0 + chunk < rows ? a0 + chunk : rows;
+    if (a0 >= rows) {  // a block without rows (small meshes)
+        for (int e = threadIdx.x; e < 2 * k * RB; e += 256) part[int64_t(blockIdx.x) * 2 * k * RB + e] = 0.0;
+        return;
+    }
     const int64_t stride = rows * RB;
     const double *w = Q + int64_t(k - 1) * stride;
     for (int j0 = 0; j0 < k; j0 += 8) {
@@ -1234,40 +1275,58 @@ __global__ void __launch_bounds__(256) k_multidot2_partial(const double *Q, cons
                     gac[jj] = __builtin_fma(qj, q, gac[jj]);
                 }
         }
-        for (int h = 0; h < 2; ++h)
-            for (int jj = 0; jj < 8 && j0 + jj < k; ++jj) {
-                red[threadIdx.x] = h ? gac[jj] : acc[jj];
-                __syncthreads();
-                for (int s = 128; s >= RB; s >>= 1) {
-                    if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
-                    __syncthreads();
-                }
-                if (threadIdx.x < RB)
-                    part[(int64_t(blockIdx.x) * 2 * k + h * k + j0 + jj) * RB + threadIdx.x] = red[threadIdx.x];
-                __syncthreads();
+        // all 16 sums go down the tree together: two barriers per level instead of per sum
+#pragma unroll
+        for (int jj = 0; jj < 8; ++jj) {
+            red[jj * 256 + threadIdx.x] = acc[jj];
+            red[(8 + jj) * 256 + threadIdx.x] = gac[jj];
+        }
+        __syncthreads();
+        for (int s = 128; s >= RB; s >>= 1) {
+            for (int e = threadIdx.x; e < 16 * s; e += 256) {
+                const int v = e / s, t = e & (s - 1);
+                red[v * 256 + t] += red[v * 256 + t + s];
             }
+            __syncthreads();
+        }
+        for (int e = threadIdx.x; e < 16 * RB; e += 256) {
+            const int v = e / RB, t = e % RB, h = v >> 3, jj = v & 7;
+            if (j0 + jj < k) part[(int64_t(blockIdx.x) * 2 * k + h * k + j0 + jj) * RB + t] = red[v * 256 + t];
+        }
+        __syncthreads();
     }
 }
 
-// Second Gram-Schmidt pass from the Gram matrix, one thread per right-hand side.
+// Second Gram-Schmidt pass from the Gram matrix, one thread per (j, right-hand side).
 // cg[j] (j < k) are the first-pass coefficients c1 = Q^T s, cg[k + j] = Q_j . Q_{k-1}.
 // Stores that row into gram ([kcap][kcap][RB], symmetric) and writes
 //   coef = c1 + c2,  c2 = Q^T (s - Q c1) = c1 - (Q^T Q) c1,
-// so that s - Q coef equals two classical Gram-Schmidt passes in exact arithmetic.
-__global__ void k_gram_coef(double *gram, int kcap, const double *cg, int k, int RB, double *coef) {
-    const int r = threadIdx.x;
-    if (r >= RB) return;
-    for (int j = 0; j < k; ++j) {
-        const double v = cg[int64_t(k + j) * RB + r];
-        gram[(int64_t(k - 1) * kcap + j) * RB + r] = v;
-        gram[(int64_t(j) * kcap + (k - 1)) * RB + r] = v;
+// so that s - Q coef equals two classical Gram-Schmidt passes in exact arithmetic.  The
+// new row and column are taken from cg, so no thread waits for another's store (with one
+// thread per right-hand side walking k x k entries this took 67 us at k = 15).
+__global__ void __launch_bounds__(256) k_gram_coef(double *gram, int kcap, const double *cg, int k, int RB,
+                                                   double *coef) {
+    const int e = int(blockIdx.x) * 256 + int(threadIdx.x), j = e / RB, r = e % RB;
+    if (j >= k) return;
+    const double vn = cg[int64_t(k + j) * RB + r];
+    gram[(int64_t(k - 1) * kcap + j) * RB + r] = vn;
+    gram[(int64_t(j) * kcap + (k - 1)) * RB + r] = vn;
+    double gc = 0.0;
+    const double *row = gram + int64_t(j) * kcap * RB + r;
+    for (int i0 = 0; i0 < k; i0 += 8) {
+        double g[8], c[8];
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+            const int i = i0 + q < k ? i0 + q : k - 1;
+            c[q] = cg[int64_t(i) * RB + r];
+            g[q] = j == k - 1 ? cg[int64_t(k + i) * RB + r] : i == k - 1 ? vn : row[int64_t(i) * RB];
+        }
+#pragma unroll
+        for (int q = 0; q < 8; ++q)
+            if (i0 + q < k) gc = __builtin_fma(g[q], c[q], gc);
     }
-    for (int j = 0; j < k; ++j) {
-        double gc = 0.0;
-        for (int i = 0; i < k; ++i) gc = __builtin_fma(gram[(int64_t(j) * kcap + i) * RB + r], cg[int64_t(i) * RB + r], gc);
-        const double c1 = cg[int64_t(j) * RB + r];
-        coef[int64_t(j) * RB + r] = c1 + (c1 - gc);
-    }
+    const double c1 = cg[int64_t(j) * RB + r];
+    coef[int64_t(j) * RB + r] = c1 + (c1 - gc);
 }
 
 // coef[j][r] = sum_b part[b][j][r]; one workgroup per j
@@ -1276,9 +1335,7 @@ __global__ void __launch_bounds__(256) k_multidot_final(const double *part, int 
     const int j = blockIdx.x;
     const int G = 256 / RB;
     const int r = threadIdx.x % RB, g = threadIdx.x / RB;
-    double acc = 0.0;
-    for (int b = g; b < nb; b += G) acc += part[(int64_t(b) * k + j) * RB + r];
-    red[threadIdx.x] = acc;
+    red[threadIdx.x] = strided_sum(part + int64_t(j) * RB + r, g, G, nb, int64_t(k) * RB, 0.0);
     __syncthreads();
     for (int s = 128; s >= RB; s >>= 1) {
         if (threadIdx.x < s) red[threadIdx.x] += red[threadIdx.x + s];
@@ -1693,30 +1750,48 @@ void launch_gext_t_combine(Prec prec, const DevOps &op, int RB, double a, double
                            a, isig, (const float *)PH, rp, out);
 }
 
-void launch_dot_partial(const double *x, const double *y, int64_t rows, int RB, double *part, hipStream_t s) {
-    hipLaunchKernelGGL(k_dot_partial, dim3(kDotBlocks), dim3(256), 0, s, x, y, rows, RB, part);
+NormParts launch_norms(const double *x, int64_t xrows, const double *y, int64_t yrows, int RB, double *part,
+                       hipStream_t s) {
+    NormParts n;
+    n.na = kDotBlocks;
+    n.a = part;
+    if (y) {
+        n.nb = kDotBlocks;
+        n.b = part + int64_t(kDotBlocks) * RB;
+    }
+    hipLaunchKernelGGL(k_norms, dim3(n.na + n.nb), dim3(256), 0, s, x, xrows, n.na, n.a, y, yrows, n.nb, n.b, RB);
+    return n;
 }
 
-void launch_diff_sq_partial(const double *a, int lda, int aoff, const double *y, int64_t rows, int RB, double *part,
-                            hipStream_t s) {
-    hipLaunchKernelGGL(k_diff_sq_partial, dim3(kDotBlocks), dim3(256), 0, s, a, lda, aoff, y, rows, RB, part);
+NormParts launch_diff_sq(const double *a, int lda, int aoff, const double *y, int64_t rows, int RB, double *part,
+                         hipStream_t s) {
+    NormParts n;
+    n.na = kDotBlocks;
+    n.a = part;
+    hipLaunchKernelGGL(k_diff_sq_partial, dim3(n.na), dim3(256), 0, s, a, lda, aoff, y, rows, RB, part);
+    return n;
 }
 
 void launch_cols(const double *in, int ldin, int c0, double *out, int64_t rows, int RB, hipStream_t s) {
     hipLaunchKernelGGL(k_cols, dim3(grid_for(rows * RB)), dim3(256), 0, s, in, ldin, c0, out, rows * RB, RB);
 }
 
-void launch_dot_final(const double *partA, const double *partB, int RB, double *out, hipStream_t s) {
-    hipLaunchKernelGGL(k_dot_final, dim3(1), dim3(256), 0, s, partA, partB, kDotBlocks, RB, out);
+void launch_norm_store(const NormParts &n, int RB, double *out, hipStream_t s) {
+    hipLaunchKernelGGL(k_norm_store, dim3(1), dim3(256), 0, s, n, RB, out);
 }
 
-void launch_scalar_alpha(const double *gamma, const double *delta, double *alpha, int RB, hipStream_t s) {
-    hipLaunchKernelGGL(k_alpha, dim3(1), dim3(256), 0, s, gamma, delta, alpha, RB);
+void launch_norm_alpha(const NormParts &n, int RB, const double *gamma, double *alpha, hipStream_t s) {
+    hipLaunchKernelGGL(k_norm_alpha, dim3(1), dim3(256), 0, s, n, RB, gamma, alpha);
 }
 
-void launch_scalar_gamma(double *gamma, const double *gnew, double *beta, double *invn, int first, int RB,
-                         hipStream_t s) {
-    hipLaunchKernelGGL(k_gamma, dim3(1), dim3(256), 0, s, gamma, gnew, beta, invn, first, RB);
+void launch_norm_gamma(const NormParts &n, int RB, double *gamma, double *beta, double *invn, int first,
+                       hipStream_t s) {
+    hipLaunchKernelGGL(k_norm_gamma, dim3(1), dim3(256), 0, s, n, RB, gamma, beta, invn, first);
+}
+
+void launch_norm_resid(const NormParts &n, double *hist, double *diag, int64_t ld, int64_t col, int64_t rb0, int64_t R,
+                       int RB, hipStream_t s) {
+    hipLaunchKernelGGL(k_norm_resid, dim3(1), dim3(256), 0, s, n, RB, hist, diag, ld, col, rb0, R);
 }
 
 void launch_resid(const double *a, const double *b, double *hist, double *diag, int64_t ld, int64_t col, int64_t rb0,
@@ -1724,9 +1799,8 @@ void launch_resid(const double *a, const double *b, double *hist, double *diag, 
     hipLaunchKernelGGL(k_resid, dim3(1), dim3(256), 0, s, a, b, hist, diag, ld, col, rb0, R, RB);
 }
 
-void launch_lsqr_scalar(LsqrStage st, const LsqrScalars &c, const double *n1, const double *n2, int RB,
-                        hipStream_t s) {
-    hipLaunchKernelGGL(k_lsqr_scalar, dim3(1), dim3(256), 0, s, st, c, n1, n2, RB);
+void launch_lsqr_scalar(LsqrStage st, const LsqrScalars &c, const NormParts &n, int RB, hipStream_t s) {
+    hipLaunchKernelGGL(k_lsqr_scalar, dim3(1), dim3(256), 0, s, st, c, n, RB);
 }
 
 void launch_lincomb(double *out, const double *a, const double *ca, double sa, const double *b, const double *cb,
@@ -1763,7 +1837,7 @@ void launch_reorth_coef(const double *Q, const double *sv, int k, int64_t rows, 
     if (k <= 0) return;
     hipLaunchKernelGGL(k_multidot2_partial, dim3(kMultiBlocks), dim3(256), 0, s, Q, sv, k, rows, RB, part);
     hipLaunchKernelGGL(k_multidot_final, dim3(2 * k), dim3(256), 0, s, part, kMultiBlocks, 2 * k, RB, cg);
-    hipLaunchKernelGGL(k_gram_coef, dim3(1), dim3(256), 0, s, gram, kcap, cg, k, RB, coef);
+    hipLaunchKernelGGL(k_gram_coef, dim3((k * RB + 255) / 256), dim3(256), 0, s, gram, kcap, cg, k, RB, coef);
 }
 
 void launch_project(const double *Q, double *sv, const double *coef, int k, int64_t rows, int RB, hipStream_t s) {
