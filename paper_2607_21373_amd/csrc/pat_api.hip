@@ -1749,14 +1749,15 @@ pat_status pat_spectral_apply(pat_problem *p, int64_t R, int transpose, const do
     const int64_t N = p->ops.n, G = p->sops.G;
     const int32_t *perm = p->perm_identity ? nullptr : p->ops.perm;
     for (int64_t rb0 = 0; rb0 < R; rb0 += RB) {
-        if (!transpose) {
-            pat::launch_pack(true, true, x, R, rb0, RB, G, nullptr, sw->lx, s);
-            pat::launch_spectral(p->sops, RB, sw->lx, sw->gr, sw->gc, pat::Prec::F64, sw->ym, N, s);
+        if (!transpose) {  // a grid vector of one right-hand side is in the work layout already
+            if (RB > 1) pat::launch_pack(true, true, x, R, rb0, RB, G, nullptr, sw->lx, s);
+            pat::launch_spectral(p->sops, RB, RB > 1 ? sw->lx : x, sw->gr, sw->gc, pat::Prec::F64, sw->ym, N, s);
             pat::launch_unpack(true, true, sw->ym, R, rb0, RB, N, perm, y, s);
         } else {
             pat::launch_pack(true, true, x, R, rb0, RB, N, perm, sw->ym, s);
-            pat::launch_spectral_t(p->sops, RB, sw->ym, pat::Prec::F64, 1.0, nullptr, sw->gr, sw->gc, sw->lx, s);
-            pat::launch_unpack(true, true, sw->lx, R, rb0, RB, G, nullptr, y, s);
+            pat::launch_spectral_t(p->sops, RB, sw->ym, pat::Prec::F64, 1.0, nullptr, sw->gr, sw->gc,
+                                   RB > 1 ? sw->lx : y, s);
+            if (RB > 1) pat::launch_unpack(true, true, sw->lx, R, rb0, RB, G, nullptr, y, s);
         }
     }
     PAT_HIP(hipGetLastError());

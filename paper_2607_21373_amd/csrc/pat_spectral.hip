@@ -9,10 +9,10 @@
 // conjugates): complex half-spectrum vectors [n][n][nh][RB], (re, im) per element.
 //
 // The 3D transform is five launches, each a batch of one-dimensional transforms
-// along one axis (one line and a chunk of up to 16 right-hand sides per
-// workgroup, staged in LDS): the real-to-complex x pass, forward y, then forward
-// z, the multiplication by a(k) and the inverse z in the same pass, inverse y, and
-// the complex-to-real x pass.  The x passes pack the n real points of a line as
+// along one axis (one line and a chunk of up to 16 right-hand sides per workgroup, or
+// several lines of a narrower block, staged in LDS): the real-to-complex x pass,
+// forward y, then forward z, the multiplication by a(k) and the inverse z in the same
+// pass, inverse y, and the complex-to-real x pass.  The x passes pack the n real points of a line as
 // n/2 complex points (even samples real, odd samples imaginary), transform those
 // with one length-n/2 FFT and split the result into the n/2 + 1 spectrum values
 // (and back), which halves the bytes of every pass after the first.  Each complex
@@ -37,9 +37,18 @@ __device__ __forceinline__ double2 csub(double2 a, double2 b) { return make_doub
 __device__ __forceinline__ double2 conjg(double2 a) { return make_double2(a.x, -a.y); }
 
 constexpr int kRC = 16;  // right-hand sides per workgroup
-// elements a thread stages between global memory and LDS at most: n * RC / 256
-// (n <= 128 points per line, RC <= 16), all loads issued before any is consumed
-constexpr int kPer = 128 * kRC / 256;
+// elements a thread of the x passes stages between global memory and LDS at most, all
+// loads issued before any is consumed
+constexpr int kPerX = 4;
+
+// log2 of the (line, RHS) pairs of a workgroup: one line (2^lrc right-hand sides), or for
+// narrow blocks on grids of 64^3 and more, 16 pairs.  With one line each, the passes of a
+// single RHS read one 16-byte element per 1 KiB, and most of a workgroup's threads have no
+// points (128^3, one RHS: 302 -> 81 us per application, 8 RHS 431 -> 383; 64^3, one RHS
+// 85 -> 41, 8 RHS 104 -> 84); on smaller grids several lines per workgroup leave too few
+// workgroups (16^3, 8 RHS: 36 against 40 us).  n >= 64 lines per plane: the line count
+// divides by the lines of a workgroup.
+__host__ __device__ inline bool fft_packed(int logn, int lrc) { return logn >= 6 && lrc < 4; }
 
 enum : int { kForward = 0, kInverse = 1, kCentre = 2 };
 
@@ -51,7 +60,7 @@ struct FftPass {
     const double *add;   // added to the real output, or null
     const double *amp;   // a(k) for the centre pass, [(ky * nh + kx) * n + kz]: z lines contiguous
     const double2 *tw;   // tw[j] = exp(-2 pi i j / n), j < n/2
-    int n, RB, axis, mode;
+    int n, logn, RB, lrc, axis, mode;  // lrc: log2 of the right-hand sides per workgroup
 };
 
 // Radix-2 butterfly (u, t) -> (u + t, u - t).
@@ -102,24 +111,24 @@ __device__ __forceinline__ double2 wpow(const double2 *tws, int e, int n) {
     return INV ? conjg(w) : w;
 }
 
-// One length-n transform (Stockham, natural order in and out) of each of the RC lines
-// of a workgroup, 8 points per thread: radix-8 stages while 8^s divides n, then a
+// One length-n transform (Stockham, natural order in and out) of each of the NL (line, RHS)
+// pairs of a workgroup, 8 points per thread: radix-8 stages while 8^s divides n, then a
 // final radix-2 or radix-4 stage.  The first stage takes its points from
 // load(line, t) and the last hands its results to store(line, t, value); the stages
 // in between exchange through the LDS tile X (line r at X + r * stride, see pidx).
 // So a pass reads its input once and writes its output once, with no staging copy
-// through LDS.  The first and last stages map thread -> (line = thread % RC,
-// j = thread / RC), so that consecutive threads touch consecutive right-hand sides
+// through LDS.  The first and last stages map thread -> (line = thread % NL,
+// j = thread / NL), so that consecutive threads touch consecutive right-hand sides
 // of a point in memory.  load may read X and store may write X: every stage reads
 // all its inputs and waits at a barrier before it writes.  Threads without a line
 // only take part in the barriers.  Ends with a barrier.
 template <bool INV, typename Load, typename Store>
-__device__ __forceinline__ void line_fft_io(double2 *X, int stride, int n, int RC, const double2 *tws, Load load,
+__device__ __forceinline__ void line_fft_io(double2 *X, int stride, int n, int lnl, const double2 *tws, Load load,
                                             Store store) {
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, NL = 1 << lnl;
     if (n < 8) {  // n = 2 or 4 (the x passes of a grid of 4 or 8): one thread per line
         double2 v[4];
-        const bool act = tid < RC;
+        const bool act = tid < NL;
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
             double2 x = make_double2(0.0, 0.0);
@@ -144,8 +153,8 @@ __device__ __forceinline__ void line_fft_io(double2 *X, int stride, int n, int R
     for (int ns = 1; ns < n8; ns *= 8) {
         const bool first = ns == 1, last = ns * 8 == n8 && rf == 1;
         const bool io = first || last;
-        const int line = io ? tid % RC : tid / tpl, j = io ? tid / RC : tid % tpl;
-        const bool act = io ? tid < RC * tpl : line < RC;
+        const int line = io ? tid & (NL - 1) : tid / tpl, j = io ? tid >> lnl : tid % tpl;
+        const bool act = io ? tid < NL * tpl : line < NL;
         double2 v[8];
         if (act) {
             double2 *x = X + line * stride;
@@ -171,8 +180,8 @@ __device__ __forceinline__ void line_fft_io(double2 *X, int stride, int n, int R
         __syncthreads();
     }
     if (rf > 1) {
-        const int ns = n8, line = tid % RC, j = tid / RC;
-        const bool act = tid < RC * tpl;
+        const int ns = n8, line = tid & (NL - 1), j = tid >> lnl;
+        const bool act = tid < NL * tpl;
         double2 v[8];  // rf = 2: four butterflies (u, t); rf = 4: two radix-4 groups
         const double2 *x = X + line * stride;
         if (act) {
@@ -221,36 +230,42 @@ __device__ __forceinline__ void line_fft_io(double2 *X, int stride, int n, int R
 // the z pass of the centre mode multiplies by a(k) between its forward and inverse
 // transforms (the forward transform's last stage writes the products to LDS, where
 // the inverse transform's first stage reads them).
+template <bool PACKED>
 __global__ void __launch_bounds__(256) k_fft_axis(const FftPass a) {
     extern __shared__ double2 X[];  // [RC][n + n/8 + 1], see pidx
     __shared__ double2 tws[64];     // the n/2 twiddles (n <= 128)
     const int n = a.n, nh = n / 2 + 1, half_n = n >> 1, stride = n + (n >> 3) + 1;
-    for (int e = threadIdx.x; e < half_n; e += 256) tws[e] = a.tw[e];
+    for (int e = threadIdx.x; e < half_n; e += blockDim.x) tws[e] = a.tw[e];
     __syncthreads();
-    const int RC = a.RB < kRC ? a.RB : kRC;
-    const int rc0 = blockIdx.y * RC;
-    const int L = blockIdx.x, i = L % nh, q = L / nh;  // line (q, i): q = k (axis 1) or j (axis 2)
-    const int64_t g0 = a.axis == 1 ? int64_t(q) * n * nh + i : int64_t(q) * nh + i;
-    const int64_t ls = a.axis == 1 ? nh : int64_t(n) * nh;
-    auto gload = [&](int r, int t) { return a.cin[(g0 + t * ls) * a.RB + rc0 + r]; };
+    const int lrc = a.lrc, rm = (1 << lrc) - 1, rc0 = int(blockIdx.y) << lrc, lnl = PACKED ? 4 : lrc;
+    const int L0 = int(blockIdx.x) << (lnl - lrc);
+    // line L = (q, i): q = k (axis 1) or j (axis 2); pair v = (line L0 + v / RC, RHS rc0 + v % RC)
+    // (the lines, n * nh of them, divide by 16 where several share a workgroup; element
+    // indices fit 32 bits: 128^3 points, 256 right-hand sides)
+    const int ls = (a.axis == 1 ? nh : n * nh) * a.RB;
+    auto at = [&](int v, int t) {
+        const int L = PACKED ? L0 + (v >> lrc) : L0, i = L % nh, q = L / nh;
+        const int g0 = a.axis == 1 ? q * n * nh + i : q * nh + i;
+        return g0 * a.RB + rc0 + (v & rm) + t * ls;
+    };
+    auto gload = [&](int v, int t) { return a.cin[at(v, t)]; };
     const double sc = a.mode == kForward ? 1.0 : 1.0 / n;
-    auto gstore = [&](int r, int t, double2 v) {
-        a.cout[(g0 + t * ls) * a.RB + rc0 + r] = make_double2(sc * v.x, sc * v.y);
+    auto gstore = [&](int v, int t, double2 z) {
+        a.cout[at(v, t)] = make_double2(sc * z.x, sc * z.y);
     };
     if (a.mode == kForward) {
-        line_fft_io<false>(X, stride, n, RC, tws, gload, gstore);
+        line_fft_io<false>(X, stride, n, lnl, tws, gload, gstore);
     } else if (a.mode == kInverse) {
-        line_fft_io<true>(X, stride, n, RC, tws, gload, gstore);
+        line_fft_io<true>(X, stride, n, lnl, tws, gload, gstore);
     } else {
         // a(k) at (kx, ky, kz) = (i, q, t): line L = q * nh + i of the z-ordered table
-        const double *amp = a.amp + int64_t(L) * n;
         auto lstore = [&](int r, int t, double2 v) {
-            const double w = amp[t];
+            const double w = a.amp[int64_t(PACKED ? L0 + (r >> lrc) : L0) * n + t];
             X[r * stride + pidx(t)] = make_double2(w * v.x, w * v.y);
         };
         auto lload = [&](int r, int t) { return X[r * stride + pidx(t)]; };
-        line_fft_io<false>(X, stride, n, RC, tws, gload, lstore);
-        line_fft_io<true>(X, stride, n, RC, tws, lload, gstore);
+        line_fft_io<false>(X, stride, n, lnl, tws, gload, lstore);
+        line_fft_io<true>(X, stride, n, lnl, tws, lload, gstore);
     }
 }
 
@@ -260,93 +275,103 @@ __global__ void __launch_bounds__(256) k_fft_axis(const FftPass a) {
 //   X[k] = E[k] + w^k O[k],  E[k] = (Z[k] + conj Z[m-k]) / 2,  O[k] = -i (Z[k] - conj Z[m-k]) / 2,
 // and back: Z[k] = E[k] + i O[k] with E[k] = (X[k] + conj X[m-k]) / 2 and
 // O[k] = w^-k (X[k] - conj X[m-k]) / 2, z = IDFT_m(Z) / m (the inverse's 1/n included).
+template <bool PACKED>
 __global__ void __launch_bounds__(256) k_fft_x(const FftPass a) {
     extern __shared__ double2 X[];  // [RC][m + m/8 + 1], see pidx
     __shared__ double2 tws[64], twh[32];  // the n/2 twiddles of length n, the m/2 of length m
-    const int n = a.n, m = n >> 1, nh = m + 1, stride = m + (m >> 3) + 1;
-    for (int e = threadIdx.x; e < m; e += 256) tws[e] = a.tw[e];
-    for (int e = threadIdx.x; e < m / 2; e += 256) twh[e] = a.tw[2 * e];
+    const int n = a.n, m = n >> 1, nh = m + 1, stride = m + (m >> 3) + 1, nthr = int(blockDim.x);
+    for (int e = threadIdx.x; e < m; e += nthr) tws[e] = a.tw[e];
+    for (int e = threadIdx.x; e < m / 2; e += nthr) twh[e] = a.tw[2 * e];
     __syncthreads();
-    const int RC = a.RB < kRC ? a.RB : kRC;
-    const int rc0 = blockIdx.y * RC;
-    const int64_t L = blockIdx.x;  // line (k, j): real points g = L*n + t, spectrum h = L*nh + k
+    const int lrc = a.lrc, rm = (1 << lrc) - 1, rc0 = int(blockIdx.y) << lrc, lnl = PACKED ? 4 : lrc;
+    const int NL = 1 << lnl;
+    // line L = (k, j): real points g = L*n + t, spectrum h = L*nh + k; pair v = (line L0 +
+    // v / RC, RHS rc0 + v % RC)
+    const int L0 = int(blockIdx.x) << (lnl - lrc);
+    auto line_of = [&](int v) { return PACKED ? L0 + (v >> lrc) : L0; };
     auto lload = [&](int r, int t) { return X[r * stride + pidx(t)]; };
     auto lstore = [&](int r, int t, double2 v) { X[r * stride + pidx(t)] = v; };
     if (a.mode == kForward) {
-        auto rload = [&](int r, int p) {
-            const int64_t g = (L * n + 2 * p) * a.RB + rc0 + r;
+        auto rload = [&](int v, int p) {
+            const int g = line_of(v) * (n * a.RB) + rc0 + (v & rm) + p * (2 * a.RB);
             return make_double2(a.rin[g], a.rin[g + a.RB]);
         };
-        line_fft_io<false>(X, stride, m, RC, twh, rload, lstore);
-        for (int e = threadIdx.x; e < nh * RC; e += 256) {
-            const int k = e / RC, r = e % RC;
-            const double2 zk = X[r * stride + pidx(k % m)], zc = conjg(X[r * stride + pidx((m - k) % m)]);
+        line_fft_io<false>(X, stride, m, lnl, twh, rload, lstore);
+        for (int e = threadIdx.x; e < nh * NL; e += nthr) {
+            const int k = e >> lnl, v = e & (NL - 1);
+            const double2 zk = X[v * stride + pidx(k % m)], zc = conjg(X[v * stride + pidx((m - k) % m)]);
             const double2 ev = make_double2(0.5 * (zk.x + zc.x), 0.5 * (zk.y + zc.y));
             const double2 od = make_double2(0.5 * (zk.y - zc.y), -0.5 * (zk.x - zc.x));  // -i (zk - zc) / 2
-            a.cout[(L * nh + k) * a.RB + rc0 + r] = cadd(ev, cmul(wpow<false>(tws, k, n), od));
+            a.cout[line_of(v) * (nh * a.RB) + rc0 + (v & rm) + k * a.RB] = cadd(ev, cmul(wpow<false>(tws, k, n), od));
         }
     } else {
-        constexpr int kPerX = kPer / 2;  // m * RC / 256 elements per thread at most
-        double2 vk[kPerX], vc[kPerX];
+        {
+            double2 vk[kPerX], vc[kPerX];
 #pragma unroll
-        for (int u = 0; u < kPerX; ++u) {
-            const int e = threadIdx.x + u * 256, k = e / RC, r = e % RC;
-            double2 xk = make_double2(0.0, 0.0), xc = xk;
-            if (e < m * RC) {
-                xk = a.cin[(L * nh + k) * a.RB + rc0 + r];
-                xc = a.cin[(L * nh + m - k) * a.RB + rc0 + r];
+            for (int u = 0; u < kPerX; ++u) {
+                const int e = threadIdx.x + u * nthr, k = e >> lnl, v = e & (NL - 1);
+                double2 xk = make_double2(0.0, 0.0), xc = xk;
+                if (e < m * NL) {
+                    const int h = line_of(v) * (nh * a.RB) + rc0 + (v & rm);
+                    xk = a.cin[h + k * a.RB];
+                    xc = a.cin[h + (m - k) * a.RB];
+                }
+                vk[u] = xk;
+                vc[u] = xc;
             }
-            vk[u] = xk;
-            vc[u] = xc;
-        }
 #pragma unroll
-        for (int u = 0; u < kPerX; ++u) {
-            const int e = threadIdx.x + u * 256, k = e / RC, r = e % RC;
-            if (e < m * RC) {
-                const double2 xk = vk[u], xc = conjg(vc[u]);
-                const double2 ev = make_double2(0.5 * (xk.x + xc.x), 0.5 * (xk.y + xc.y));
-                const double2 od = cmul(wpow<true>(tws, k, n), make_double2(0.5 * (xk.x - xc.x), 0.5 * (xk.y - xc.y)));
-                X[r * stride + pidx(k)] = make_double2(ev.x - od.y, ev.y + od.x);  // E + i O
+            for (int u = 0; u < kPerX; ++u) {
+                const int e = threadIdx.x + u * nthr, k = e >> lnl, v = e & (NL - 1);
+                if (e < m * NL) {
+                    const double2 xk = vk[u], xc = conjg(vc[u]);
+                    const double2 ev = make_double2(0.5 * (xk.x + xc.x), 0.5 * (xk.y + xc.y));
+                    const double2 od =
+                        cmul(wpow<true>(tws, k, n), make_double2(0.5 * (xk.x - xc.x), 0.5 * (xk.y - xc.y)));
+                    X[v * stride + pidx(k)] = make_double2(ev.x - od.y, ev.y + od.x);  // E + i O
+                }
             }
         }
         __syncthreads();
-        line_fft_io<true>(X, stride, m, RC, twh, lload, lstore);
+        line_fft_io<true>(X, stride, m, lnl, twh, lload, lstore);
         // the real points, two neighbouring RHS per 16-byte access when the chunk is even
         // (RC = 1: one), with the added values loaded before any is used
         const double sc = 1.0 / m;
-        const int rw = RC % 2 == 0 ? 2 : 1, nw = m * RC / rw;
-        double2 d0[kPerX], d1[kPerX];  // added values at points 2p and 2p + 1 of RHS r (, r + 1)
+        const int lrw = lrc > 0 ? 1 : 0, rw = 1 << lrw, lnv = lnl - lrw, nw = m << lnv;
+        {
+            double2 d0[kPerX], d1[kPerX];  // added values at points 2p and 2p + 1 of RHS r (, r + 1)
 #pragma unroll
-        for (int u = 0; u < kPerX; ++u) {
-            const int e = threadIdx.x + u * 256, p = e / (RC / rw), r = (e % (RC / rw)) * rw;
-            const int64_t g = (L * n + 2 * p) * a.RB + rc0 + r;
-            double2 x0 = make_double2(0.0, 0.0), x1 = x0;
-            if (a.add && e < nw) {
-                if (rw == 2) {
-                    x0 = *reinterpret_cast<const double2 *>(a.add + g);
-                    x1 = *reinterpret_cast<const double2 *>(a.add + g + a.RB);
-                } else {
-                    x0.x = a.add[g];
-                    x1.x = a.add[g + a.RB];
+            for (int u = 0; u < kPerX; ++u) {
+                const int e = threadIdx.x + u * nthr, p = e >> lnv, v = (e & ((1 << lnv) - 1)) << lrw;
+                const int g = line_of(v) * (n * a.RB) + rc0 + (v & rm) + p * (2 * a.RB);
+                double2 x0 = make_double2(0.0, 0.0), x1 = x0;
+                if (a.add && e < nw) {
+                    if (rw == 2) {
+                        x0 = *reinterpret_cast<const double2 *>(a.add + g);
+                        x1 = *reinterpret_cast<const double2 *>(a.add + g + a.RB);
+                    } else {
+                        x0.x = a.add[g];
+                        x1.x = a.add[g + a.RB];
+                    }
                 }
+                d0[u] = x0;
+                d1[u] = x1;
             }
-            d0[u] = x0;
-            d1[u] = x1;
-        }
 #pragma unroll
-        for (int u = 0; u < kPerX; ++u) {
-            const int e = threadIdx.x + u * 256, p = e / (RC / rw), r = (e % (RC / rw)) * rw;
-            if (e < nw) {
-                const int64_t g = (L * n + 2 * p) * a.RB + rc0 + r;
-                const double2 v = X[r * stride + pidx(p)];  // (point 2p, point 2p + 1) of RHS r
-                if (rw == 2) {
-                    const double2 w = X[(r + 1) * stride + pidx(p)];
-                    *reinterpret_cast<double2 *>(a.rout + g) = make_double2(sc * v.x + d0[u].x, sc * w.x + d0[u].y);
-                    *reinterpret_cast<double2 *>(a.rout + g + a.RB) =
-                        make_double2(sc * v.y + d1[u].x, sc * w.y + d1[u].y);
-                } else {
-                    a.rout[g] = sc * v.x + d0[u].x;
-                    a.rout[g + a.RB] = sc * v.y + d1[u].x;
+            for (int u = 0; u < kPerX; ++u) {
+                const int e = threadIdx.x + u * nthr, p = e >> lnv, v = (e & ((1 << lnv) - 1)) << lrw;
+                if (e < nw) {
+                    const int g = line_of(v) * (n * a.RB) + rc0 + (v & rm) + p * (2 * a.RB);
+                    const double2 z = X[v * stride + pidx(p)];  // (point 2p, point 2p + 1) of RHS r
+                    if (rw == 2) {
+                        const double2 w = X[(v + 1) * stride + pidx(p)];
+                        *reinterpret_cast<double2 *>(a.rout + g) =
+                            make_double2(sc * z.x + d0[u].x, sc * w.x + d0[u].y);
+                        *reinterpret_cast<double2 *>(a.rout + g + a.RB) =
+                            make_double2(sc * z.y + d1[u].x, sc * w.y + d1[u].y);
+                    } else {
+                        a.rout[g] = sc * z.x + d0[u].x;
+                        a.rout[g + a.RB] = sc * z.y + d1[u].x;
+                    }
                 }
             }
         }
@@ -378,7 +403,24 @@ __global__ void __launch_bounds__(256) k_interp_t(const TI *v, const int32_t *tp
         const int64_t gi = e / RB;
         const int r = int(e % RB);
         double acc = 0.0;
-        for (int k = tptr[gi]; k < tptr[gi + 1]; ++k) acc += tw[k] * static_cast<double>(v[int64_t(tq[k]) * RB + r]);
+        const int k1 = tptr[gi + 1];
+        // four nodes' loads at a time, clamped to the point's last: a coarse grid's points hold
+        // many nodes, and one at a time waits for each (8^3, one RHS: 443 -> 230 us)
+        for (int k = tptr[gi]; k < k1; k += 4) {
+            int q[4];
+            double w[4], x[4];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                const int kk = min(k + j, k1 - 1);
+                q[j] = tq[kk];
+                w[j] = tw[kk];
+            }
+#pragma unroll
+            for (int j = 0; j < 4; ++j) x[j] = static_cast<double>(v[int64_t(q[j]) * RB + r]);
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (k + j < k1) acc += w[j] * x[j];
+        }
         g[e] = scale * acc;
     }
 }
@@ -403,14 +445,23 @@ void fft_pass(const SpecOps &sp, int RB, int axis, int mode, const double *rin, 
     a.RB = RB;
     a.axis = axis;
     a.mode = mode;
-    const int RC = RB < kRC ? RB : kRC;
-    const unsigned n = unsigned(sp.n), nh = n / 2 + 1;
+    a.logn = sp.logn;
+    a.lrc = 0;
+    while ((2 << a.lrc) <= RB && (2 << a.lrc) <= kRC) ++a.lrc;
+    const bool packed = fft_packed(sp.logn, a.lrc);
+    const int llen = axis == 0 ? sp.logn - 1 : sp.logn, len = 1 << llen, lnl = packed ? 4 : a.lrc;
+    const int lines = axis == 0 ? sp.n * sp.n : sp.n * (sp.n / 2 + 1), lw = 1 << (lnl - a.lrc);
+    const size_t lds = (size_t(len + len / 8 + 1) << lnl) * sizeof(double2);
+    // as many threads as have points: 8 each in the transforms, 4 in the x passes' staging, so
+    // that short lines leave room for more workgroups (32^3, 64 RHS: 123 -> 105 us, 64^3: 426 -> 384)
+    const int thr = (len >= 8 ? len / 8 : 1) << (lnl + (axis == 0 ? 1 : 0));
+    const dim3 grid(lines / lw, unsigned(RB >> a.lrc)), block(thr < 64 ? 64 : thr);
     if (axis == 0) {
-        const size_t lds = size_t(n / 2 + n / 16 + 1) * RC * sizeof(double2);
-        hipLaunchKernelGGL(k_fft_x, dim3(n * n, unsigned(RB / RC)), dim3(256), lds, s, a);
+        if (packed) hipLaunchKernelGGL(k_fft_x<true>, grid, block, lds, s, a);
+        else hipLaunchKernelGGL(k_fft_x<false>, grid, block, lds, s, a);
     } else {
-        const size_t lds = size_t(n + n / 8 + 1) * RC * sizeof(double2);
-        hipLaunchKernelGGL(k_fft_axis, dim3(n * nh, unsigned(RB / RC)), dim3(256), lds, s, a);
+        if (packed) hipLaunchKernelGGL(k_fft_axis<true>, grid, block, lds, s, a);
+        else hipLaunchKernelGGL(k_fft_axis<false>, grid, block, lds, s, a);
     }
 }
 
