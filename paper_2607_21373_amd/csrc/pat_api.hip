@@ -1143,6 +1143,16 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
                 rspec[i] = int32_t(spec.size() / 2);
             }
         }
+        std::vector<int32_t> order(size_t(hp.n)), pos(size_t(hp.n));
+        for (int32_t i = 0; i < hp.n; ++i) order[i] = i;
+        auto kind = [&](int32_t i) {
+            return (hp.xptr[i + 1] > hp.xptr[i] ? 4 : 0) + (hp.bsoff[i] >= 0 ? 2 : 0) +
+                   (hp.injptr[i + 1] > hp.injptr[i] ? 1 : 0);
+        };
+        std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return kind(x) > kind(y); });
+        for (int32_t i = 0; i < hp.n; ++i) pos[order[i]] = i;
+        UP(order, order);
+        UP(pos, pos);
         op.n_spec = int32_t(spec.size() / 2);
         op.n_x = hp.xptr[hp.n];
         op.n_inj = hp.injptr[hp.n];

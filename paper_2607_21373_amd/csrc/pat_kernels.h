@@ -38,6 +38,9 @@ struct DevOps {
     const double *ht_bw = nullptr;
     int32_t n_ht = 0;
     int32_t n_cu = 0;  // compute units of the device
+    // rows of a kind together (overflow entries, boundary, sensor weights, neither), and its
+    // inverse (pat_small.hip)
+    const int32_t *order = nullptr, *pos = nullptr;
     double dt = 0.0;
     // sizes of the extra tables: records, boundary rows and their largest bnum, entries beyond the
     // padded slots, sensor weights, and the largest count of either kind in one row

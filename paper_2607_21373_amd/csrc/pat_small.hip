@@ -60,6 +60,7 @@ __host__ __device__ inline SmallLds small_lds(int cap, const SmallSizes &z, bool
 template <typename T>
 struct SmallArgs {
     const int32_t *ecol, *xcol, *rspec;
+    const int32_t *order, *pos;  // row at each place, place of each row (rows of a kind together)
     const T *eval, *xval, *bslot, *dtm;
     const int4 *spec;
     // forward: sensor rows; transpose: their transpose by node (CSR)
@@ -90,7 +91,10 @@ struct SmallTables {
     int n_spec, nb4;
 };
 
-// The rows of one thread (row threadIdx.x + u blockDim.x).  SPLIT: the sums of the
+// The rows of one thread: those at places threadIdx.x + u blockDim.x of the order that
+// puts rows with overflow entries, boundary rows and sensor rows together, so that few
+// waves walk those tables (in the node order nearly every wave of a small mesh has some of
+// each).  State vectors are held by place.  SPLIT: the sums of the
 // scalar-lane kernels (four partial sums over every fourth slot), for the block widths
 // those kernels take; else one sum in slot order.
 template <typename T, int RPT, bool SPLIT>
@@ -108,14 +112,15 @@ struct SmallRows {
     __device__ __forceinline__ void load(const SmallArgs<T> &a, uint32_t *rec, T *bw) {
 #pragma unroll
         for (int u = 0; u < RPT; ++u) {
-            const int row = int(threadIdx.x) + u * int(blockDim.x);
+            const int at = int(threadIdx.x) + u * int(blockDim.x);
             sp[u] = 0;
             dm[u] = T(0);
 #pragma unroll
             for (int j = 0; j < 16; ++j) kv[u][j] = T(0);
 #pragma unroll
             for (int j = 0; j < 8; ++j) off[u][j] = 0u;
-            if (row >= a.z.n) continue;
+            if (at >= a.z.n) continue;
+            const int row = a.order[at];
             int32_t c[16];
             T w[16];
 #pragma unroll
@@ -123,6 +128,8 @@ struct SmallRows {
                 load_quad(a.ecol + int64_t(row) * 16 + 4 * p, c + 4 * p);
                 load_quad(a.eval + int64_t(row) * 16 + 4 * p, w + 4 * p);
             }
+#pragma unroll
+            for (int j = 0; j < 16; ++j) c[j] = a.pos[c[j]];
 #pragma unroll
             for (int j = 0; j < 16; ++j) {  // slot j at quad j % 4, element j / 4
                 kv[u][j] = w[4 * (j % 4) + j / 4];
@@ -144,10 +151,10 @@ struct SmallRows {
         }
     }
 
-    // acc = K X and bacc = B D of row u (D the increments S - Sp), and the row's own X
-    // (slot 0)
-    __device__ __forceinline__ void sums(int u, const char *X, const char *D, bool negate, const SmallTables<T> &t,
-                                         T &acc, T &bacc, T &cur) {
+    // acc = K X and bacc = B D (NEGATE: -B D) of row u, and the row's own X (slot 0)
+    template <bool NEGATE>
+    __device__ __forceinline__ void sums(int u, const char *X, const char *D, const SmallTables<T> &t, T &acc, T &bacc,
+                                         T &cur) {
         // unpacked again in every step: kept apart they would take twice the registers
 #pragma unroll
         for (int j = 0; j < 8; ++j) asm volatile("" : "+v"(off[u][j]));
@@ -181,7 +188,7 @@ struct SmallRows {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     T &o = b[SPLIT ? j : 0];
-                    o = mad(wv[j], j0 + j < nb ? (negate ? -d[j] : d[j]) : T(0), o);
+                    o = mad(wv[j], j0 + j < nb ? (NEGATE ? -d[j] : d[j]) : T(0), o);
                 }
             }
             for (int k = 0; k < nx; k += 4) {  // four entries' reads at a time, clamped to the row's last
@@ -231,17 +238,17 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(const SmallArgs<T> 
     R.load(a, rec, bw);
     for (int e = tid; e < a.z.n_x; e += nt) {
         xv[e] = a.xval[e];
-        xc[e] = uint16_t(a.xcol[e] * int(sizeof(T)));
+        xc[e] = uint16_t(a.pos[a.xcol[e]] * int(sizeof(T)));
     }
     for (int e = tid; e < 4 * a.z.n_obs; e += nt) {
         sw[e] = a.sw[e];
-        sn[e] = uint16_t(a.snode[e] * int(sizeof(T)));
+        sn[e] = uint16_t(a.pos[a.snode[e]] * int(sizeof(T)));
     }
 #pragma unroll
     for (int u = 0; u < RPT; ++u) {
         const int row = tid + u * nt;
         if (row < a.z.n) {
-            const T v = a.in[int64_t(row) * a.RB + r];
+            const T v = a.in[int64_t(a.order[row]) * a.RB + r];
             reinterpret_cast<T *>(lds)[row] = v;
             reinterpret_cast<T *>(lds + 2 * VB)[row] = v;  // S^{-1} = S^0
             reinterpret_cast<T *>(lds + l.inc)[row] = v - v;
@@ -281,7 +288,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(const SmallArgs<T> 
             if (row < a.z.n) {
                 T acc, bacc, cur;
                 const T d = reinterpret_cast<const T *>(D)[row];
-                R.sums(u, X, D, false, tab, acc, bacc, cur);
+                R.template sums<false>(u, X, D, tab, acc, bacc, cur);
                 const T z = step_update_d(cur, d, acc, bacc, T(0), R.dm[u], a.dt);
                 Z[row] = z;
                 E[row] = z - cur;
@@ -314,7 +321,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_adj_small(const SmallArgs<T> 
     R.load(a, rec, bw);
     for (int e = tid; e < a.z.n_x; e += nt) {
         xv[e] = a.xval[e];
-        xc[e] = uint16_t(a.xcol[e] * int(sizeof(T)));
+        xc[e] = uint16_t(a.pos[a.xcol[e]] * int(sizeof(T)));
     }
     for (int e = tid; e < a.z.n_inj; e += nt) {
         iw[e] = a.injw[e];
@@ -359,41 +366,44 @@ __global__ void __launch_bounds__(kSmallThreads) k_adj_small(const SmallArgs<T> 
     }
     lds_barrier();
     // step k: q_k in vector k % 3, q_{k-1} in (k + 2) % 3, q_{k+1} into (k + 1) % 3, q_k -
-    // q_{k-1} in increment vector k % 2; the last (k = N_T - 1) writes the result instead
+    // q_{k-1} in increment vector k % 2
     auto step = [&](auto U, int k) {
         constexpr int m = decltype(U)::value;
-        const char *X = lds + m * VB, *Y = lds + (m + 2) % 3 * VB;
-        const char *D = lds + l.inc + (k & 1) * IB;
+        const char *X = lds + m * VB, *D = lds + l.inc + (k & 1) * IB;
         T *Z = reinterpret_cast<T *>(lds + (m + 1) % 3 * VB), *E = reinterpret_cast<T *>(lds + l.inc + (~k & 1) * IB);
-        const bool last = k == NT - 1;
-        const int tb = last ? 0 : NT - 2 - k, ta = last ? -1 : tb + 1;
-        if (!last) {
-            put(tb - 1, pend[m]);  // read by the next step; its slot held yhat^{ta + 1}
-            pend[m] = fetch(tb - 4);
-        }
+        const int tb = NT - 2 - k;
+        put(tb - 1, pend[m]);  // read by the next step; its slot held yhat^{tb + 2}
+        pend[m] = fetch(tb - 4);
 #pragma unroll
         for (int u = 0; u < RPT; ++u) {
             const int row = tid + u * nt;
             if (row < a.z.n) {
                 T acc, bacc, cur;
-                R.sums(u, X, last ? Y : D, last, tab, acc, bacc, cur);  // the closing step: -B q_{k-1}
-                const T src = T(0.5) * inject(u, ta, tb);
-                if (last) {
-                    const T prev = reinterpret_cast<const T *>(Y)[row];
-                    a.out[int64_t(row) * a.RB + r] = adj_result(cur, prev, acc, bacc, src, R.dm[u], a.dt);
-                } else {
-                    const T z = step_update_d(cur, reinterpret_cast<const T *>(D)[row], acc, bacc, src, R.dm[u], a.dt);
-                    Z[row] = z;
-                    E[row] = z - cur;
-                }
+                R.template sums<false>(u, X, D, tab, acc, bacc, cur);
+                const T src = T(0.5) * inject(u, tb + 1, tb);
+                const T z = step_update_d(cur, reinterpret_cast<const T *>(D)[row], acc, bacc, src, R.dm[u], a.dt);
+                Z[row] = z;
+                E[row] = z - cur;
             }
         }
         lds_barrier();
     };
-    for (int k = 0; k < NT; k += 3)
+    for (int k = 0; k < NT - 1; k += 3)
         static_for<0, 3>([&](auto U) {
-            if (k + U.value < NT) step(U, k + U.value);
+            if (k + U.value < NT - 1) step(U, k + U.value);
         });
+    // the closing step, with -B q_{k-1}
+    const char *X = lds + (NT - 1) % 3 * VB, *Y = lds + (NT + 1) % 3 * VB;
+#pragma unroll
+    for (int u = 0; u < RPT; ++u) {
+        const int row = tid + u * nt;
+        if (row < a.z.n) {
+            T acc, bacc, cur;
+            R.template sums<true>(u, X, Y, tab, acc, bacc, cur);
+            const T src = T(0.5) * inject(u, -1, 0), prev = reinterpret_cast<const T *>(Y)[row];
+            a.out[int64_t(a.order[row]) * a.RB + r] = adj_result(cur, prev, acc, bacc, src, R.dm[u], a.dt);
+        }
+    }
 }
 
 SmallSizes small_sizes(const DevOps &op) {
@@ -404,13 +414,13 @@ template <typename T>
 SmallArgs<T> small_args(const DevOps &op, int RB);
 template <>
 SmallArgs<double> small_args<double>(const DevOps &op, int RB) {
-    return SmallArgs<double>{op.ell_col, op.xcol, op.rspec, op.ell_val64, op.xval64, op.bslot64, op.dtm64, op.spec,
+    return SmallArgs<double>{op.ell_col, op.xcol, op.rspec, op.order, op.pos, op.ell_val64, op.xval64, op.bslot64, op.dtm64, op.spec,
                              op.snode, op.injs, op.sw64, op.injw64, nullptr, nullptr, nullptr, 1.0,
                              small_sizes(op), op.n_steps, RB, op.dt};
 }
 template <>
 SmallArgs<float> small_args<float>(const DevOps &op, int RB) {
-    return SmallArgs<float>{op.ell_col, op.xcol, op.rspec, op.ell_val32, op.xval32, op.bslot32, op.dtm32, op.spec,
+    return SmallArgs<float>{op.ell_col, op.xcol, op.rspec, op.order, op.pos, op.ell_val32, op.xval32, op.bslot32, op.dtm32, op.spec,
                             op.snode, op.injs, op.sw32, op.injw32, nullptr, nullptr, nullptr, 1.0,
                             small_sizes(op), op.n_steps, RB, float(op.dt)};
 }
