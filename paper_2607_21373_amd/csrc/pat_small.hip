@@ -2,19 +2,25 @@
 //
 // A step of a mesh of a few thousand nodes is launch- and latency-bound: each step
 // kernel takes 3 to 8 us whatever its work.  Here one workgroup owns one right-hand
-// side for the whole sweep.  The state lives in LDS (three rotating vectors), every
-// thread keeps the padded stiffness rows it owns in registers (RPT rows of 16 weights
-// and 16 LDS offsets), and the boundary, overflow and sensor tables sit in LDS, so a
-// step is 16 LDS reads per row and one barrier, with no launch and no traffic but the
-// sensor data.  Right-hand sides are independent, so workgroups never wait for each
-// other.  A row's arithmetic is the step kernels' (pat_step.h, in their slot order),
-// and so are the bits.
+// side for the whole sweep.  The state lives in LDS (three rotating vectors, and two of
+// its increments, which the boundary part reads), every thread keeps in registers the
+// padded stiffness rows it owns (RPT rows of 16 weights and 16 LDS offsets), their state,
+// records, first B values and overflow columns, and the rest of the boundary, overflow
+// and sensor tables sit in LDS.  So a step is 15 LDS reads per row and one barrier, with
+// no launch and no traffic but the sensor data.  Right-hand sides are independent, so
+// workgroups never wait for each other.  A row's arithmetic is the step kernels'
+// (pat_step.h, in their slot order), and so are the bits.
 //
-// Bound: the LDS reads of the CU that holds the right-hand side (16 gathers per row, at
-// several cycles each for the bank conflicts of their addresses).  Measured per forward /
-// transposed step: 729 nodes, one float64 RHS 1.6 / 1.9 us against 3.0 / 3.2 us as step
-// launches, 16 RHS 1.7 / 1.9 against 6.9 / 7.5; 2,028 nodes, 16 float32 RHS 2.5 / 2.8
-// against 7.7 / 7.9.
+// Bound: the barrier waits for the wave with the longest chain, the one with overflow
+// rows, and for the LDS reads of the CU that holds the right-hand side (15 gathers per
+// row, at several cycles each for the bank conflicts of their addresses; without the
+// special rows a step of 729 nodes takes 0.7 us).  The overflow entries in a loop of four
+// took two dependent LDS reads a turn (an 11-entry row: 0.5 us of a step); with their
+// columns in registers all reads of a group go out together.  Measured per forward /
+// transposed step: 729 nodes, one float64 RHS 1.05 / 1.29 us (3.0 / 3.2 as step launches;
+// 1.58 / 1.81 with records, B values and overflow columns read from LDS), 16 RHS 1.04 /
+// 1.19 (6.9 / 7.5; 1.65 / 1.91); 1,331 nodes, one float32 RHS 1.33 / 1.46 (1.64 / 1.92
+// from LDS); 2,028 nodes, 16 float32 RHS 1.75 / 1.76 (7.7 / 7.9; 1.88 / 1.95).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -27,6 +33,8 @@ namespace {
 
 constexpr int kSmallThreads = 1024;
 constexpr size_t kLdsBytes = 163840;
+
+constexpr int kOverRegs = 12;  // overflow entries whose columns a thread of one row keeps in registers
 
 // LDS behind the three state vectors (bytes from the start): two vectors of the state's
 // increments, the records of the rows with more than padded slots, the B values by
@@ -47,7 +55,7 @@ __host__ __device__ inline SmallLds small_lds(int cap, const SmallSizes &z, bool
     l.rec = l.inc + 2 * up(size_t(z.n) * sizeof(T));
     l.bw = l.rec + up(size_t(3) * z.n_spec * sizeof(uint32_t));
     l.xv = l.bw + up(size_t(z.n_bnd) * z.nb4() * sizeof(T));
-    l.xc = l.xv + up(size_t(z.n_x) * sizeof(T));
+    l.xc = l.xv + up(size_t(z.n_x + kOverRegs) * sizeof(T));  // rows read kOverRegs values, used or not
     l.sw = l.xc + up(size_t(z.n_x) * sizeof(uint16_t));
     l.sn = l.sw + (fwd ? up(size_t(4) * z.n_obs * sizeof(T)) : 0);
     l.iw = l.sn + (fwd ? up(size_t(4) * z.n_obs * sizeof(uint16_t)) : 0);
@@ -97,13 +105,23 @@ struct SmallTables {
 // each).  State vectors are held by place.  SPLIT: the sums of the
 // scalar-lane kernels (four partial sums over every fourth slot), for the block widths
 // those kernels take; else one sum in slot order.
-template <typename T, int RPT, bool SPLIT>
+template <typename T, int RPT, bool SPLIT, bool FWD>
 struct SmallRows {
     static constexpr int CAP = RPT * kSmallThreads;
+    // what a step would read again from LDS and the registers hold (not with two float64 rows):
+    // the row's state and increment, its record, and the first NBR of its B values
+    static constexpr bool KEEP = RPT * sizeof(T) <= 8;
+    static constexpr int NBR = !KEEP ? 0 : !FWD && SPLIT && RPT * sizeof(T) > 4 ? 4 : 8;
     uint32_t off[RPT][8];  // byte offsets of slots 2j and 2j + 1
     T kv[RPT][16];
     T dm[RPT];
     int sp[RPT];           // 0, or 1 + the row's record
+    T own[RPT], inc[RPT];
+    uint32_t rb[RPT], rx[RPT], re[RPT];
+    T bv[RPT][NBR > 0 ? NBR : 1];
+    // byte offsets of overflow entries 2j and 2j + 1 of the first row
+    static constexpr int NXR = KEEP ? kOverRegs : 0;
+    uint32_t xo[NXR / 2 + 1];
 
     __device__ __forceinline__ uint32_t slot(int u, int j) const {
         return j & 1 ? off[u][j >> 1] >> 16 : off[u][j >> 1] & 0xFFFFu;
@@ -114,9 +132,14 @@ struct SmallRows {
         for (int u = 0; u < RPT; ++u) {
             const int at = int(threadIdx.x) + u * int(blockDim.x);
             sp[u] = 0;
+            rb[u] = rx[u] = re[u] = 0u;
             dm[u] = T(0);
 #pragma unroll
             for (int j = 0; j < 16; ++j) kv[u][j] = T(0);
+#pragma unroll
+            for (int j = 0; j < NBR; ++j) bv[u][j] = T(0);
+#pragma unroll
+            for (int j = 0; j < NXR / 2 && u == 0; ++j) xo[j] = 0u;
 #pragma unroll
             for (int j = 0; j < 8; ++j) off[u][j] = 0u;
             if (at >= a.z.n) continue;
@@ -141,9 +164,20 @@ struct SmallRows {
             if (const int k = a.rspec[row]) {
                 const int4 s = a.spec[2 * (k - 1)], v = a.spec[2 * (k - 1) + 1];
                 sp[u] = k;
-                rec[k - 1] = uint32_t(v.z | s.y << 16);
-                rec[a.z.n_spec + k - 1] = uint32_t(s.z | (s.w - s.z) << 16);
-                rec[2 * a.z.n_spec + k - 1] = uint32_t(v.x | (v.y - v.x) << 16);
+                rb[u] = uint32_t(v.z | s.y << 16);
+                rx[u] = uint32_t(s.z | (s.w - s.z) << 16);
+                re[u] = uint32_t(v.x | (v.y - v.x) << 16);
+                rec[k - 1] = rb[u];
+                rec[a.z.n_spec + k - 1] = rx[u];
+                rec[2 * a.z.n_spec + k - 1] = re[u];
+#pragma unroll
+                for (int j = 0; j < NBR; ++j)
+                    if (j < s.y) bv[u][j] = a.bslot[s.x + 4 * (j % 4) + j / 4];
+                if (u == 0 && s.w > s.z) {
+#pragma unroll
+                    for (int j = 0; j < NXR; ++j)
+                        xo[j >> 1] |= uint32_t(a.pos[a.xcol[min(s.z + j, s.w - 1)]] * int(sizeof(T))) << (16 * (j & 1));
+                }
                 if (s.y)
                     for (int j = 0; j < a.z.nb4(); ++j)
                         bw[v.z * a.z.nb4() + j] = j < s.y ? a.bslot[s.x + 4 * (j % 4) + j / 4] : T(0);
@@ -164,8 +198,9 @@ struct SmallRows {
         for (int j0 = 0; j0 < 16; j0 += CH) {
             T x[CH];
 #pragma unroll
-            for (int j = 0; j < CH; ++j) x[j] = *reinterpret_cast<const T *>(X + slot(u, j0 + j));
-            if (j0 == 0) cur = x[0];
+            for (int j = 0; j < CH; ++j)
+                x[j] = KEEP && j0 + j == 0 ? own[u] : *reinterpret_cast<const T *>(X + slot(u, j0 + j));
+            if (j0 == 0) cur = KEEP ? own[u] : x[0];
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
                 T &o = s[SPLIT ? j % 4 : 0];
@@ -174,12 +209,24 @@ struct SmallRows {
             if (CH == 4) __builtin_amdgcn_sched_barrier(0);
         }
         if (sp[u]) {
-            const uint32_t rb = t.rec[sp[u] - 1], rx = t.rec[t.n_spec + sp[u] - 1];
-            const int nb = int(rb >> 16), nx = int(rx >> 16), x0 = int(rx & 0xFFFFu);
-            // four slots at a time; those past nb have weight 0 in the table and add +0
-            const T *w = t.bw + int(rb & 0xFFFFu) * t.nb4;
+            const uint32_t rbu = KEEP ? rb[u] : t.rec[sp[u] - 1], rxu = KEEP ? rx[u] : t.rec[t.n_spec + sp[u] - 1];
+            const int nb = int(rbu >> 16), nx = int(rxu >> 16), x0 = int(rxu & 0xFFFFu);
+            // those past nb have weight 0 in the table and add +0
+            const T *w = t.bw + int(rbu & 0xFFFFu) * t.nb4;
+            if constexpr (KEEP) {
+                if (nb) {
+                    T d[NBR];
 #pragma unroll
-            for (int j0 = 0; j0 < 16; j0 += 4) {
+                    for (int j = 0; j < NBR; ++j) d[j] = *reinterpret_cast<const T *>(D + slot(u, j));
+#pragma unroll
+                    for (int j = 0; j < NBR; ++j) {
+                        T &o = b[SPLIT ? j % 4 : 0];
+                        o = mad(bv[u][j], j < nb ? (NEGATE ? -d[j] : d[j]) : T(0), o);
+                    }
+                }
+            }
+#pragma unroll
+            for (int j0 = NBR; j0 < 16; j0 += 4) {  // four slots at a time
                 if (j0 >= nb) break;
                 T wv[4], d[4];
                 load_quad(w + j0, wv);
@@ -191,7 +238,32 @@ struct SmallRows {
                     o = mad(wv[j], j0 + j < nb ? (NEGATE ? -d[j] : d[j]) : T(0), o);
                 }
             }
-            for (int k = 0; k < nx; k += 4) {  // four entries' reads at a time, clamped to the row's last
+            // overflow entries: the columns in registers, XG values at a time
+            const int kr = u == 0 ? NXR : 0;
+            if (kr > 0) {
+                constexpr int XG = SPLIT && sizeof(T) > 4 ? 4 : 6;
+#pragma unroll
+                for (int j = 0; j < NXR / 2; ++j) asm volatile("" : "+v"(xo[j]));
+                static_for<0, NXR, XG>([&](auto K0) {
+                    constexpr int k0 = decltype(K0)::value;
+                    if (k0 < nx) {
+                        T v[XG], y[XG];
+#pragma unroll
+                        for (int p = 0; p < XG; ++p) {
+                            y[p] = *reinterpret_cast<const T *>(
+                                X + ((k0 + p) & 1 ? xo[(k0 + p) >> 1] >> 16 : xo[(k0 + p) >> 1] & 0xFFFFu));
+                            v[p] = t.xv[x0 + k0 + p];
+                        }
+#pragma unroll
+                        for (int p = 0; p < XG; ++p)
+                            if (k0 + p < nx) {
+                                T &o = s[SPLIT ? (k0 + p) % 4 : 0];
+                                o = mad(v[p], y[p], o);
+                            }
+                    }
+                });
+            }
+            for (int k = kr; k < nx; k += 4) {  // four entries' reads at a time, clamped to the row's last
                 T v[4], y[4];
                 uint32_t c[4];
 #pragma unroll
@@ -225,7 +297,7 @@ struct SmallRows {
 template <typename T, typename OT, int RPT, bool SPLIT>
 __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(const SmallArgs<T> a) {
     extern __shared__ __align__(16) char lds[];
-    using Rows = SmallRows<T, RPT, SPLIT>;
+    using Rows = SmallRows<T, RPT, SPLIT, true>;
     constexpr uint32_t VB = uint32_t(Rows::CAP * sizeof(T));
     const SmallLds l = small_lds<T>(Rows::CAP, a.z, true);
     const uint32_t IB = uint32_t((l.rec - l.inc) / 2);
@@ -252,6 +324,8 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(const SmallArgs<T> 
             reinterpret_cast<T *>(lds)[row] = v;
             reinterpret_cast<T *>(lds + 2 * VB)[row] = v;  // S^{-1} = S^0
             reinterpret_cast<T *>(lds + l.inc)[row] = v - v;
+            R.own[u] = v;
+            R.inc[u] = v - v;
         }
     }
     const SmallTables<T> tab{rec, bw, xv, xc, a.z.n_spec, a.z.nb4()};
@@ -287,11 +361,11 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(const SmallArgs<T> 
             const int row = tid + u * nt;
             if (row < a.z.n) {
                 T acc, bacc, cur;
-                const T d = reinterpret_cast<const T *>(D)[row];
+                const T d = Rows::KEEP ? R.inc[u] : reinterpret_cast<const T *>(D)[row];
                 R.template sums<false>(u, X, D, tab, acc, bacc, cur);
                 const T z = step_update_d(cur, d, acc, bacc, T(0), R.dm[u], a.dt);
-                Z[row] = z;
-                E[row] = z - cur;
+                Z[row] = R.own[u] = z;
+                E[row] = R.inc[u] = z - cur;
             }
         }
         lds_barrier();
@@ -308,7 +382,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_fwd_small(const SmallArgs<T> 
 template <typename T, typename YT, int RPT, bool SPLIT>
 __global__ void __launch_bounds__(kSmallThreads) k_adj_small(const SmallArgs<T> a) {
     extern __shared__ __align__(16) char lds[];
-    using Rows = SmallRows<T, RPT, SPLIT>;
+    using Rows = SmallRows<T, RPT, SPLIT, false>;
     constexpr uint32_t VB = uint32_t(Rows::CAP * sizeof(T));
     const SmallLds l = small_lds<T>(Rows::CAP, a.z, false);
     const uint32_t IB = uint32_t((l.rec - l.inc) / 2);
@@ -340,7 +414,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_adj_small(const SmallArgs<T> 
     auto inject = [&](int u, int ta, int tb) {
         T v = T(0);
         if (!R.sp[u]) return v;
-        const uint32_t re = rec[2 * a.z.n_spec + R.sp[u] - 1];
+        const uint32_t re = Rows::KEEP ? R.re[u] : rec[2 * a.z.n_spec + R.sp[u] - 1];
         const int e0 = int(re & 0xFFFFu), ne = int(re >> 16);
         for (int e = e0; e < e0 + ne; ++e) {
             T d = ring[tb % 3 * a.z.n_obs + is[e]];
@@ -362,6 +436,7 @@ __global__ void __launch_bounds__(kSmallThreads) k_adj_small(const SmallArgs<T> 
             reinterpret_cast<T *>(lds)[row] = v;
             reinterpret_cast<T *>(lds + 2 * VB)[row] = T(0);
             reinterpret_cast<T *>(lds + l.inc)[row] = v;
+            R.own[u] = R.inc[u] = v;
         }
     }
     lds_barrier();
@@ -381,9 +456,10 @@ __global__ void __launch_bounds__(kSmallThreads) k_adj_small(const SmallArgs<T> 
                 T acc, bacc, cur;
                 R.template sums<false>(u, X, D, tab, acc, bacc, cur);
                 const T src = T(0.5) * inject(u, tb + 1, tb);
-                const T z = step_update_d(cur, reinterpret_cast<const T *>(D)[row], acc, bacc, src, R.dm[u], a.dt);
-                Z[row] = z;
-                E[row] = z - cur;
+                const T d = Rows::KEEP ? R.inc[u] : reinterpret_cast<const T *>(D)[row];
+                const T z = step_update_d(cur, d, acc, bacc, src, R.dm[u], a.dt);
+                Z[row] = R.own[u] = z;
+                E[row] = R.inc[u] = z - cur;
             }
         }
         lds_barrier();
