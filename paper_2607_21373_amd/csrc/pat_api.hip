@@ -1159,6 +1159,12 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
         const std::vector<double> val = quads(hp.ell_val, rows), bval = quads(hp.bslot, brows);
         UP(quads(hp.ell_col, rows), ell_col);
         UP(rspec, rspec);
+        if (hp.n <= pat::kFewRows) {
+            std::vector<int4> rdir(size_t(hp.n), int4{0, 0, 0, 0});
+            for (int32_t i = 0; i < hp.n; ++i)
+                if (rspec[i]) rdir[i] = spec[size_t(2 * (rspec[i] - 1))];
+            UP(rdir, rdir);
+        }
         UP(spec, spec);
         UP(val, ell_val64);
         UP(bval, bslot64);

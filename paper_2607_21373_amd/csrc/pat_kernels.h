@@ -7,6 +7,10 @@
 
 namespace pat {
 
+// Launches of at most kFewGroups workgroups are latency-bound (few_waves in pat_kernels.hip);
+// a workgroup holds at most 256 rows.
+constexpr int kFewGroups = 512, kFewRows = kFewGroups * 256;
+
 // Device copy of the assembled operators (internal node numbering).
 struct DevOps {
     int32_t n = 0, n_obs = 0, n_steps = 0;
@@ -25,6 +29,9 @@ struct DevOps {
     // rows, 0}
     const int32_t *rspec = nullptr;
     const int4 *spec = nullptr;
+    // the first half of every row's record by row (zero for rows without one), on meshes that
+    // a launch of few waves can hold (kFewRows)
+    const int4 *rdir = nullptr;
     const double *ell_val64 = nullptr, *xval64 = nullptr, *bslot64 = nullptr;
     const float *ell_val32 = nullptr, *xval32 = nullptr, *bslot32 = nullptr;
     // halo tiles (HaloTiles; pat_halo.hip): per tile {first row, first halo entry, rank of its

@@ -64,7 +64,7 @@ __device__ __forceinline__ double lane_sum(double v) {
 // that one 16-byte load gives a lane the columns (or float32 weights) of the four
 // slots it sums or hands out.  Entries beyond 16 in (xptr, xcol, xval); boundary rows
 // hold the B value of each slot at bslot[bsoff[row]], in the same quad order, then
-// the entries beyond 16.  rspec[row] is 0 for the rows with nothing but their padded
+// the entries beyond 16 (bsoff, xptr: a row's record).  rspec[row] is 0 for the rows with nothing but their padded
 // slots, so that most rows read one word for all of that; any other row's extra ranges
 // are record rspec[row] - 1 of `spec`, loaded while the first gathers are in flight.
 template <typename T>
@@ -73,6 +73,7 @@ struct RowOps {
     const T *eval, *xval, *bslot, *dtm;
     const int32_t *rspec;
     const int4 *spec;
+    const int4 *rdir;  // the first half of every row's record, by row (few-wave launches)
 };
 // Operands of one row as seen by one lane of the scalar-lane kernels: its quad of
 // padded slots (part, part + 4, ...), the row's special record and dt/m.
@@ -84,48 +85,159 @@ struct RowMeta {
     T dm;
 };
 
-template <typename T, int RB>
-__device__ __forceinline__ void load_meta(const RowOps<T> &o, int row, int part, RowMeta<T, RB> &m) {
+// DIRECT: launches with few waves (few_waves) wait for the record as long as for everything
+// else, and read it by row with the operands, at 16 bytes a row instead of 4.
+template <bool DIRECT, typename T, int RB>
+__device__ __forceinline__ void load_meta(const RowOps<T> &o, int row, int part, RowMeta<T, RB> &m, RowSpec &rs) {
     using G = Geo<RB>;
     static_assert(G::SPLIT == 4 && G::PER == 4, "one quad of slots per lane");
     const int64_t eb = int64_t(row) * G::W + 4 * part;
     load_quad(o.ecol + eb, m.c);
     load_quad(o.eval + eb, m.w);
-    m.sp = o.rspec[row];
+    if constexpr (DIRECT) rs.load_direct(o.rdir, row);
+    else m.sp = o.rspec[row];
     m.dm = o.dtm[row];
 }
 
 // acc = sum over the row's entries of K(row, k) X[col_k][r], and for a boundary row
 // bacc = sum of B(row, k) bdiff(X[col_k][r], Y[col_k][r]).  All PER gathers of the
 // lane are issued before any is consumed; sums run in slot order, then the entries
-// beyond 16.  rs receives the row's record.
-template <typename T, int RB>
+// beyond 16.  rs receives the row's record (DIRECT: has it), own the row's X value (slot
+// 0, in the lane of part 0).  early: loads of the caller that need the record (first) and
+// what those return (second).
+template <bool DIRECT, typename T, int RB, typename Early>
 __device__ __forceinline__ void row_sums(const RowOps<T> &o, const RowMeta<T, RB> &m, int part, int r,
                                          const T *__restrict__ X, const T *__restrict__ Y, bool only_prev, T &acc,
-                                         T &bacc, RowSpec &rs) {
+                                         T &bacc, T &own, RowSpec &rs, Early &early) {
     using G = Geo<RB>;
     T x[G::PER];
 #pragma unroll
     for (int j = 0; j < G::PER; ++j) x[j] = X[int64_t(m.c[j]) * RB + r];
-    if (m.sp) rs.load(o.spec, m.sp);
+    bool special;
+    if constexpr (DIRECT) {
+        special = rs.any();
+    } else {
+        special = m.sp != 0;
+        if (special) rs.load(o.spec, m.sp);
+    }
+    // everything the record leads to is on its way before any of it is used; entries
+    // beyond 16: XN per lane at a time, clamped to the row's last
+    constexpr int XN = 3;
+    int e[XN];
+    uint32_t cj[XN];
+    T w[XN], xv[XN], bw[G::PER], y[G::PER];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int j = 0; j < XN; ++j) {
+            e[j] = min(k + j * G::SPLIT, rs.x1 - 1);
+            cj[j] = uint32_t(o.xcol[e[j]]) * RB + r;
+            w[j] = o.xval[e[j]];
+        }
+    };
+    auto gather = [&] {
+#pragma unroll
+        for (int j = 0; j < XN; ++j) xv[j] = X[cj[j]];
+    };
+    auto add = [&](int k) {
+        if (rs.nb) {
+            T bv[XN], yv[XN];
+#pragma unroll
+            for (int j = 0; j < XN; ++j) {
+                bv[j] = o.bslot[rs.bo + G::W + (e[j] - rs.x0)];
+                yv[j] = Y[cj[j]];
+            }
+#pragma unroll
+            for (int j = 0; j < XN; ++j)
+                if (k + j * G::SPLIT < rs.x1) bacc = mad(bv[j], bdiff(xv[j], yv[j], only_prev), bacc);
+        }
+#pragma unroll
+        for (int j = 0; j < XN; ++j)
+            if (k + j * G::SPLIT < rs.x1) acc = mad(w[j], xv[j], acc);
+    };
+    int k = rs.x0 + part;
+    const bool over = k < rs.x1;
+    if (special) {
+        if (over) fetch(k);
+        early.first(rs);
+        if (rs.nb) {
+            load_quad(o.bslot + rs.bo + 4 * part, bw);
+#pragma unroll
+            for (int j = 0; j < G::PER; ++j) y[j] = Y[int64_t(m.c[j]) * RB + r];
+        }
+        if (over) gather();
+        early.second(rs);
+    }
+    own = x[0];
 #pragma unroll
     for (int j = 0; j < G::PER; ++j) acc = mad(m.w[j], x[j], acc);
-    if (!m.sp) return;
+    if (!special) return;
     if (rs.nb) {
-        T bw[G::PER], y[G::PER];
-        load_quad(o.bslot + rs.bo + 4 * part, bw);
-#pragma unroll
-        for (int j = 0; j < G::PER; ++j) y[j] = Y[int64_t(m.c[j]) * RB + r];
 #pragma unroll
         for (int j = 0; j < G::PER; ++j) bacc = mad(bw[j], bdiff(x[j], y[j], only_prev), bacc);
     }
-    for (int k = rs.x0 + part; k < rs.x1; k += G::SPLIT) {
-        const int64_t cj = int64_t(o.xcol[k]) * RB + r;
-        const T xv = X[cj];
-        acc = mad(o.xval[k], xv, acc);
-        if (rs.nb) bacc = mad(o.bslot[rs.bo + G::W + (k - rs.x0)], bdiff(xv, Y[cj], only_prev), bacc);
+    if (over) add(k);
+    for (k += XN * G::SPLIT; k < rs.x1; k += XN * G::SPLIT) {
+        fetch(k);
+        gather();
+        add(k);
     }
 }
+
+struct NothingEarly {
+    __device__ __forceinline__ void first(const RowSpec &) {}
+    __device__ __forceinline__ void second(const RowSpec &) {}
+};
+
+// Pi^T (yhat^{ta} + yhat^{tb}) over the injection entries of a row, for VEC right-hand sides
+// from rhs0 (yhat^{ta} left out for ta < 0); A: the kernel's arguments.  The first entry's
+// operands are loaded ahead of the sum if the row sums call first and second.
+template <typename T, typename YT, int RB, int VEC, typename A>
+struct Inject {
+    const A &a;
+    int rhs0;
+    bool mine;  // this lane injects
+    bool ahead = false;
+    int s = 0;
+    T w = T(0);
+    YT ya[VEC], yb[VEC];
+    __device__ __forceinline__ void operands(int e) {
+        s = a.injs[e];
+        w = a.injw[e];
+    }
+    __device__ __forceinline__ void data() {
+        const YT *yh = static_cast<const YT *>(a.yh);
+        const int64_t sb = (int64_t(a.tb) * a.n_obs + s) * RB + rhs0;
+        const int64_t sa = (int64_t(a.ta) * a.n_obs + s) * RB + rhs0;
+#pragma unroll
+        for (int i = 0; i < VEC; ++i) yb[i] = yh[sb + i];
+        if (a.ta >= 0) {
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) ya[i] = yh[sa + i];
+        }
+    }
+    __device__ __forceinline__ void first(const RowSpec &rs) {
+        ahead = true;
+        if (mine && rs.e1 > rs.e0) operands(rs.e0);
+    }
+    __device__ __forceinline__ void second(const RowSpec &rs) {
+        if (mine && rs.e1 > rs.e0) data();
+    }
+    template <typename V>
+    __device__ __forceinline__ void sum(const RowSpec &rs, V &&add) {
+        for (int e = rs.e0; e < rs.e1; ++e) {
+            if (!ahead || e > rs.e0) {
+                operands(e);
+                data();
+            }
+#pragma unroll
+            for (int i = 0; i < VEC; ++i) {
+                T v = static_cast<T>(static_cast<double>(yb[i]) * a.yscale);
+                if (a.ta >= 0) v = static_cast<T>(static_cast<double>(ya[i]) * a.yscale) + v;
+                add(i, w, v);
+            }
+        }
+    }
+};
 
 template <typename T>
 struct FwdArgs {
@@ -145,7 +257,12 @@ struct FwdArgs {
 // tile of RPB rows per workgroup; the sampling blocks placed among them write the
 // samples y = Pi p^n = Pi (S^n + S^{n-1})/2 of the incoming state, one (sensor, RHS)
 // pair per thread.
-template <typename T, typename OT, int RB>
+//
+// Bound: the chain operands -> gathers -> boundary gathers of the waves on small meshes, the
+// operands' traffic on large ones.  The row's own state is in hand when the sums end
+// (its S^n is slot 0, its S^{n-1} comes with the operands): loaded after them it was one more
+// round trip in every wave, 374,400 nodes, 1 float32 RHS 12.45 -> 11.6 us (4.8 TB/s).
+template <typename T, typename OT, int RB, bool DIRECT>
 __global__ void __launch_bounds__(256) k_fwd(const FwdArgs<T> a) {
     using G = Geo<RB>;
     const int tile = fwd_work(xcd_tile(blockIdx.x, gridDim.x), a.n_tiles, a.n_samp);
@@ -155,14 +272,16 @@ __global__ void __launch_bounds__(256) k_fwd(const FwdArgs<T> a) {
         const int row = tile * G::RPB + wave * G::RPW + lane / G::LPR;
         if (row >= a.n) return;
         RowMeta<T, RB> m;
-        load_meta<T, RB>(a.o, row, part, m);
-        const int64_t id = int64_t(row) * RB + r;
-        T acc = T(0), bacc = T(0);
         RowSpec rs;
-        row_sums<T, RB>(a.o, m, part, r, a.S, a.Sp, false, acc, bacc, rs);
+        load_meta<DIRECT>(a.o, row, part, m, rs);
+        const int64_t id = int64_t(row) * RB + r;
+        const T prev = a.Sp[id];
+        T acc = T(0), bacc = T(0), cur;
+        NothingEarly none;
+        row_sums<DIRECT, T, RB>(a.o, m, part, r, a.S, a.Sp, false, acc, bacc, cur, rs, none);
         acc = lane_sum<RB, G::LPR>(acc);
         bacc = lane_sum<RB, G::LPR>(bacc);
-        if (part == 0) a.Sn[id] = step_update(a.S[id], a.Sp[id], acc, bacc, T(0), m.dm, a.dt);
+        if (part == 0) a.Sn[id] = step_update(cur, prev, acc, bacc, T(0), m.dm, a.dt);
         return;
     }
     const int64_t e = int64_t(tile - a.n_tiles) * 256 + threadIdx.x;
@@ -191,23 +310,15 @@ struct AdjArgs {
     T dt;
 };
 
-// (Pi^T (yhat^{ta} + yhat^{tb}))_row for RHS r over the row's injection entries
-// [e0, e1) (yhat^{ta} left out for ta < 0)
-template <typename T, typename YT, int RB>
-__device__ __forceinline__ T inject_range(const AdjArgs<T> &a, int e0, int e1, int r) {
-    const YT *yh = static_cast<const YT *>(a.yh);
-    T inj = T(0);
-    for (int e = e0; e < e1; ++e) {
-        const int s = a.injs[e];
-        T v = static_cast<T>(static_cast<double>(yh[(int64_t(a.tb) * a.n_obs + s) * RB + r]) * a.yscale);
-        if (a.ta >= 0) v = static_cast<T>(static_cast<double>(yh[(int64_t(a.ta) * a.n_obs + s) * RB + r]) * a.yscale) + v;
-        inj = mad(a.injw[e], v, inj);
-    }
-    return inj;
-}
+// (Pi^T (yhat^{ta} + yhat^{tb}))_row for RHS r (yhat^{ta} left out for ta < 0)
 template <typename T, typename YT, int RB>
 __device__ __forceinline__ T inject(const AdjArgs<T> &a, int row, int r) {
-    return inject_range<T, YT, RB>(a, a.injptr[row], a.injptr[row + 1], r);
+    RowSpec rs;
+    rs.load_inject(a.injptr, row);
+    Inject<T, YT, RB, 1, AdjArgs<T>> in{a, r, true};
+    T inj = T(0);
+    in.sum(rs, [&](int, T w, T v) { inj = mad(w, v, inj); });
+    return inj;
 }
 
 // Transposed step q_{k+1} = q_k + (q_k - q_{k-1}) - (dt/m)(dt K q_k + B (q_k - q_{k-1})
@@ -215,7 +326,7 @@ __device__ __forceinline__ T inject(const AdjArgs<T> &a, int row, int r) {
 // (q_k - q_{k-1}) m/dt - (dt K q_k - B q_{k-1} - inj/2), inj = Pi^T yhat^{tb}.
 // One tile of RPB rows per workgroup, each XCD's range walked from its end
 // (xcd_tile_rev).
-template <typename T, typename YT, int RB>
+template <typename T, typename YT, int RB, bool DIRECT>
 __global__ void __launch_bounds__(256) k_adj(const AdjArgs<T> a) {
     using G = Geo<RB>;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -224,16 +335,21 @@ __global__ void __launch_bounds__(256) k_adj(const AdjArgs<T> a) {
     const int row = wrow0 + lane / G::LPR;
     if (row >= a.n) return;
     RowMeta<T, RB> m;
-    load_meta<T, RB>(a.o, row, part, m);
-    const int64_t id = int64_t(row) * RB + r;
-    T kq = T(0), bq = T(0);
     RowSpec rs;
-    row_sums<T, RB>(a.o, m, part, r, a.S, a.Sp, a.last, kq, bq, rs);
+    load_meta<DIRECT>(a.o, row, part, m, rs);
+    if constexpr (DIRECT) {
+        rs.load_inject(a.injptr, row);
+    }
+    const int64_t id = int64_t(row) * RB + r;
+    const T prev = a.Sp[id];
+    T kq = T(0), bq = T(0), cur, inj = T(0);
+    Inject<T, YT, RB, 1, AdjArgs<T>> in{a, r, part == 0};
+    row_sums<DIRECT, T, RB>(a.o, m, part, r, a.S, a.Sp, a.last, kq, bq, cur, rs, in);
     kq = lane_sum<RB, G::LPR>(kq);
     bq = lane_sum<RB, G::LPR>(bq);
     if (part == 0) {
-        const T cur = a.S[id], prev = a.Sp[id];
-        const T src = T(0.5) * inject_range<T, YT, RB>(a, rs.e0, rs.e1, r);
+        in.sum(rs, [&](int, T w, T v) { inj = mad(w, v, inj); });
+        const T src = T(0.5) * inj;
         a.Sn[id] = a.last ? adj_result(cur, prev, kq, bq, src, m.dm, a.dt)
                           : step_update(cur, prev, kq, bq, src, m.dm, a.dt);
     }
@@ -282,7 +398,7 @@ enum class Var : int { Plain, Stream, Few };
 // boundary chunks fit 96 registers).
 template <typename T, int RB>
 constexpr int vwaves(Var v) {
-    return v == Var::Few ? 1 : RB * sizeof(T) <= 32 ? 2 : 5;
+    return v == Var::Few ? 2 : RB * sizeof(T) <= 32 ? 2 : 5;
 }
 #define PAT_VOCC(T, RB, VAR) __attribute__((amdgpu_waves_per_eu(vwaves<T, RB>(VAR))))
 
@@ -378,13 +494,18 @@ __device__ __forceinline__ VT vfma(T w, VT x, VT acc) {
 // rows.  Slot 0 of every row is its diagonal, so the first gather is the row's own
 // X value; it is returned in `own`.  sp: the row's rspec, its record is returned in rs.
 // LAT (launches with few waves, see few_waves): everything a row needs is in flight at
-// once, all 16 gathers and, as soon as the row's record is there, the boundary gathers,
-// so that a wave waits for three round trips instead of up to seven.
-template <typename T, int RB, bool LAT>
+// once, all 16 gathers and, as soon as the row's record is there, the boundary gathers, the
+// first four entries beyond the slots and the first sensor entry; the next four entries'
+// operands come with each four's gathers.  An 11-entry row waits for five round trips
+// instead of ten.  DIRECT: rs holds the row's record already; the transposed step does
+// not take it (waiting for two tables by row costs as much as the record: 5.18 against 5.36
+// us on 15,625 nodes, 16 float64 RHS).  early: as in row_sums.
+template <typename T, int RB, bool LAT, bool DIRECT, typename Early>
 __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, const T *__restrict__ X,
                                           const T *__restrict__ Y, bool only_prev, typename Vec16<T>::t &acc,
                                           typename Vec16<T>::t &bacc, typename Vec16<T>::t &own,
-                                          const SlotRegs<T, RB, int> &off, const SlotRegs<T, RB, T> &kv, RowSpec &rs) {
+                                          const SlotRegs<T, RB, int> &off, const SlotRegs<T, RB, T> &kv, RowSpec &rs,
+                                          Early &early) {
     using G = VGeo<T, RB>;
     using VT = typename Vec16<T>::t;
     constexpr int CH = kGatherChunk;
@@ -394,10 +515,23 @@ __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, con
     const uint32_t qoff = uint32_t(q) * 16u;
     constexpr uint32_t ROWB = uint32_t(RB * sizeof(T));
     constexpr int YL = LAT ? 12 : 0;  // boundary slots gathered early (more follow below)
+    // entries beyond the padded slots, four at a time, clamped to the row's last
+    int c[4];
+    T w[4], w0[4];
+    VT xv[4];
+    auto fetch = [&](int k) {
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = min(k + j, rs.x1 - 1);
+            c[j] = o.xcol[e];
+            w[j] = o.xval[e];
+        }
+    };
     VT ye[YL + 1], xe[YL + 1];
     SlotRegs<T, RB, T> bv;
     if constexpr (LAT) {
-        if (sp) rs.load(o.spec, sp);
+        if constexpr (!DIRECT)
+            if (sp) rs.load(o.spec, sp);
         VT x[G::W];
         static_for<0, G::W>([&](auto J) {
             x[J.value] = *reinterpret_cast<const VT *>(Xc + (uint32_t(off.template get<J.value>()) + qoff));
@@ -408,9 +542,24 @@ __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, con
                 ye[J.value] = *reinterpret_cast<const VT *>(Yc + (uint32_t(off.template get<J.value>()) + qoff));
             });
         }
+        const bool over = rs.x1 > rs.x0;
+        if (over) fetch(rs.x0);
+        early.first(rs);
+        if (over) {
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                xv[j] = *reinterpret_cast<const VT *>(Xc + (uint32_t(c[j]) * ROWB + qoff));
+                w0[j] = w[j];
+            }
+            fetch(rs.x0 + 4);
+        }
+        early.second(rs);
         own = x[0];
         static_for<0, G::W>([&](auto J) { acc = vfma(kv.template get<J.value>(), x[J.value], acc); });
         static_for<0, YL>([&](auto J) { xe[J.value] = x[J.value]; });
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+            if (rs.x0 + j < rs.x1) acc = vfma(w0[j], xv[j], acc);
     } else
     static_for<0, G::W, CH>([&](auto J0) {
         constexpr int j0 = decltype(J0)::value;
@@ -430,21 +579,17 @@ __device__ __forceinline__ void vrow_sums(const RowOps<T> &o, int q, int sp, con
     });
     pin(acc);  // the sums end here: moved further down, they would keep the gathers live
     if (!sp) return;
-    for (int k = rs.x0; k < rs.x1; k += 4) {  // four entries at a time, clamped to the row's last
-        int c[4];
-        T w[4];
-        VT xv[4];
+    for (int k = rs.x0 + (LAT ? 4 : 0); k < rs.x1; k += 4) {
+        if constexpr (!LAT) fetch(k);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            const int e = min(k + j, rs.x1 - 1);
-            c[j] = o.xcol[e];
-            w[j] = o.xval[e];
+            xv[j] = *reinterpret_cast<const VT *>(Xc + (uint32_t(c[j]) * ROWB + qoff));
+            w0[j] = w[j];
         }
-#pragma unroll
-        for (int j = 0; j < 4; ++j) xv[j] = *reinterpret_cast<const VT *>(Xc + (uint32_t(c[j]) * ROWB + qoff));
+        if constexpr (LAT) fetch(k + 4);  // the next four's operands with this four's gathers
 #pragma unroll
         for (int j = 0; j < 4; ++j)
-            if (k + j < rs.x1) acc = vfma(w[j], xv[j], acc);
+            if (k + j < rs.x1) acc = vfma(w0[j], xv[j], acc);
     }
     if (rs.nb) {
         // only the row's first bnum slots carry B; the neighbours' X values are read again
@@ -550,12 +695,19 @@ __device__ __forceinline__ void fwd_tile(const VFwdArgs<T> &a, int tile) {
         SlotRegs<T, RB, int> off;
         SlotRegs<T, RB, T> kv;
         load_slots<T, RB>(a.o, row, q, off, kv);
-        const int sp = a.o.rspec[row];
+        RowSpec rs;
+        int sp;
+        if constexpr (VAR == Var::Few) {
+            rs.load_direct(a.o.rdir, row);
+            sp = rs.any();
+        } else {
+            sp = a.o.rspec[row];
+        }
         const T dm = a.o.dtm[row];
         const VT prev = vload_own<VAR == Var::Stream, VT>(a.Sp + id);
         VT acc = {}, bacc = {}, cur;
-        RowSpec rs;
-        vrow_sums<T, RB, VAR == Var::Few>(a.o, q, sp, a.S, a.Sp, false, acc, bacc, cur, off, kv, rs);
+        NothingEarly none;
+        vrow_sums<T, RB, VAR == Var::Few, VAR == Var::Few>(a.o, q, sp, a.S, a.Sp, false, acc, bacc, cur, off, kv, rs, none);
         VT sn;
 #pragma unroll
         for (int i = 0; i < G::VEC; ++i) sn[i] = step_update(cur[i], prev[i], acc[i], bacc[i], T(0), dm, a.dt);
@@ -593,7 +745,7 @@ __global__ void __launch_bounds__(256) PAT_VOCC(T, RB, VAR) k_fwd_vm(const Multi
 template <typename T>
 struct VAdjArgs {
     RowOps<T> o;
-    const int32_t *injptr, *injs;
+    const int32_t *injs;
     const T *injw;
     const T *S, *Sp;  // q_k, q_{k-1}
     T *Sn;            // q_{k+1}, or the result after the last step
@@ -604,27 +756,6 @@ struct VAdjArgs {
     int stream;  // state beyond the Infinity Cache: launch the non-temporal variant
     T dt;
 };
-
-// Pi^T (yhat^{ta} + yhat^{tb}) over the injection entries [e0, e1) of a row, for
-// the VEC right-hand sides from rhs0 (yhat^{ta} left out for ta < 0).
-template <typename T, typename YT, int RB, typename VT>
-__device__ __forceinline__ VT vinject(const VAdjArgs<T> &a, int e0, int e1, int rhs0) {
-    VT inj = {};
-    const YT *yh = static_cast<const YT *>(a.yh);
-    for (int e = e0; e < e1; ++e) {
-        const int s = a.injs[e];
-        const int64_t sb = (int64_t(a.tb) * a.n_obs + s) * RB + rhs0;
-        const int64_t sa = (int64_t(a.ta) * a.n_obs + s) * RB + rhs0;
-        const T w = a.injw[e];
-#pragma unroll
-        for (int i = 0; i < Vec16<T>::n; ++i) {
-            T v = static_cast<T>(static_cast<double>(yh[sb + i]) * a.yscale);
-            if (a.ta >= 0) v = static_cast<T>(static_cast<double>(yh[sa + i]) * a.yscale) + v;
-            inj[i] = mad(w, v, inj[i]);
-        }
-    }
-    return inj;
-}
 
 // Transposed step (same update as k_adj) with vector lanes on logical tile `tile`;
 // LAST: the closing launch.
@@ -637,6 +768,7 @@ __device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile) {
     const int row = tile * G::RPB + wave * G::RPW + lane / G::LPR;
     if (row >= a.n) return;
     const int64_t id = int64_t(row) * RB + q * G::VEC;
+    RowSpec rs;
     const int sp = a.o.rspec[row];
     SlotRegs<T, RB, int> off;
     SlotRegs<T, RB, T> kv;
@@ -644,9 +776,9 @@ __device__ __forceinline__ void adj_tile(const VAdjArgs<T> &a, int tile) {
     const T dm = a.o.dtm[row];
     const VT prev = vload_own<VAR == Var::Stream, VT>(a.Sp + id);
     VT kq = {}, bq = {}, cur, inj = {};
-    RowSpec rs;
-    vrow_sums<T, RB, VAR == Var::Few>(a.o, q, sp, a.S, a.Sp, LAST, kq, bq, cur, off, kv, rs);
-    if (rs.e1 > rs.e0) inj = vinject<T, YT, RB, VT>(a, rs.e0, rs.e1, q * G::VEC);
+    Inject<T, YT, RB, G::VEC, VAdjArgs<T>> in{a, q * G::VEC, true};
+    vrow_sums<T, RB, VAR == Var::Few, false>(a.o, q, sp, a.S, a.Sp, LAST, kq, bq, cur, off, kv, rs, in);
+    in.sum(rs, [&](int i, T w, T v) { inj[i] = mad(w, v, inj[i]); });
     VT out;
 #pragma unroll
     for (int i = 0; i < G::VEC; ++i) {
@@ -1401,12 +1533,12 @@ RowOps<T> row_ops(const DevOps &op);
 template <>
 RowOps<double> row_ops<double>(const DevOps &op) {
     return RowOps<double>{op.ell_col, op.xcol, op.ell_val64, op.xval64, op.bslot64, op.dtm64, op.rspec,
-                          op.spec};
+                          op.spec, op.rdir};
 }
 template <>
 RowOps<float> row_ops<float>(const DevOps &op) {
     return RowOps<float>{op.ell_col, op.xcol, op.ell_val32, op.xval32, op.bslot32, op.dtm32, op.rspec,
-                          op.spec};
+                          op.spec, op.rdir};
 }
 template <typename T>
 const T *sw_of(const DevOps &op);
@@ -1444,11 +1576,13 @@ VFwdArgs<T> fwd_args_v(const DevOps &op, const void *S, const void *Sp, void *Sn
     return a;
 }
 
-// Launches of at most 512 workgroups, two waves per SIMD, take the variant with everything
-// in flight and up to 200 registers: it saves round trips (15,625 nodes, 8 float32 RHS 4.5 /
-// 4.9 -> 4.0 / 4.6 us per forward / transposed step, 4,913 nodes, 16 RHS 4.9 -> 4.6), and
-// loses once a launch has the waves to hide them (64,000 nodes, 16 RHS 7.0 -> 7.8).
-inline bool few_waves(int workgroups) { return workgroups <= 512; }
+// Launches of at most kFewGroups = 512 workgroups, two waves per SIMD, take the variants with
+// everything in flight (up to 200 registers) and the records by row: the wave with the
+// longest chain of round trips is what such a launch takes.  15,625 nodes, per forward /
+// transposed step: 1 float32 RHS 2.87 / 3.07 -> 2.58 / 2.86 us, 4 RHS 4.6 / 5.0 -> 4.0 /
+// 4.2, 16 RHS 4.0 / 4.5 -> 3.7 / 4.2; 4,913 nodes, 16 RHS 4.9 / 4.9 -> 4.2 / 4.2.  With the
+// waves to hide the round trips the registers cost more (64,000 nodes, 16 RHS 7.0 -> 7.8).
+static inline bool few_waves(const DevOps &op, int workgroups) { return op.rdir && workgroups <= kFewGroups; }
 
 template <typename T, typename OT, int RB>
 void fwd_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool rows, bool sample, int t, void *y,
@@ -1457,7 +1591,7 @@ void fwd_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool 
     const VFwdArgs<T> a = fwd_args_v<T, RB>(op, S, Sp, Sn, rows, sample, t, y, yscale, &grid);
     if (grid <= 0) return;
     const dim3 g(grid), b(256);
-    if (few_waves(grid)) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Few>), g, b, 0, s, a);
+    if (few_waves(op, grid)) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Few>), g, b, 0, s, a);
     else if (a.stream) hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Stream>), g, b, 0, s, a);
     else hipLaunchKernelGGL((k_fwd_v<T, OT, RB, Var::Plain>), g, b, 0, s, a);
 }
@@ -1484,7 +1618,7 @@ VAdjArgs<T> adj_args_v(const DevOps &op, const void *S, const void *Sp, void *Sn
     using G = VGeo<T, RB>;
     VAdjArgs<T> a;
     a.o = row_ops<T>(op);
-    a.injptr = op.injptr; a.injs = op.injs;
+    a.injs = op.injs;
     a.injw = injw_of<T>(op);
     a.S = static_cast<const T *>(S); a.Sp = static_cast<const T *>(Sp); a.Sn = static_cast<T *>(Sn);
     a.yh = yh; a.yscale = yscale;
@@ -1502,7 +1636,7 @@ void adj_impl_v(const DevOps &op, const void *S, const void *Sp, void *Sn, bool 
     const VAdjArgs<T> a = adj_args_v<T, RB>(op, S, Sp, Sn, last, tb, yh, yscale);
     const dim3 g(a.n_tiles), b(256);
     if (last) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Plain, true>), g, b, 0, s, a);
-    else if (few_waves(a.n_tiles)) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Few, false>), g, b, 0, s, a);
+    else if (few_waves(op, a.n_tiles)) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Few, false>), g, b, 0, s, a);
     else if (a.stream) hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Stream, false>), g, b, 0, s, a);
     else hipLaunchKernelGGL((k_adj_v<T, YT, RB, Var::Plain, false>), g, b, 0, s, a);
 }
@@ -1546,7 +1680,9 @@ void fwd_impl(const DevOps &op, const void *S, const void *Sp, void *Sn, bool ro
         a.dt = T(op.dt);
         a.n_samp = sample ? int((int64_t(op.n_obs) * RB + 255) / 256) : 0;
         const int grid = a.n_tiles + a.n_samp;
-        if (grid > 0) hipLaunchKernelGGL((k_fwd<T, OT, RB>), dim3(grid), dim3(256), 0, s, a);
+        if (grid <= 0) return;
+        if (few_waves(op, grid)) hipLaunchKernelGGL((k_fwd<T, OT, RB, true>), dim3(grid), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_fwd<T, OT, RB, false>), dim3(grid), dim3(256), 0, s, a);
     }
 }
 
@@ -1573,7 +1709,8 @@ void adj_impl(const DevOps &op, const void *S, const void *Sp, void *Sn, bool la
         if constexpr (RB * sizeof(T) <= 1024) adj_impl_v<T, YT, RB>(op, S, Sp, Sn, last, tb, yh, yscale, s);
     } else {
         const AdjArgs<T> a = adj_args<T, YT, RB>(op, S, Sp, Sn, last, last ? -1 : tb + 1, tb, yh, yscale);
-        hipLaunchKernelGGL((k_adj<T, YT, RB>), dim3(a.n_tiles), dim3(256), 0, s, a);
+        if (few_waves(op, a.n_tiles)) hipLaunchKernelGGL((k_adj<T, YT, RB, true>), dim3(a.n_tiles), dim3(256), 0, s, a);
+        else hipLaunchKernelGGL((k_adj<T, YT, RB, false>), dim3(a.n_tiles), dim3(256), 0, s, a);
     }
 }
 

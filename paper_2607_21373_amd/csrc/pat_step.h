@@ -45,6 +45,17 @@ struct RowSpec {
         bo = u.x; nb = u.y; x0 = u.z; x1 = u.w;
         e0 = v.x; e1 = v.y;
     }
+    // from the table by row; the sensor weights' range is not in it
+    __device__ __forceinline__ void load_direct(const int4 *rdir, int row) {
+        const int4 u = rdir[row];
+        bo = u.x; nb = u.y; x0 = u.z; x1 = u.w;
+    }
+    __device__ __forceinline__ void load_inject(const int32_t *injptr, int row) {
+        int32_t e[2];  // one 8-byte load
+        __builtin_memcpy(e, injptr + row, sizeof(e));
+        e0 = e[0]; e1 = e[1];
+    }
+    __device__ __forceinline__ bool any() const { return nb || x1 > x0 || e1 > e0; }
 };
 
 // the four values of one quad
