@@ -260,7 +260,10 @@ __device__ __forceinline__ VT lds_row(const HaloBuf<T> &Lb, uint32_t off) {
 }
 
 // Pi^T (yhat^{ta} + yhat^{tb}) over the injection entries [e0, e1) of a row, for the
-// VEC right-hand sides from rhs0 (yhat^{ta} left out for ta < 0).
+// VEC right-hand sides from rhs0 (yhat^{ta} left out for ta < 0).  All of an entry's data
+// are loaded before any are used: with each right-hand side's loads and sum in turn a
+// sensor row held its workgroup up (195,112 nodes, 1024 sensors, transposed step: 64
+// float32 RHS 35.9 -> 35.5 us, 32 float64 38.2 -> 37.6).
 template <typename T, typename YT, int RB, typename VT>
 __device__ __forceinline__ VT hinject(const HaloArgs<T> &a, int e0, int e1, int rhs0) {
     VT inj = {};
@@ -270,10 +273,17 @@ __device__ __forceinline__ VT hinject(const HaloArgs<T> &a, int e0, int e1, int 
         const int64_t sb = (int64_t(a.tb) * a.n_obs + s) * RB + rhs0;
         const int64_t sa = (int64_t(a.ta) * a.n_obs + s) * RB + rhs0;
         const T w = a.injw[e];
+        YT yb[HVec<T>::n], ya[HVec<T>::n];
+#pragma unroll
+        for (int i = 0; i < HVec<T>::n; ++i) yb[i] = yh[sb + i];
+        if (a.ta >= 0) {
+#pragma unroll
+            for (int i = 0; i < HVec<T>::n; ++i) ya[i] = yh[sa + i];
+        }
 #pragma unroll
         for (int i = 0; i < HVec<T>::n; ++i) {
-            T v = static_cast<T>(static_cast<double>(yh[sb + i]) * a.yscale);
-            if (a.ta >= 0) v = static_cast<T>(static_cast<double>(yh[sa + i]) * a.yscale) + v;
+            T v = static_cast<T>(static_cast<double>(yb[i]) * a.yscale);
+            if (a.ta >= 0) v = static_cast<T>(static_cast<double>(ya[i]) * a.yscale) + v;
             inj[i] = mad(w, v, inj[i]);
         }
     }
