@@ -57,7 +57,7 @@ def kernel_source_sha():
     """Hash of what decides the step kernels' memory traffic: their code, their work mappings and
     the host setup that lays out and orders the rows (comments and layout whitespace left out)."""
     h = hashlib.sha256()
-    for name in ("pat_kernels.hip", "pat_tiles.h", "pat_setup.cpp"):
+    for name in ("pat_kernels.hip", "pat_halo.hip", "pat_step.h", "pat_tiles.h", "pat_setup.cpp"):
         with open(os.path.join(ROOT, "paper_2607_21373_amd", "csrc", name)) as f:
             src = f.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -245,8 +245,8 @@ def big_leg(pat, W, dev, n_iter):
 def roofline_record(fwd_s, adj_s, fb, ab, survey_bytes, sweep_share, wname, RB):
     """Roofline of the two step kernels, which share the sweep time almost equally: the one with the
     longer average launch leads the record, the other follows with its own fraction of the HBM peak."""
-    # float32 blocks of 64, 128 or 256 RHS run the halo-tile step kernels, narrower ones the vector-lane ones
-    fk, ak = (f"k_fwd_h<double,{RB}>", f"k_adj_h<double,{RB}>") if RB >= 64 else \
+    # float32 blocks of 64, 128 or 256 RHS run the halo-tile step kernel, narrower ones the vector-lane ones
+    fk, ak = (f"k_halo<float,double,true,false,{RB}>", f"k_halo<float,double,false,false,{RB}>") if RB >= 64 else \
         (f"k_fwd_v<float,double,{RB}>", f"k_adj_v<float,double,{RB}>")
     kern = {"fwd": (f"{fk} (forward leapfrog step)", fwd_s, fb, f"k_fwd_f32_rb{RB}"),
             "adj": (f"{ak} (transpose leapfrog step)", adj_s, ab, f"k_adj_f32_rb{RB}")}

@@ -235,6 +235,7 @@ pat_status pat_spectral_apply(pat_problem *p, int64_t R, int transpose, const do
  *   rhs_block  host int32 or NULL: the chosen block
  *   step_us    host double or NULL: its priced cost of one forward plus one
  *              transpose step for all S samples, in microseconds
+ * A mesh of up to 2,048 nodes whose sweeps run as one launch each is timed by whole sweeps.
  * Synchronises `stream`.  The sweep workspaces it allocates for candidate blocks
  * other than the chosen one are freed again (those that existed before are kept,
  * with their contents overwritten). */
