@@ -256,15 +256,17 @@ pat_status pat_batch_destroy(pat_batch *b);
 /* pat_autotune for the batch (S = the largest per-problem sample count).  For each
  * candidate block it also times, per direction (forward, transpose), the three
  * launch modes of pat_batch_merge and keeps the fastest; rto_sample_batch uses
- * these choices when rhs_block is 0 or equals the tuned block (otherwise it merges). */
+ * these choices when rhs_block is 0 or equals the tuned block (otherwise as when not tuned). */
 pat_status pat_batch_autotune(pat_batch *b, int64_t S, pat_precision prec, int32_t *rhs_block, double *step_us,
                               void *stream);
 
 /* Launch mode of rto_sample_batch per sweep direction: 1 = one merged launch per
  * time step for all problems; 0 = one launch per problem within each time step;
  * 2 = each problem's whole sweep in turn (keeps a small mesh's working set in
- * cache across its steps); -1 = the autotuned choice (merged when not tuned).
- * Results do not depend on it. */
+ * cache across its steps; sweeps of meshes of up to 2,048 nodes run in one launch
+ * in this mode only); -1 = the autotuned choice (when not tuned: merged, or 2 for a batch
+ * with such meshes in which all are that small, the block is too narrow to merge or a larger mesh
+ * has halo tiles for it).  Results do not depend on it. */
 pat_status pat_batch_merge(pat_batch *b, int32_t forward, int32_t transpose);
 
 /* rto_sample for every problem m of the batch at once: arrays of n entries

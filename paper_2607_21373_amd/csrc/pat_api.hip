@@ -492,37 +492,11 @@ void adj_steps(pat::Prec prec, int RB, bool y_f64, const std::vector<pat::AdjSte
         pat::launch_adj_step(prec, RB, *a.op, a.S, a.Sp, a.Sn, a.last, a.tb, a.yh, y_f64, a.yscale, s);
 }
 
-// Meshes whose sweeps run in one launch each take no part in the shared steps.  Runs
-// `whole` for those and returns the others' indices.
-template <class F>
-std::vector<size_t> split_small(const std::vector<pat_problem *> &P, pat::Prec prec, F &&whole) {
-    std::vector<size_t> rest;
-    for (size_t m = 0; m < P.size(); ++m)
-        if (pat::small_sweep_supported(prec, P[m]->ops)) whole(m);
-        else rest.push_back(m);
-    return rest;
-}
-template <typename V>
-V pick(const V &v, const std::vector<size_t> &at) {
-    V o;
-    for (size_t m : at) o.push_back(v[m]);
-    return o;
-}
-
 // enqueue_forward for several meshes with equal N_T: the same launches, merged per step.
-void enqueue_forward_multi(const std::vector<pat_problem *> &Pall, const std::vector<SweepWS *> &Wall,
-                           const std::vector<void *> &yall, bool y_f64, const std::vector<double> &scall,
+void enqueue_forward_multi(const std::vector<pat_problem *> &P, const std::vector<SweepWS *> &W,
+                           const std::vector<void *> &yout, bool y_f64, const std::vector<double> &scale,
                            hipStream_t s, bool merge) {
-    const std::vector<size_t> rest = split_small(Pall, Wall[0]->prec, [&](size_t m) {
-        enqueue_forward(Pall[m], *Wall[m], yall[m], y_f64, scall[m], s);
-    });
-    if (rest.empty()) return;
-    const auto P = pick(Pall, rest);
-    const auto W = pick(Wall, rest);
-    const auto yout = pick(yall, rest);
-    const auto scale = pick(scall, rest);
     const size_t n = P.size();
-    merge = merge && n > 1;
     const int NT = P[0]->ops.n_steps;
     const pat::Prec prec = W[0]->prec;
     const int RB = W[0]->RB;
@@ -540,17 +514,9 @@ void enqueue_forward_multi(const std::vector<pat_problem *> &Pall, const std::ve
 }
 
 // enqueue_adjoint for several meshes with equal N_T.
-void enqueue_adjoint_multi(const std::vector<pat_problem *> &Pall, const std::vector<SweepWS *> &Wall,
-                           const std::vector<const void *> &yall, bool y_f64, hipStream_t s, bool merge) {
-    const std::vector<size_t> rest = split_small(Pall, Wall[0]->prec, [&](size_t m) {
-        enqueue_adjoint(Pall[m], *Wall[m], yall[m], y_f64, s);
-    });
-    if (rest.empty()) return;
-    const auto P = pick(Pall, rest);
-    const auto W = pick(Wall, rest);
-    const auto yin = pick(yall, rest);
+void enqueue_adjoint_multi(const std::vector<pat_problem *> &P, const std::vector<SweepWS *> &W,
+                           const std::vector<const void *> &yin, bool y_f64, hipStream_t s, bool merge) {
     const size_t n = P.size();
-    merge = merge && n > 1;
     const int NT = P[0]->ops.n_steps;
     const pat::Prec prec = W[0]->prec;
     const int RB = W[0]->RB;
@@ -570,16 +536,17 @@ void enqueue_adjoint_multi(const std::vector<pat_problem *> &Pall, const std::ve
 // Autotuner: for each candidate RHS block, time `reps` forward and transpose
 // steps of all meshes (after a warm-up) with HIP events and price a run of S
 // samples as ceil(S/RB) * (forward + transpose step); return the cheapest.  With
-// several meshes each direction is timed merged (one launch per step) and one
-// launch per mesh, and the faster is kept (*mf, *ma).  Small meshes, whose sweeps
-// are one launch each, are timed by whole sweeps and take no part in that choice.
-pat_status tune_rb(const std::vector<pat_problem *> &Pall, hipStream_t cap, int64_t S, pat::Prec pr, hipStream_t s,
+// several meshes each direction is timed merged (one launch per step), with one
+// launch per mesh within each step and with each mesh's whole sweep in turn, and the
+// fastest is kept (*mf, *ma).  Alone, a mesh whose sweep is one launch is timed by
+// whole sweeps.
+pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t S, pat::Prec pr, hipStream_t s,
                    int *best, double *best_us, int *mf = nullptr, int *ma = nullptr) {
     // candidates: up to the smallest block holding all S samples (beyond 64 only when S needs it)
     int top = 1;
     while (top < S && top < pat::max_rhs_block(pr)) top <<= 1;
     int64_t nmax = 0;
-    for (const pat_problem *q : Pall) nmax = std::max<int64_t>(nmax, q->ops.n);
+    for (const pat_problem *q : P) nmax = std::max<int64_t>(nmax, q->ops.n);
     top = fit_rb(nmax, pr, top);
     const int lo = std::max(1, std::min(top, 64) / 16);
     const int reps = 8;
@@ -596,25 +563,20 @@ pat_status tune_rb(const std::vector<pat_problem *> &Pall, hipStream_t cap, int6
     if (ma) *ma = 1;
     pat_status st = PAT_OK;
     for (int RB = lo; RB <= top && st == PAT_OK; RB <<= 1) {
-        std::vector<SweepWS *> Wall(Pall.size());
-        for (size_t m = 0; m < Pall.size() && st == PAT_OK; ++m) {
-            st = get_sweep(Pall[m], pr, RB, true, &Wall[m]);
+        std::vector<SweepWS *> W(P.size());
+        for (size_t m = 0; m < P.size() && st == PAT_OK; ++m) {
+            st = get_sweep(P[m], pr, RB, true, &W[m]);
             if (st != PAT_OK) break;
-            const size_t nb = size_t(Pall[m]->ops.n) * RB * tsize(pr);
-            const size_t yb = size_t(Pall[m]->ops.n_steps) * Pall[m]->ops.n_obs * RB * tsize(pr);
+            const size_t nb = size_t(P[m]->ops.n) * RB * tsize(pr);
+            const size_t yb = size_t(P[m]->ops.n_steps) * P[m]->ops.n_obs * RB * tsize(pr);
             for (int k = 0; k < 3; ++k) {
-                if (hipMemsetAsync(Wall[m]->S[k], 0, nb, s) != hipSuccess)
+                if (hipMemsetAsync(W[m]->S[k], 0, nb, s) != hipSuccess)
                     st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
             }
-            if (hipMemsetAsync(Wall[m]->Y, 0, yb, s) != hipSuccess)
-                st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
+            if (hipMemsetAsync(W[m]->Y, 0, yb, s) != hipSuccess) st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
         }
         if (st != PAT_OK) break;
         const bool yf = pr == pat::Prec::F64;
-        std::vector<size_t> small;
-        const std::vector<size_t> rest = split_small(Pall, pr, [&](size_t m) { small.push_back(m); });
-        const auto P = pick(Pall, rest);
-        const auto W = pick(Wall, rest);
         std::vector<pat::FwdStep> fs(P.size());
         std::vector<pat::AdjStep> as(P.size());
         for (size_t m = 0; m < P.size(); ++m) {
@@ -623,59 +585,53 @@ pat_status tune_rb(const std::vector<pat_problem *> &Pall, hipStream_t cap, int6
             as[m] = pat::AdjStep{&P[m]->ops, W[m]->S[0], W[m]->S[1], W[m]->S[2], P[m]->ops.n_steps < 2, 0, W[m]->Y,
                                  1.0};
         }
-        // milliseconds of one replay of a captured graph, after a warm-up
-        auto timed = [&](hipGraphExec_t x, float *out) {
-            (void)hipGraphLaunch(x, s);
-            (void)hipEventRecord(ev[0], s);
-            (void)hipGraphLaunch(x, s);
-            (void)hipEventRecord(ev[1], s);
-            if (hipEventSynchronize(ev[1]) != hipSuccess) return fail(PAT_ERR_HIP, "autotune: a timed step failed");
-            (void)hipEventElapsedTime(out, ev[0], ev[1]);
-            return PAT_OK;
-        };
-        double small_ms = 0.0;  // of `reps` forward and transpose steps of the small meshes
-        for (size_t m : small)
-            for (int q = 0; q < 2 && st == PAT_OK; ++q) {
-                hipGraphExec_t x = nullptr;
-                float ms = 0.f;
-                st = capture_on(cap, &x, [&](hipStream_t cs) {
-                    if (q == 0) enqueue_forward(Pall[m], *Wall[m], Wall[m]->Y, yf, 1.0, cs);
-                    else enqueue_adjoint(Pall[m], *Wall[m], Wall[m]->Y, yf, cs);
-                });
-                if (st == PAT_OK) st = timed(x, &ms);
-                if (x) (void)hipGraphExecDestroy(x);
-                small_ms += double(ms) * reps / Pall[m]->ops.n_steps;
-            }
-        if (st != PAT_OK) break;
-        // The sweeps replay captured graphs, so time captured sequences of `reps` steps
-        // (sequence q: direction q % 2).  Several meshes: q = 0, 1 merged launches per
-        // step; q = 2, 3 one launch per mesh within each step; then one graph per mesh
-        // and direction (that mesh alone, as a whole sweep per mesh runs it).
+        // The sweeps replay captured graphs, so time captured sequences of `reps` steps, or
+        // one whole sweep where that is one launch (sequence q: direction q % 2).  Several
+        // meshes: q = 0, 1 merged launches per step; q = 2, 3 one launch per mesh within each
+        // step; then one graph per mesh and direction (that mesh alone, as a whole sweep per
+        // mesh runs it).
         const size_t nm = P.size();
         const bool multi = nm > 1;
-        const int nq = multi ? 4 + 2 * int(nm) : 2 * int(nm);
+        const int nq = multi ? 4 + 2 * int(nm) : 2;
+        const int q1 = multi ? 4 : 0;  // the first sequence of one mesh alone
+        auto whole = [&](int q) {
+            return q >= q1 && pat::small_sweep_supported(pr, P[size_t(q - q1) / 2]->ops);
+        };
         std::vector<hipGraphExec_t> g(size_t(nq), nullptr);
         for (int q = 0; q < nq && st == PAT_OK; ++q)
             st = capture_on(cap, &g[size_t(q)], [&](hipStream_t cs) {
+                const size_t m = q < q1 ? 0 : size_t(q - q1) / 2;
+                if (whole(q)) {
+                    if (q % 2 == 0) enqueue_forward(P[m], *W[m], W[m]->Y, yf, 1.0, cs);
+                    else enqueue_adjoint(P[m], *W[m], W[m]->Y, yf, cs);
+                    return;
+                }
                 for (int k = 0; k < reps; ++k) {
-                    if (q < 4) {
-                        if (q % 2 == 0) fwd_steps(pr, RB, yf, fs, cs, multi && q < 2);
-                        else adj_steps(pr, RB, yf, as, cs, multi && q < 2);
+                    if (q < q1) {
+                        if (q % 2 == 0) fwd_steps(pr, RB, yf, fs, cs, q < 2);
+                        else adj_steps(pr, RB, yf, as, cs, q < 2);
                     } else {
-                        const size_t m = size_t(q - 4) / 2;
                         if (q % 2 == 0) fwd_steps(pr, RB, yf, {fs[m]}, cs, false);
                         else adj_steps(pr, RB, yf, {as[m]}, cs, false);
                     }
                 }
             });
-        std::vector<float> ms(size_t(nq), 0.f);
+        std::vector<float> ms(size_t(nq), 0.f);  // per sequence of `reps` steps
         if (st == PAT_OK) {
-            for (int q = 0; q < nq && st == PAT_OK; ++q) st = timed(g[size_t(q)], &ms[size_t(q)]);
+            for (int q = 0; q < nq && st == PAT_OK; ++q) {
+                (void)hipGraphLaunch(g[size_t(q)], s);  // warm-up
+                (void)hipEventRecord(ev[0], s);
+                (void)hipGraphLaunch(g[size_t(q)], s);
+                (void)hipEventRecord(ev[1], s);
+                if (hipEventSynchronize(ev[1]) != hipSuccess) st = fail(PAT_ERR_HIP, "autotune: a timed step failed");
+                else (void)hipEventElapsedTime(&ms[size_t(q)], ev[0], ev[1]);
+                if (whole(q)) ms[size_t(q)] *= float(reps) / float(P[size_t(q - q1) / 2]->ops.n_steps);
+            }
         }
         for (auto &x : g)
             if (x) (void)hipGraphExecDestroy(x);
         if (st != PAT_OK) break;
-        float f_ms = nm ? ms[0] : 0.f, a_ms = nm ? ms[1] : 0.f;
+        float f_ms = ms[0], a_ms = ms[1];
         int m_f = 1, m_a = 1;
         if (multi) {
             const bool merged_ok = pat::multi_step_supported(pr, RB);
@@ -689,7 +645,7 @@ pat_status tune_rb(const std::vector<pat_problem *> &Pall, hipStream_t cap, int6
             if (sf < f_ms) { f_ms = sf; m_f = 2; }
             if (sa < a_ms) { a_ms = sa; m_a = 2; }
         }
-        const double us = double((S + RB - 1) / RB) * 1e3 * (double(f_ms + a_ms) + small_ms) / reps;
+        const double us = double((S + RB - 1) / RB) * 1e3 * double(f_ms + a_ms) / reps;
         if (us < *best_us) {
             *best_us = us;
             *best = RB;
@@ -700,6 +656,23 @@ pat_status tune_rb(const std::vector<pat_problem *> &Pall, hipStream_t cap, int6
     for (auto &e : ev) (void)hipEventDestroy(e);
     if (st == PAT_OK && hipGetLastError() != hipSuccess) st = fail(PAT_ERR_HIP, "autotune: launch failed");
     return st;
+}
+
+// Launch mode of a batch that was not tuned.  Merged, but each mesh's sweep in turn where that
+// runs some of them in one launch and the rest lose nothing: all meshes are that small, or a
+// block is too narrow to merge, or a larger mesh has halo tiles, which a merged launch does
+// not use.  Per forward and transposed step with the solver's share, merged against in turn:
+// 729 + 864 + 1,331 + 2,028 nodes, 16 float32 RHS 13.6 / 10.3 us; 729 + 864 + 4,913, two 18.9 /
+// 10.6; 2,028 + 195,112, 64 float32 82.5 / 72.4.  Elsewhere the small meshes' tiles ride along: 729 +
+// 2,028 + 1,980 + 195,112 nodes, 16 float32 RHS 33.1 / 40.4, 16 float64 52.5 / 72.3.
+int batch_mode(const std::vector<pat_problem *> &P, pat::Prec pr, int RB) {
+    size_t small = 0;
+    bool halo = false;
+    for (const pat_problem *p : P) {
+        if (pat::small_sweep_supported(pr, p->ops)) ++small;
+        else halo = halo || pat::halo_step_supported(pr, RB, p->ops);
+    }
+    return small && (small == P.size() || halo || !pat::multi_step_supported(pr, RB)) ? 2 : 1;
 }
 
 // One RHS block's least-squares solve, split into the phases between sweeps so
@@ -1526,13 +1499,15 @@ pat_status rto_sample_batch(pat_batch *b, const double *const *y_obs, const pat_
     int64_t nmax = 0;
     for (size_t m = 0; m < n; ++m) nmax = std::max<int64_t>(nmax, b->probs[m]->ops.n);
     int RB = prm[0].rhs_block ? prm[0].rhs_block : fit_rb(nmax, pr, choose_rb(smax));
-    int mf = 1, ma = 1;
+    int mf, ma;
     {
         auto it = b->tune.find({smax, int(pr)});
         if (it != b->tune.end() && (prm[0].rhs_block == 0 || prm[0].rhs_block == it->second.rb)) {
             RB = it->second.rb;
             mf = it->second.mf;
             ma = it->second.ma;
+        } else {
+            mf = ma = batch_mode(b->probs, pr, RB);
         }
         if (b->force_mf >= 0) mf = b->force_mf;
         if (b->force_ma >= 0) ma = b->force_ma;
