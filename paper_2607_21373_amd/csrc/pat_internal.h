@@ -38,7 +38,8 @@ struct HostProblem {
     // Padded row layout of K used by the time-step kernels: entry j < kEll of row i
     // at i*kEll + j (padding: column i, value 0); entries beyond kEll of a long row
     // in a small CSR (xptr, xcol, xval).  Boundary rows keep their B values per
-    // slot: B(i, slot) = bslot[bsoff[i] + slot], slot < kEll + (xptr[i+1]-xptr[i]).
+    // slot: B(i, slot) = bslot[bsoff[i] + slot], slot < kEll + (xptr[i+1]-xptr[i]); bsoff[i] is
+    // a multiple of four.
     static constexpr int kEll = 16;
     std::vector<int32_t> ell_col, xptr, xcol, bsoff;
     std::vector<double> ell_val, xval, bslot;

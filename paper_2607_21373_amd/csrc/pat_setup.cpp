@@ -513,7 +513,8 @@ void build_padded_rows(HostProblem &hp) {
     for (int32_t i = 0; i < N; ++i)
         if (hp.boff[i] >= 0) {
             hp.bsoff[i] = int32_t(boff);
-            boff += W + (hp.xptr[i + 1] - hp.xptr[i]);
+            // a multiple of four: the kernels load a row's values four at a time
+            boff += W + (hp.xptr[i + 1] - hp.xptr[i] + 3) / 4 * 4;
         }
     hp.bslot.assign(size_t(boff), 0.0);
     hp.bnum.assign(size_t(N), 0);
