@@ -57,7 +57,7 @@ def kernel_source_sha():
     """Hash of what decides the step kernels' memory traffic: their code, their work mappings and
     the host setup that lays out and orders the rows (comments and layout whitespace left out)."""
     h = hashlib.sha256()
-    for name in ("pat_kernels.hip", "pat_halo.hip", "pat_step.h", "pat_tiles.h", "pat_setup.cpp"):
+    for name in ("pat_kernels.hip", "pat_halo.hip", "pat_step.h", "pat_tiles.h", "pat_setup.cpp", "pat_internal.h"):
         with open(os.path.join(ROOT, "paper_2607_21373_amd", "csrc", name)) as f:
             src = f.read()
         src = re.sub(r"/\*.*?\*/", " ", src, flags=re.S)
@@ -242,12 +242,15 @@ def big_leg(pat, W, dev, n_iter):
     return res
 
 
-def roofline_record(fwd_s, adj_s, fb, ab, survey_bytes, sweep_share, wname, RB):
+def roofline_record(fwd_s, adj_s, fb, ab, survey_bytes, sweep_share, wname, n_nodes, RB):
     """Roofline of the two step kernels, which share the sweep time almost equally: the one with the
     longer average launch leads the record, the other follows with its own fraction of the HBM peak."""
-    # float32 blocks of 64, 128 or 256 RHS run the halo-tile step kernel, narrower ones the vector-lane ones
-    fk, ak = (f"k_halo<float,double,true,false,{RB}>", f"k_halo<float,double,false,false,{RB}>") if RB >= 64 else \
-        (f"k_fwd_v<float,double,{RB}>", f"k_adj_v<float,double,{RB}>")
+    # float32 blocks of 64, 128 or 256 RHS run the halo-tile step kernel, narrower ones the vector-lane ones;
+    # the last argument: non-temporal own rows for states beyond the 256 MiB cache
+    stream = 3 * n_nodes * RB * 4 > 256 << 20
+    nt = "true" if stream else "false"
+    fk, ak = (f"k_halo<float,double,true,false,{RB},{nt}>", f"k_halo<float,double,false,false,{RB},{nt}>") \
+        if RB >= 64 else (f"k_fwd_v<float,double,{RB},{int(stream)}>", f"k_adj_v<float,double,{RB},{int(stream)},false>")
     kern = {"fwd": (f"{fk} (forward leapfrog step)", fwd_s, fb, f"k_fwd_f32_rb{RB}"),
             "adj": (f"{ak} (transpose leapfrog step)", adj_s, ab, f"k_adj_f32_rb{RB}")}
 
@@ -570,7 +573,7 @@ def main():
             "n_nodes": w.n_nodes, "n_steps": w.n_steps, "n_obs": w.n_obs, "samples_per_step": R,
             "cgls_iters": n_iter, "rhs_block": 64, "cgls_dtype": "f64",
         },
-        "roofline": roofline_record(fwd_avg_s, adj_avg_s, fb, ab, survey_step_bytes, sweep_share, w.name, 64),
+        "roofline": roofline_record(fwd_avg_s, adj_avg_s, fb, ab, survey_step_bytes, sweep_share, w.name, w.n_nodes, 64),
         "final_residual_f64": final,
     }
     if not args.no_wide_probe:

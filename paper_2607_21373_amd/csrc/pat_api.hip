@@ -235,12 +235,13 @@ void dev_free(pat_problem *p, void *ptr) {
     (void)hipFree(ptr);
 }
 
-template <typename T>
-pat_status upload(pat_problem *p, const std::vector<T> &h, const T **out) {
+template <typename T, typename U>
+pat_status upload(pat_problem *p, const std::vector<T> &h, const U **out) {
+    static_assert(sizeof(T) == sizeof(U), "the device type of the host words");
     void *d = nullptr;
     PAT_TRY(dev_alloc(p, &d, h.size() * sizeof(T)));
     if (!h.empty()) PAT_HIP(hipMemcpy(d, h.data(), h.size() * sizeof(T), hipMemcpyHostToDevice));
-    *out = static_cast<const T *>(d);
+    *out = static_cast<const U *>(d);
     return PAT_OK;
 }
 
@@ -1092,57 +1093,24 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
     UP(to_f32(hp.sw), sw32);
     UP(to_f32(hp.injw), injw32);
     {
-        // the device keeps a row's 16 padded slots (and a boundary row's first 16 B values)
-        // in quad order; the halo tiles below are built from the plain slot order
-        constexpr int W = pat::HostProblem::kEll;
-        auto quads = [](const auto &v, const std::vector<int64_t> &at) {
-            auto o = v;
-            for (int64_t b : at)
-                for (int j = 0; j < W; ++j) o[size_t(b + 4 * (j % 4) + j / 4)] = v[size_t(b + j)];
-            return o;
-        };
-        std::vector<int64_t> rows, brows;
-        std::vector<int32_t> rspec(size_t(hp.n), 0);
-        std::vector<int4> spec;
-        for (int32_t i = 0; i < hp.n; ++i) {
-            rows.push_back(int64_t(i) * W);
-            if (hp.bsoff[i] >= 0) brows.push_back(hp.bsoff[i]);
-            if (hp.bsoff[i] >= 0 || hp.xptr[i + 1] > hp.xptr[i] || hp.injptr[i + 1] > hp.injptr[i]) {
-                spec.push_back(int4{std::max(hp.bsoff[i], 0), hp.bnum[i], hp.xptr[i], hp.xptr[i + 1]});
-                spec.push_back(int4{hp.injptr[i], hp.injptr[i + 1], op.n_bnd, 0});
-                if (hp.bsoff[i] >= 0) ++op.n_bnd;
-                op.max_nb = std::max(op.max_nb, hp.bnum[i]);
-                op.max_spec = std::max({op.max_spec, hp.xptr[i + 1] - hp.xptr[i], hp.injptr[i + 1] - hp.injptr[i]});
-                rspec[i] = int32_t(spec.size() / 2);
-            }
-        }
-        std::vector<int32_t> order(size_t(hp.n)), pos(size_t(hp.n));
-        for (int32_t i = 0; i < hp.n; ++i) order[i] = i;
-        auto kind = [&](int32_t i) {
-            return (hp.xptr[i + 1] > hp.xptr[i] ? 4 : 0) + (hp.bsoff[i] >= 0 ? 2 : 0) +
-                   (hp.injptr[i + 1] > hp.injptr[i] ? 1 : 0);
-        };
-        std::stable_sort(order.begin(), order.end(), [&](int32_t x, int32_t y) { return kind(x) > kind(y); });
-        for (int32_t i = 0; i < hp.n; ++i) pos[order[i]] = i;
-        UP(order, order);
-        UP(pos, pos);
-        op.n_spec = int32_t(spec.size() / 2);
+        pat::DeviceRows dr;
+        pat::build_device_rows(hp, dr);
+        UP(dr.ell_col, ell_col);
+        UP(dr.rspec, rspec);
+        UP(dr.spec, spec);
+        if (!dr.rdir.empty()) UP(dr.rdir, rdir);
+        UP(dr.order, order);
+        UP(dr.pos, pos);
+        UP(dr.ell_val, ell_val64);
+        UP(dr.bslot, bslot64);
+        UP(to_f32(dr.ell_val), ell_val32);
+        UP(to_f32(dr.bslot), bslot32);
+        op.n_spec = int32_t(dr.spec.size() / 2);
+        op.n_bnd = dr.n_bnd;
+        op.max_nb = dr.max_nb;
+        op.max_spec = dr.max_spec;
         op.n_x = hp.xptr[hp.n];
         op.n_inj = hp.injptr[hp.n];
-        const std::vector<double> val = quads(hp.ell_val, rows), bval = quads(hp.bslot, brows);
-        UP(quads(hp.ell_col, rows), ell_col);
-        UP(rspec, rspec);
-        if (hp.n <= pat::kFewRows) {
-            std::vector<int4> rdir(size_t(hp.n), int4{0, 0, 0, 0});
-            for (int32_t i = 0; i < hp.n; ++i)
-                if (rspec[i]) rdir[i] = spec[size_t(2 * (rspec[i] - 1))];
-            UP(rdir, rdir);
-        }
-        UP(spec, spec);
-        UP(val, ell_val64);
-        UP(bval, bslot64);
-        UP(to_f32(val), ell_val32);
-        UP(to_f32(bval), bslot32);
     }
     UP(hp.xcol, xcol);
     UP(hp.xval, xval64);
@@ -1150,35 +1118,14 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
     {
         pat::HaloTiles ht;
         pat::build_halo_tiles(hp, ht);
-        // the float64 kernels read the row operands from the padded layout and a tile's own
-        // local indices, info words and B values from these arrays
-        std::vector<int4> desc;
-        std::vector<uint8_t> loc(ht.n_tiles ? size_t(hp.n) * 16 : 0), bloc;
-        std::vector<uint32_t> rinfo(ht.n_tiles ? size_t(hp.n) * 4 : 0);
-        std::vector<double> bw;
-        for (int32_t t = 0; t < ht.n_tiles; ++t) {
-            const int32_t *D = &ht.desc[size_t(t) * 4];
-            constexpr int B = pat::HaloTiles::kNrBits, M = (1 << B) - 1;
-            const int32_t r0 = D[0], nr = D[3] & M, nbr = (D[3] >> (B + 16)) & M;
-            const uint32_t *m = ht.meta.data() + size_t(D[2]) * 4, *info = m + size_t(nr) * 4;
-            const auto *l8 = reinterpret_cast<const uint8_t *>(m);
-            const auto *b8 = reinterpret_cast<const uint8_t *>(m + size_t(nr) * 24 + size_t(nbr) * 16);
-            desc.push_back(int4{r0, D[1], int32_t(bloc.size() / 16), D[3]});
-            std::copy(l8, l8 + size_t(nr) * 16, loc.begin() + size_t(r0) * 16);
-            bloc.insert(bloc.end(), b8, b8 + size_t(nbr) * 16);
-            for (int32_t g = 0; g < nr; ++g) {
-                std::copy(info + size_t(g) * 4, info + size_t(g) * 4 + 4, rinfo.begin() + size_t(r0 + g) * 4);
-                if (hp.bsoff[r0 + g] >= 0)
-                    bw.insert(bw.end(), hp.bslot.begin() + hp.bsoff[r0 + g],
-                              hp.bslot.begin() + hp.bsoff[r0 + g] + pat::HostProblem::kEll);
-            }
-        }
-        UP(desc, ht_desc);
+        pat::DeviceTiles dt;
+        pat::build_device_tiles(hp, ht, dt);
+        UP(dt.desc, ht_desc);
         UP(ht.hrow, ht_hrow);
-        UP(loc, ht_loc);
-        UP(bloc, ht_bloc);
-        UP(rinfo, ht_info);
-        UP(bw, ht_bw);
+        UP(dt.loc, ht_loc);
+        UP(dt.bloc, ht_bloc);
+        UP(dt.info, ht_info);
+        UP(dt.bw, ht_bw);
         UP(ht.meta, ht_meta);
         op.n_ht = ht.n_tiles;
         int ncu = 0;

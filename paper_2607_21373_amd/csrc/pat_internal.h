@@ -58,8 +58,8 @@ pat_status build_host_problem(const pat_problem_desc &d, HostProblem &hp, std::s
 void build_padded_rows(HostProblem &hp);
 
 // Halo tiles of the step kernels whose RHS block rows are 256-byte multiples (the
-// float64 kernels take the K and B values from memory, the rest from here).  Consecutive rows (a compact cluster of the node order) are cut
-// greedily into tiles of at most kRows rows whose halo, the distinct rows that
+// float64 kernels take the K and B values from memory, the rest from here).
+// Consecutive rows (a compact cluster of the node order) are cut greedily into tiles of at most kRows rows whose halo, the distinct rows that
 // the tile's padded slots refer to (K rows) plus the distinct rows its boundary
 // slots refer to (B rows), each padded to a multiple of 4, holds at most kMax
 // rows.  Per tile: a descriptor, the halo's row list and one metadata block
@@ -90,6 +90,42 @@ struct HaloTiles {
 };
 void build_halo_tiles(const HostProblem &hp, HaloTiles &ht);
 
+// Launches of at most kFewGroups workgroups are latency-bound (few_waves in pat_kernels.hip);
+// a workgroup holds at most 256 rows.
+constexpr int kFewGroups = 512, kFewRows = kFewGroups * 256;
+
+// Four 32-bit words, as the device reads them (int4)
+struct Int4 {
+    int32_t x, y, z, w;
+};
+
+// The row tables as the device holds them (DevOps), from the plain layouts above.
+struct DeviceRows {
+    // ell_col, ell_val, and the first kEll B values of every boundary row: slots in quad order
+    // (slot p + 4 i of a row at 4 p + i)
+    std::vector<int32_t> ell_col;
+    std::vector<double> ell_val, bslot;
+    // per row 0, or 1 + its record in spec; the records, two Int4 each; the first half of
+    // each row's record by row (meshes of up to kFewRows nodes, else empty)
+    std::vector<int32_t> rspec;
+    std::vector<Int4> spec, rdir;
+    // rows of a kind together (overflow entries, boundary, sensor weights, neither), and its inverse
+    std::vector<int32_t> order, pos;
+    // boundary rows, their largest bnum, the largest count of overflow entries or sensor weights in a row
+    int32_t n_bnd = 0, max_nb = 0, max_spec = 0;
+};
+void build_device_rows(const HostProblem &hp, DeviceRows &dr);
+
+// The halo tiles' tables as the device holds them: per tile {first row, first halo entry, rank
+// of its first boundary row, packed counts}; for the float64 kernels by row the local indices
+// and info words, by boundary row the local indices and the values of its first kEll slots.
+struct DeviceTiles {
+    std::vector<Int4> desc;
+    std::vector<uint8_t> loc, bloc;
+    std::vector<uint32_t> info;
+    std::vector<double> bw;
+};
+void build_device_tiles(const HostProblem &hp, const HaloTiles &ht, DeviceTiles &dt);
 
 // Largest eigenvalue of M_L^{-1} K by power iteration on M^{-1/2} K M^{-1/2}.
 double estimate_lambda_max(const HostProblem &hp, int iters);

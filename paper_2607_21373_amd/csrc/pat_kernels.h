@@ -1,15 +1,13 @@
-// Kernel launch interface of libpat (implemented in pat_kernels.hip).
+// Kernel launch interface of libpat (pat_kernels.hip, pat_halo.hip, pat_small.hip, pat_spectral.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>
 
 #include <cstdint>
 
-namespace pat {
+#include "pat_internal.h"
 
-// Launches of at most kFewGroups workgroups are latency-bound (few_waves in pat_kernels.hip);
-// a workgroup holds at most 256 rows.
-constexpr int kFewGroups = 512, kFewRows = kFewGroups * 256;
+namespace pat {
 
 // Device copy of the assembled operators (internal node numbering).
 struct DevOps {

@@ -639,6 +639,69 @@ void build_halo_tiles(const HostProblem &hp, HaloTiles &ht) {
     ht.n_tiles = int32_t(ht.desc.size() / 4);
 }
 
+void build_device_rows(const HostProblem &hp, DeviceRows &dr) {
+    constexpr int W = HostProblem::kEll;
+    const size_t N = size_t(hp.n);
+    dr = DeviceRows{};
+    auto quads = [](const auto &v, auto &o, size_t at) {
+        for (size_t j = 0; j < W; ++j) o[at + 4 * (j % 4) + j / 4] = v[at + j];
+    };
+    dr.ell_col.resize(N * W);
+    dr.ell_val.resize(N * W);
+    dr.bslot = hp.bslot;
+    dr.rspec.assign(N, 0);
+    for (size_t i = 0; i < N; ++i) {
+        quads(hp.ell_col, dr.ell_col, i * W);
+        quads(hp.ell_val, dr.ell_val, i * W);
+        const int32_t bo = hp.bsoff[i], x0 = hp.xptr[i], x1 = hp.xptr[i + 1], e0 = hp.injptr[i], e1 = hp.injptr[i + 1];
+        if (bo >= 0) quads(hp.bslot, dr.bslot, size_t(bo));
+        if (bo < 0 && x1 == x0 && e1 == e0) continue;
+        dr.spec.push_back({std::max(bo, 0), hp.bnum[i], x0, x1});
+        dr.spec.push_back({e0, e1, dr.n_bnd, 0});
+        dr.rspec[i] = int32_t(dr.spec.size() / 2);
+        if (bo >= 0) ++dr.n_bnd;
+        dr.max_nb = std::max(dr.max_nb, hp.bnum[i]);
+        dr.max_spec = std::max({dr.max_spec, x1 - x0, e1 - e0});
+    }
+    if (hp.n <= kFewRows) {
+        dr.rdir.assign(N, Int4{0, 0, 0, 0});
+        for (size_t i = 0; i < N; ++i)
+            if (dr.rspec[i]) dr.rdir[i] = dr.spec[size_t(2 * (dr.rspec[i] - 1))];
+    }
+    dr.order.resize(N);
+    dr.pos.resize(N);
+    for (int32_t i = 0; i < hp.n; ++i) dr.order[size_t(i)] = i;
+    auto kind = [&](int32_t r) {
+        const size_t i = size_t(r);
+        return (hp.xptr[i + 1] > hp.xptr[i] ? 4 : 0) + (hp.bsoff[i] >= 0 ? 2 : 0) +
+               (hp.injptr[i + 1] > hp.injptr[i] ? 1 : 0);
+    };
+    std::stable_sort(dr.order.begin(), dr.order.end(), [&](int32_t x, int32_t y) { return kind(x) > kind(y); });
+    for (int32_t i = 0; i < hp.n; ++i) dr.pos[size_t(dr.order[size_t(i)])] = i;
+}
+
+void build_device_tiles(const HostProblem &hp, const HaloTiles &ht, DeviceTiles &dt) {
+    dt = DeviceTiles{};
+    dt.loc.resize(ht.n_tiles ? size_t(hp.n) * 16 : 0);
+    dt.info.resize(ht.n_tiles ? size_t(hp.n) * 4 : 0);
+    for (int32_t t = 0; t < ht.n_tiles; ++t) {
+        const int32_t *D = &ht.desc[size_t(t) * 4];
+        constexpr int B = HaloTiles::kNrBits, M = (1 << B) - 1;
+        const size_t r0 = size_t(D[0]), nr = size_t(D[3] & M), nbr = size_t((D[3] >> (B + 16)) & M);
+        const uint32_t *m = ht.meta.data() + size_t(D[2]) * 4, *info = m + nr * 4;
+        const auto *l8 = reinterpret_cast<const uint8_t *>(m);
+        const auto *b8 = reinterpret_cast<const uint8_t *>(m + nr * 24 + nbr * 16);
+        dt.desc.push_back({D[0], D[1], int32_t(dt.bloc.size() / 16), D[3]});
+        std::copy(l8, l8 + nr * 16, dt.loc.begin() + int64_t(r0 * 16));
+        std::copy(info, info + nr * 4, dt.info.begin() + int64_t(r0 * 4));
+        dt.bloc.insert(dt.bloc.end(), b8, b8 + nbr * 16);
+        for (size_t i = r0; i < r0 + nr; ++i)
+            if (hp.bsoff[i] >= 0)
+                dt.bw.insert(dt.bw.end(), hp.bslot.begin() + hp.bsoff[i],
+                             hp.bslot.begin() + hp.bsoff[i] + HostProblem::kEll);
+    }
+}
+
 namespace {
 void spmv_host(const HostProblem &hp, const std::vector<double> &val, const std::vector<double> &x,
                std::vector<double> &y) {
