@@ -1099,8 +1099,8 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
         UP(dr.rspec, rspec);
         UP(dr.spec, spec);
         if (!dr.rdir.empty()) UP(dr.rdir, rdir);
-        UP(dr.order, order);
-        UP(dr.pos, pos);
+        if (!dr.order.empty()) UP(dr.order, order);
+        if (!dr.pos.empty()) UP(dr.pos, pos);
         UP(dr.ell_val, ell_val64);
         UP(dr.bslot, bslot64);
         UP(to_f32(dr.ell_val), ell_val32);
@@ -1122,9 +1122,6 @@ pat_status pat_problem_create(const pat_problem_desc *desc, pat_problem **out) {
         pat::build_device_tiles(hp, ht, dt);
         UP(dt.desc, ht_desc);
         UP(ht.hrow, ht_hrow);
-        UP(dt.loc, ht_loc);
-        UP(dt.bloc, ht_bloc);
-        UP(dt.info, ht_info);
         UP(dt.bw, ht_bw);
         UP(ht.meta, ht_meta);
         op.n_ht = ht.n_tiles;

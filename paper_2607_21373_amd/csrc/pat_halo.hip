@@ -50,9 +50,7 @@ template <typename T>
 struct HaloArgs {
     const int4 *desc;  // per tile: first row, first halo entry, first boundary rank, packed counts
     const int32_t *hrow;
-    const uint8_t *loc, *bloc;
-    const uint32_t *info;  // [N][4], see HOps
-    const uint32_t *meta;  // float32: the tiles' metadata blocks
+    const uint32_t *meta;  // the tiles' metadata blocks
     const T *eval, *bw, *dtm, *xval, *bslot, *injw, *sw;
     const int32_t *rspec, *xcol, *injs, *snode;
     const int4 *spec;
@@ -149,6 +147,13 @@ __device__ __forceinline__ HDesc desc_uniform(const int4 u) {
     return {r0, f & M, h0, (f >> B) & 255, (f >> (B + 8)) & 255, b0, (f >> (B + 16)) & M};
 }
 
+// A tile's metadata block (HaloTiles): 96 bytes per row and 80 per boundary row, of all tiles
+// before it too.
+template <typename T>
+__device__ __forceinline__ const char *tile_meta(const HaloArgs<T> &a, const HDesc &d) {
+    return reinterpret_cast<const char *>(a.meta) + uint64_t(uint32_t(d.r0) * 6u + uint32_t(d.b0) * 5u) * 16u;
+}
+
 // Work items of this workgroup: (chunk c, tile t).  XCD x (workgroups b with
 // b % 8 == x) owns the x-th eighth of the tiles, [t_lo, t_lo + ntx), seen as rows
 // of G8 consecutive tiles (one per workgroup of the XCD: neighbouring tiles are in
@@ -212,15 +217,14 @@ __device__ __forceinline__ void halo_issue(const HaloArgs<T> &a, uint32_t coff, 
     }
     const int u = kHWaves - 1 - wave;  // 16-byte units, 64 per instruction
     if constexpr (sizeof(T) == 4) {
-        // 96 bytes per row and 80 per boundary row, of all tiles before this one too
         const int nu = d.nr * 6 + d.nbr * 5;
-        const char *src = reinterpret_cast<const char *>(a.meta) + uint64_t(uint32_t(d.r0) * 6u + uint32_t(d.b0) * 5u + uint32_t(u * 64)) * 16u;
+        const char *src = tile_meta(a, d) + u * 1024;
         if (u * 64 < nu && u * 64 + lane < nu) lds_copy16(src + uint32_t(lane) * 16u, &Lb.meta[u * 256]);
     } else if (d.nbr) {
         const int nu = d.nbr * 8;
         const char *src = reinterpret_cast<const char *>(a.bw) + uint64_t(uint32_t(d.b0) * 8u + uint32_t(u * 64)) * 16u;
         if (u * 64 < nu && u * 64 + lane < nu) lds_copy16(src + uint32_t(lane) * 16u, &Lb.bws[u * 128]);
-        if (wave == 0 && lane < d.nbr) lds_copy16(a.bloc + uint64_t(uint32_t(d.b0)) * 16u + uint32_t(lane) * 16u, Lb.blocs);
+        if (wave == 0 && lane < d.nbr) lds_copy16(tile_meta(a, d) + (d.nr * 96 + d.nbr * 64) + uint32_t(lane) * 16u, Lb.blocs);
     }
 }
 
@@ -238,11 +242,13 @@ struct HOps {
         info = Lb.meta[nr * 4 + g * 4 + (q & 3)];
         kv = reinterpret_cast<const float *>(Lb.meta + nr * 8 + g * 16)[q];
     }
-    // float64: row `row` of the mesh from memory
-    __device__ __forceinline__ void from_memory(const HaloArgs<T> &a, uint32_t row, int q) {
-        loc = a.loc[row * 16u + uint32_t(q)];
+    // float64: row g of tile d from memory (K and dt/m in float64, the rest from the tile's block)
+    __device__ __forceinline__ void from_memory(const HaloArgs<T> &a, const HDesc &d, int g, int q) {
+        const uint32_t row = uint32_t(d.r0 + g);
+        const char *m = tile_meta(a, d);
+        loc = *reinterpret_cast<const uint8_t *>(m + uint32_t(g * 16 + q));
         kv = a.eval[int64_t(row) * 16 + 4 * (q & 3) + (q >> 2)];  // slot q of the quad-ordered row
-        info = a.info[row * 4u + uint32_t(q & 3)];
+        info = *reinterpret_cast<const uint32_t *>(m + uint32_t((d.nr + g) * 16 + (q & 3) * 4));
         dm = a.dtm[row];
     }
     __device__ __forceinline__ T dtm() const {
@@ -368,7 +374,7 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
         if (g < d.nr) {
             const uint32_t row = uint32_t(d.r0 + g);
             prev_nxt = load_own<NT, VT>(Spc + (row * RS + uint32_t(wk.chunk(it)) * 256u + q16));
-            if constexpr (sizeof(T) == 8) o_nxt.from_memory(a, row, q);
+            if constexpr (sizeof(T) == 8) o_nxt.from_memory(a, d, g, q);
         }
     };
     auto fn_rot = [&]() {
@@ -491,7 +497,7 @@ __global__ void __launch_bounds__(kHThreads) __attribute__((amdgpu_waves_per_eu(
 template <typename T>
 HaloArgs<T> halo_args(const DevOps &op, const void *S, const void *Sp, void *Sn) {
     HaloArgs<T> a{};
-    a.desc = op.ht_desc; a.hrow = op.ht_hrow; a.loc = op.ht_loc; a.bloc = op.ht_bloc; a.info = op.ht_info; a.meta = op.ht_meta;
+    a.desc = op.ht_desc; a.hrow = op.ht_hrow; a.meta = op.ht_meta;
     a.rspec = op.rspec; a.xcol = op.xcol; a.injs = op.injs; a.snode = op.snode; a.spec = op.spec;
     if constexpr (sizeof(T) == 8) {
         a.eval = op.ell_val64; a.bw = op.ht_bw; a.dtm = op.dtm64; a.xval = op.xval64; a.bslot = op.bslot64;

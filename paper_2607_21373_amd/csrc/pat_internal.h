@@ -94,6 +94,9 @@ void build_halo_tiles(const HostProblem &hp, HaloTiles &ht);
 // a workgroup holds at most 256 rows.
 constexpr int kFewGroups = 512, kFewRows = kFewGroups * 256;
 
+// Meshes whose whole sweep may run in one launch (pat_small.hip): one or two rows per thread.
+constexpr int kSmallThreads = 1024, kSmallRows = 2 * kSmallThreads;
+
 // Four 32-bit words, as the device reads them (int4)
 struct Int4 {
     int32_t x, y, z, w;
@@ -109,20 +112,20 @@ struct DeviceRows {
     // each row's record by row (meshes of up to kFewRows nodes, else empty)
     std::vector<int32_t> rspec;
     std::vector<Int4> spec, rdir;
-    // rows of a kind together (overflow entries, boundary, sensor weights, neither), and its inverse
+    // rows of a kind together (overflow entries, boundary, sensor weights, neither), and its
+    // inverse (meshes of up to kSmallRows nodes, else empty)
     std::vector<int32_t> order, pos;
     // boundary rows, their largest bnum, the largest count of overflow entries or sensor weights in a row
     int32_t n_bnd = 0, max_nb = 0, max_spec = 0;
 };
 void build_device_rows(const HostProblem &hp, DeviceRows &dr);
 
-// The halo tiles' tables as the device holds them: per tile {first row, first halo entry, rank
-// of its first boundary row, packed counts}; for the float64 kernels by row the local indices
-// and info words, by boundary row the local indices and the values of its first kEll slots.
+// The halo tiles' tables that the device holds beside hrow and meta: per tile {first row, first
+// halo entry, rank of its first boundary row, packed counts} (its metadata block starts at 96
+// bytes per row and 80 per boundary row before it); for the float64 kernels by boundary row the
+// values of its first kEll slots.
 struct DeviceTiles {
     std::vector<Int4> desc;
-    std::vector<uint8_t> loc, bloc;
-    std::vector<uint32_t> info;
     std::vector<double> bw;
 };
 void build_device_tiles(const HostProblem &hp, const HaloTiles &ht, DeviceTiles &dt);

@@ -33,18 +33,16 @@ struct DevOps {
     const double *ell_val64 = nullptr, *xval64 = nullptr, *bslot64 = nullptr;
     const float *ell_val32 = nullptr, *xval32 = nullptr, *bslot32 = nullptr;
     // halo tiles (HaloTiles; pat_halo.hip): per tile {first row, first halo entry, rank of its
-    // first boundary row, packed counts}, the halos' rows and the metadata blocks (float32);
-    // for the float64 kernels per row the K-local index of each slot and the four info words,
-    // per boundary row the B-local index and the value of each slot
+    // first boundary row, packed counts}, the halos' rows and the metadata blocks; for the
+    // float64 kernels the values of each boundary row's first 16 slots
     const int4 *ht_desc = nullptr;
     const int32_t *ht_hrow = nullptr;
-    const uint8_t *ht_loc = nullptr, *ht_bloc = nullptr;
-    const uint32_t *ht_info = nullptr, *ht_meta = nullptr;
+    const uint32_t *ht_meta = nullptr;
     const double *ht_bw = nullptr;
     int32_t n_ht = 0;
     int32_t n_cu = 0;  // compute units of the device
     // rows of a kind together (overflow entries, boundary, sensor weights, neither), and its
-    // inverse (pat_small.hip)
+    // inverse (pat_small.hip; meshes of up to kSmallRows nodes)
     const int32_t *order = nullptr, *pos = nullptr;
     double dt = 0.0;
     // sizes of the extra tables: records, boundary rows and their largest bnum, entries beyond the

@@ -668,6 +668,7 @@ void build_device_rows(const HostProblem &hp, DeviceRows &dr) {
         for (size_t i = 0; i < N; ++i)
             if (dr.rspec[i]) dr.rdir[i] = dr.spec[size_t(2 * (dr.rspec[i] - 1))];
     }
+    if (hp.n > kSmallRows) return;
     dr.order.resize(N);
     dr.pos.resize(N);
     for (int32_t i = 0; i < hp.n; ++i) dr.order[size_t(i)] = i;
@@ -682,19 +683,10 @@ void build_device_rows(const HostProblem &hp, DeviceRows &dr) {
 
 void build_device_tiles(const HostProblem &hp, const HaloTiles &ht, DeviceTiles &dt) {
     dt = DeviceTiles{};
-    dt.loc.resize(ht.n_tiles ? size_t(hp.n) * 16 : 0);
-    dt.info.resize(ht.n_tiles ? size_t(hp.n) * 4 : 0);
     for (int32_t t = 0; t < ht.n_tiles; ++t) {
         const int32_t *D = &ht.desc[size_t(t) * 4];
-        constexpr int B = HaloTiles::kNrBits, M = (1 << B) - 1;
-        const size_t r0 = size_t(D[0]), nr = size_t(D[3] & M), nbr = size_t((D[3] >> (B + 16)) & M);
-        const uint32_t *m = ht.meta.data() + size_t(D[2]) * 4, *info = m + nr * 4;
-        const auto *l8 = reinterpret_cast<const uint8_t *>(m);
-        const auto *b8 = reinterpret_cast<const uint8_t *>(m + nr * 24 + nbr * 16);
-        dt.desc.push_back({D[0], D[1], int32_t(dt.bloc.size() / 16), D[3]});
-        std::copy(l8, l8 + nr * 16, dt.loc.begin() + int64_t(r0 * 16));
-        std::copy(info, info + nr * 4, dt.info.begin() + int64_t(r0 * 4));
-        dt.bloc.insert(dt.bloc.end(), b8, b8 + nbr * 16);
+        const size_t r0 = size_t(D[0]), nr = size_t(D[3] & ((1 << HaloTiles::kNrBits) - 1));
+        dt.desc.push_back({D[0], D[1], int32_t(dt.bw.size() / HostProblem::kEll), D[3]});
         for (size_t i = r0; i < r0 + nr; ++i)
             if (hp.bsoff[i] >= 0)
                 dt.bw.insert(dt.bw.end(), hp.bslot.begin() + hp.bsoff[i],

@@ -31,7 +31,6 @@
 namespace pat {
 namespace {
 
-constexpr int kSmallThreads = 1024;
 constexpr size_t kLdsBytes = 163840;
 
 constexpr int kOverRegs = 12;  // overflow entries whose columns a thread of one row keeps in registers
@@ -510,7 +509,7 @@ SmallArgs<float> small_args<float>(const DevOps &op, int RB) {
 template <typename T>
 int small_rpt(const DevOps &op) {
     const int rpt = (op.n + kSmallThreads - 1) / kSmallThreads;
-    if (rpt > 2 || op.n_obs > kSmallThreads) return 0;
+    if (op.n > kSmallRows || op.n_obs > kSmallThreads) return 0;
     if (op.max_nb > 16 || op.n_bnd > 0x7FFF || op.n_x > 0x7FFF || op.n_inj > 0x7FFF || op.max_spec > 0x7FFF)
         return 0;
     const SmallSizes z = small_sizes(op);

@@ -54,6 +54,16 @@ int main(int argc, char **argv) {
     }
     if (dr.n_bnd != bnd || dr.max_nb != nb || dr.max_spec != most || dr.spec.size() != 2 * size_t(special))
         return fail("counts");
+    // the order of the one-launch sweeps, only where they may run
+    if (dr.order.size() != (hp.n <= pat::kSmallRows ? N : 0) || dr.pos.size() != dr.order.size()) return fail("order");
+    auto kind = [&](size_t i) {
+        return (hp.xptr[i + 1] > hp.xptr[i]) * 4 + (hp.bsoff[i] >= 0) * 2 + (hp.injptr[i + 1] > hp.injptr[i]);
+    };
+    for (size_t k = 0; k < dr.order.size(); ++k) {
+        const size_t i = size_t(dr.order[k]);
+        if (dr.pos[i] != int32_t(k)) return fail("order: inverse");
+        if (k && kind(size_t(dr.order[k - 1])) < kind(i)) return fail("order: kinds");
+    }
     // halo tiles: the metadata blocks lie one after another, 96 bytes a row and 80 a boundary row
     if (dt.desc.size() != size_t(ht.n_tiles)) return fail("tiles");
     int32_t rank = 0;
