@@ -574,7 +574,8 @@ pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t
                 if (hipMemsetAsync(W[m]->S[k], 0, nb, s) != hipSuccess)
                     st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
             }
-            if (hipMemsetAsync(W[m]->Y, 0, yb, s) != hipSuccess) st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
+            if (hipMemsetAsync(W[m]->Y, 0, yb, s) != hipSuccess)
+                st = fail(PAT_ERR_HIP, "autotune: hipMemsetAsync failed");
         }
         if (st != PAT_OK) break;
         const bool yf = pr == pat::Prec::F64;

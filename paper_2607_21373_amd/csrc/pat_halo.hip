@@ -557,11 +557,20 @@ bool beyond_cache(const DevOps &op, Prec prec, int RB) {
 }  // namespace
 
 // Rows of one to four 256-byte chunks, and at least 1.5 tiles per workgroup: below that
-// the pipelines have nothing to overlap and the vector-lane kernels win (float64, 64 RHS:
-// 9.3 / 9.0 against 8.1 / 8.3 us per forward / transposed step on 9,261 nodes, 11.4 / 11.5
-// against 10.6 / 10.9 on 15,625 (564 tiles); float32, 64 RHS: 4.9 / 5.4 against 4.4 / 5.3
-// on 4,913, even on 15,625); on 29,791 nodes (1,075 tiles) and above the tiles win (15.4
-// against 17.7 us, float64, 64 RHS).
+// the pipelines have nothing to overlap, and the vector-lane kernels win or are even at
+// every width, although a wider row gives a workgroup more items.  Halo tiles against
+// vector lanes, us per forward / transposed step:
+//               4,913 nodes              15,625 (564 tiles)        19,683
+//   float32  64   5.2 /  5.5,  4.7 /  5.4    7.0 /  7.0,  7.1 /  7.1    7.6 /  7.8,  7.5 /  7.8
+//           128   7.3 /  8.1,  5.8 /  6.5   11.2 / 11.6, 10.5 / 10.6   11.9 / 12.4, 12.0 / 12.4
+//           256  11.7 / 13.6,  8.2 /  8.5   19.4 / 20.3, 17.2 / 16.7   20.5 / 21.3, 20.5 / 21.5
+//   float64  32   5.5 /  5.4,  4.9 /  5.4    7.4 /  7.0,  7.2 /  7.3    7.7 /  7.8,  7.8 /  7.8
+//            64   7.6 /  7.9,  6.1 /  6.6   11.4 / 11.2, 10.6 / 10.6   12.3 / 12.0, 12.2 / 12.1
+//           128  12.4 / 12.8,  8.4 /  8.4   19.5 / 20.0, 17.7 / 17.2   20.8 / 21.1, 20.9 / 21.1
+// (one chunk on 9,261 to 12,167 nodes, one tile per workgroup: the tiles are ahead, 5.6 / 6.0
+// against 5.8 / 6.6 with 64 float32 RHS; wider rows lose on the smaller and are within 4% on
+// the larger).  On 29,791 nodes (1,075 tiles) and above the tiles win (15.4 against 17.7
+// us, float64, 64 RHS).
 bool halo_step_supported(Prec prec, int RB, const DevOps &op) {
     const int row = RB * (prec == Prec::F64 ? 8 : 4);
     return row >= 256 && row <= 1024 && op.n_cu > 0 && op.n_ht >= 3 * op.n_cu;

@@ -59,7 +59,8 @@ void build_padded_rows(HostProblem &hp);
 
 // Halo tiles of the step kernels whose RHS block rows are 256-byte multiples (the
 // float64 kernels take the K and B values from memory, the rest from here).
-// Consecutive rows (a compact cluster of the node order) are cut greedily into tiles of at most kRows rows whose halo, the distinct rows that
+// Consecutive rows (a compact cluster of the node order) are cut greedily into
+// tiles of at most kRows rows whose halo, the distinct rows that
 // the tile's padded slots refer to (K rows) plus the distinct rows its boundary
 // slots refer to (B rows), each padded to a multiple of 4, holds at most kMax
 // rows.  Per tile: a descriptor, the halo's row list and one metadata block

@@ -369,9 +369,8 @@ __global__ void __launch_bounds__(256) k_adj(const AdjArgs<T> a) {
 // traffic.  Operands staged in LDS for the whole tile (a round trip and two barriers
 // more per tile, and for 16-byte rows 82 KiB of LDS per workgroup, one workgroup per
 // CU) took 29.2 us per forward step of 4 float32 RHS on the 195,112-node ball against
-// 10.3 us here (34 MB, 3.3 TB/s); 19.2 -> 12.6 us at 8 RHS, 19.0 -> 15.7 at 16 (63 MB,
-// 4.0 TB/s), 25.5 -> 23.0 at 32; float64: 42.5 -> 13.9 us at 2 RHS, 21.5 -> 16.6 at 8,
-// 43.2 -> 41.9 at 32.
+// 9.4 us here (34 MB, 3.6 TB/s); 19.2 -> 11.9 us at 8 RHS, 19.0 -> 15.4 at 16 (63 MB,
+// 4.1 TB/s), 25.5 -> 22.5 at 32; float64: 42.5 -> 12.5 us at 2 RHS, 21.5 -> 16.3 at 8.
 // ---------------------------------------------------------------------------
 
 template <typename T>
@@ -1156,7 +1155,7 @@ __global__ void __launch_bounds__(256) k_norms(const double *x, int64_t xrows, i
 }
 
 // part[b][r] = sum over rows of block b of (a[row][aoff + r] - y[row][r])^2, a with row
-// stride lda, y with row stride RB (same reduction shape as k_dot_partial)
+// stride lda, y with row stride RB (the reduction tree of norm_partial)
 __global__ void __launch_bounds__(256) k_diff_sq_partial(const double *a, int lda, int aoff, const double *y,
                                                          int64_t rows, int RB, double *part) {
     __shared__ double red[256];
@@ -1577,7 +1576,7 @@ VFwdArgs<T> fwd_args_v(const DevOps &op, const void *S, const void *Sp, void *Sn
 }
 
 // Launches of at most kFewGroups = 512 workgroups, two waves per SIMD, take the variants with
-// everything in flight (up to 200 registers) and the records by row: the wave with the
+// everything in flight (174 to 249 registers) and the records by row: the wave with the
 // longest chain of round trips is what such a launch takes.  15,625 nodes, per forward /
 // transposed step: 1 float32 RHS 2.87 / 3.07 -> 2.58 / 2.86 us, 4 RHS 4.6 / 5.0 -> 4.0 /
 // 4.2, 16 RHS 4.0 / 4.5 -> 3.7 / 4.2; 4,913 nodes, 16 RHS 4.9 / 4.9 -> 4.2 / 4.2.  With the

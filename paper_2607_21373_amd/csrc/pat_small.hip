@@ -20,7 +20,7 @@
 // transposed step: 729 nodes, one float64 RHS 1.05 / 1.29 us (3.0 / 3.2 as step launches;
 // 1.58 / 1.81 with records, B values and overflow columns read from LDS), 16 RHS 1.04 /
 // 1.19 (6.9 / 7.5; 1.65 / 1.91); 1,331 nodes, one float32 RHS 1.33 / 1.46 (1.64 / 1.92
-// from LDS); 2,028 nodes, 16 float32 RHS 1.75 / 1.76 (7.7 / 7.9; 1.88 / 1.95).
+// from LDS); 2,028 nodes, 16 float32 RHS 1.64 / 1.75 (7.8 / 7.9; 1.88 / 1.95).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -502,10 +502,13 @@ SmallArgs<float> small_args<float>(const DevOps &op, int RB) {
 
 // rows per thread, or 0 where the mesh does not fit: its rows (24 registers of float32
 // or 40 of float64 operands each, of the 128 a thread of a full workgroup has), its
-// tables (counts packed into 16-bit fields) or its sensors (one thread each).  Four
-// float32 rows per thread would fit but spill, and lose: 4.4 / 5.1 against 2.9 / 3.0 us
-// per forward / transposed step of one RHS on 2,940 nodes, 3.3 / 4.6 against 4.4 / 4.5
-// for 16.
+// tables (counts packed into 16-bit fields) or its sensors (one thread each).  Two
+// float64 rows spill 9 to 42 registers in three of the four kernels and still beat the
+// step launches: 1,056 / 1,690 nodes, one RHS 2.1 / 2.5 and 2.2 / 2.7 us per forward / transposed
+// step against 2.7 / 2.9 and 2.9 / 3.1, 16 RHS 1.9 / 2.3 and 2.1 / 2.5 against 4.2 / 4.4 and
+// 4.3 / 4.4.  (2,028 float64 nodes do not fit the LDS.)  Four float32 rows per thread would
+// fit but spill, and lose: 4.4 / 5.1 against 2.9 / 3.0 us per forward / transposed step of one
+// RHS on 2,940 nodes, 3.3 / 4.6 against 4.4 / 4.5 for 16.
 template <typename T>
 int small_rpt(const DevOps &op) {
     const int rpt = (op.n + kSmallThreads - 1) / kSmallThreads;
