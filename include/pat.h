@@ -265,8 +265,9 @@ pat_status pat_batch_autotune(pat_batch *b, int64_t S, pat_precision prec, int32
  * 2 = each problem's whole sweep in turn (keeps a small mesh's working set in
  * cache across its steps; sweeps of meshes of up to 2,048 nodes run in one launch
  * in this mode only); -1 = the autotuned choice (when not tuned: merged, or 2 for a batch
- * with such meshes in which all are that small, the block is too narrow to merge or a larger mesh
- * has halo tiles for it).  Results do not depend on it. */
+ * with such meshes in which all are that small, the block is too narrow to merge, a larger mesh
+ * has halo tiles for it, or a mesh of up to 1,024 nodes is paired with one that a launch of at
+ * most 512 workgroups holds).  Results do not depend on it. */
 pat_status pat_batch_merge(pat_batch *b, int32_t forward, int32_t transpose);
 
 /* rto_sample for every problem m of the batch at once: arrays of n entries

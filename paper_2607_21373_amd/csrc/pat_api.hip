@@ -663,18 +663,31 @@ pat_status tune_rb(const std::vector<pat_problem *> &P, hipStream_t cap, int64_t
 // Launch mode of a batch that was not tuned.  Merged, but each mesh's sweep in turn where that
 // runs some of them in one launch and the rest lose nothing: all meshes are that small, or a
 // block is too narrow to merge, or a larger mesh has halo tiles, which a merged launch does
-// not use.  Per forward and transposed step with the solver's share, merged against in turn:
-// 729 + 864 + 1,331 + 2,028 nodes, 16 float32 RHS 13.6 / 10.3 us; 729 + 864 + 4,913, two 18.9 /
-// 10.6; 2,028 + 195,112, 64 float32 82.5 / 72.4.  Elsewhere the small meshes' tiles ride along: 729 +
-// 2,028 + 1,980 + 195,112 nodes, 16 float32 RHS 33.1 / 40.4, 16 float64 52.5 / 72.3.
+// not use, or one mesh of one row per thread stands beside one whose launches have few waves, a
+// variant that merged launches do not have either.  Per forward and transposed step with the
+// solver's share, merged against in turn: 729 + 864 + 1,331 + 2,028 nodes, 16 float32 RHS 13.6 /
+// 10.3 us; 729 + 864 + 4,913, two 18.9 / 10.6; 2,028 + 195,112, 64 float32 82.5 / 72.4; 729 +
+// 4,913, 16 float32 12.4 / 11.5, 16 float64 13.3 / 11.2; 729 + 15,625, 16 float32 13.0 / 10.6.
+// Elsewhere the small meshes' tiles ride along: 729 + 2,028 + 1,980 + 195,112 nodes, 16 float32
+// RHS 33.1 / 40.4, 16 float64 52.5 / 72.3; 729 + 1,331 + 4,913, 16 float32 12.9 / 14.1; 729 +
+// 27,000, 32 float32 (844 workgroups) 16.7 / 17.1.  Two rows per thread are even in float32 (1,690 +
+// 4,913, 16 RHS 12.1 / 12.6; 1,690 + 15,625 12.4 / 11.7) and lose in float64 (11.8 / 13.6).
 int batch_mode(const std::vector<pat_problem *> &P, pat::Prec pr, int RB) {
+    const int tile = int(4096 / (size_t(RB) * tsize(pr)));  // rows of a vector-lane workgroup
     size_t small = 0;
-    bool halo = false;
+    bool halo = false, quick = P.size() == 2;
     for (const pat_problem *p : P) {
-        if (pat::small_sweep_supported(pr, p->ops)) ++small;
-        else halo = halo || pat::halo_step_supported(pr, RB, p->ops);
+        const pat::DevOps &op = p->ops;
+        if (pat::small_sweep_supported(pr, op)) {
+            ++small;
+            quick = quick && op.n <= pat::kSmallThreads;
+        } else {
+            halo = halo || pat::halo_step_supported(pr, RB, op);
+            quick = quick && tile > 0 && op.rdir && (op.n + tile - 1) / tile <= pat::kFewGroups;
+        }
     }
-    return small && (small == P.size() || halo || !pat::multi_step_supported(pr, RB)) ? 2 : 1;
+    const bool merge = pat::multi_step_supported(pr, RB) && small < P.size() && !halo && !quick;
+    return small && !merge ? 2 : 1;
 }
 
 // One RHS block's least-squares solve, split into the phases between sweeps so

@@ -71,6 +71,8 @@ def test_merged_blocks(meshes, prec, rb):
 @pytest.mark.parametrize("names,prec,rb,expect", [
     ("acb", "f32", 8, MERGED),          # the small meshes' tiles ride along with the larger one's
     ("ab", "f32", 8, WHOLE),            # nothing to ride along with
+    ("ad", "f32", 8, WHOLE | TURNS),    # one row per thread beside launches with few waves
+    ("bc", "f64", 16, WHOLE | TURNS),
     ("acb", "f32", 2, WHOLE | {"k_fwd", "k_adj"}),  # too narrow to merge
     ("cd", "f32", 8, MERGED),
 ])
